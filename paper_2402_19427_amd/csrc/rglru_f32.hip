@@ -32,6 +32,8 @@ struct CoeffArgs {
   int t_lo, n, nrun;     // the chunk of steps in hand
   float *A, *Bv;         // [B][n][D]
   float2 *agg;           // [B][nrun][D]
+  const float *h0;       // first piece: copied into `cell`, or null
+  float *cell;
 };
 
 // MAXT: column tiles of 16 outputs per wave (a block of up to 64 MAXT channels); RT: runs per workgroup
@@ -141,6 +143,7 @@ __global__ void __launch_bounds__(NTHREADS) f32_coeff_kernel(CoeffArgs a) {
     const int ct = wv + 4 * q;
     if (ct >= ntile) break;
     const int c = ct * 16 + j, d = g * bs + c;
+    if (a.h0 && run == 0 && kq == 0) a.cell[(size_t)b * D + d] = a.h0[(size_t)b * D + d];
     const float ba = p.b_a[d], bx = p.b_x[d], neg_cs = -p.c * softplus_f(-p.Lambda[d]);
 #pragma unroll
     for (int m = 0; m < RT; ++m) {
@@ -190,7 +193,8 @@ struct ApplyArgs {
   float *fin;            // [B][D] or null: the state after the chunk's last step
 };
 // MERGE: 0, or the merge as epilogue (1: exact GeLU, 2: tanh form). A workgroup: 64 channels x 4 runs;
-// with `last`, one more row of workgroups writes the Conv1D ring.
+// with `last`, one more row of workgroups writes the Conv1D ring. Every run reads `init` while the last
+// one writes `fin`, in no order: the two are never the same memory (launch_forward_f32).
 template <int MERGE>
 __global__ void __launch_bounds__(NTHREADS) f32_apply_kernel(ApplyArgs a) {
   const Problem &p = a.p;
@@ -246,13 +250,16 @@ __global__ void __launch_bounds__(NTHREADS) f32_apply_kernel(ApplyArgs a) {
 }
 
 struct Plan {
-  size_t off_A, off_B, off_agg, off_in, off_carry, total;
+  size_t off_A, off_B, off_agg, off_in, off_cell[2], total;
 };
 Plan plan(int B, int n, int D) {
   const size_t nrun = (size_t)(n + FT - 1) / FT;
   Plan q;
   size_t off = 256;
-  q.off_carry = off; off += align256((size_t)B * D * 4);
+  for (int k = 0; k < 2; ++k) {
+    q.off_cell[k] = off;
+    off += align256((size_t)B * D * 4);
+  }
   q.off_A = off; off += align256((size_t)B * n * D * 4);
   q.off_B = off; off += align256((size_t)B * n * D * 4);
   q.off_agg = off; off += align256((size_t)B * nrun * D * 8);
@@ -286,7 +293,7 @@ int chunk_that_fits(int B, int T, int D, size_t bytes) {
 }  // namespace
 
 size_t forward_f32_ws_bytes(int B, int T, int D) {
-  const size_t most = 256 + align256((size_t)4 * B * D) + ((size_t)128 << 20), all = plan(B, T, D).total;
+  const size_t most = 256 + 2 * align256((size_t)4 * B * D) + ((size_t)128 << 20), all = plan(B, T, D).total;
   return all < most ? all : most;
 }
 bool forward_f32_supported(const Problem &p, bool bf) {
@@ -300,14 +307,19 @@ hipError_t launch_forward_f32(const Problem &p, hipStream_t s) {
   const Plan q = plan(p.B, n, p.D);
   char *ws = (char *)p.ws;
   hipError_t e;
-  float *carry = (float *)(ws + q.off_carry);
-  for (int t_lo = 0; t_lo < p.T; t_lo += n) {
+  // The state in front of a piece lies in one of two cells of the scratch, the one behind it in the other
+  // or, after the last piece, in hT: what a launch reads is never what it writes. h0 may be the same
+  // array as hT, so the first piece's coefficient pass copies it into a cell.
+  float *cell[2] = {(float *)(ws + q.off_cell[0]), (float *)(ws + q.off_cell[1])};
+  for (int t_lo = 0, k = 0; t_lo < p.T; t_lo += n, k ^= 1) {
     CoeffArgs c;
     c.p = p;
     c.t_lo = t_lo;
     c.n = p.T - t_lo < n ? p.T - t_lo : n;
     c.nrun = (c.n + FT - 1) / FT;
     c.A = (float *)(ws + q.off_A); c.Bv = (float *)(ws + q.off_B); c.agg = (float2 *)(ws + q.off_agg);
+    c.h0 = t_lo == 0 ? p.h0 : nullptr;
+    c.cell = cell[0];
     {
       KernelTimer kt("f32_coeff_kernel", s);
       // four runs per workgroup from two workgroups per CU on
@@ -323,8 +335,8 @@ hipError_t launch_forward_f32(const Problem &p, hipStream_t s) {
     y.t_lo = t_lo; y.n = c.n; y.nrun = c.nrun;
     y.last = t_lo + c.n == p.T;
     y.A = c.A; y.Bv = c.Bv; y.agg = c.agg;
-    y.init = t_lo == 0 ? p.h0 : carry;
-    y.fin = y.last ? p.hT : carry;
+    y.init = t_lo > 0 || p.h0 ? cell[k] : nullptr;
+    y.fin = y.last ? p.hT : cell[k ^ 1];
     y.in = nullptr;
     if (c.nrun > MAX_DIRECT) {
       float *in = (float *)(ws + q.off_in);

@@ -155,6 +155,40 @@ def test_fp32_forward_in_runs(B, T, bs, nb, merge):
     np.testing.assert_array_equal(gen.chrono_from_ring(rn.to_host(st), 5 + T), st_ref)
 
 
+@pytest.mark.parametrize("B,T,bs,nb,steps", [(2, 1000, 64, 4, None), (1, 1024, 128, 8, None),   # one piece of 63, 64 runs
+                                             (3, 250, 64, 4, 48), (2, 1000, 64, 2, 240), (1, 4100, 32, 2, 1040)])
+@pytest.mark.parametrize("merge", [False, True])
+def test_fp32_forward_state_in_place_and_in_pieces(B, T, bs, nb, steps, merge):
+    """hT in the memory of h0, over many workgroups; `steps`: scratch for that many steps at a time (pieces
+    of 3, 15 and 65 runs, at least two of them neither first nor last)."""
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D, act, pos0 = bs * nb, "f32", 5
+    inp = gen.make_inputs(B, T, D, nb, act=act, seed=T + bs, h0=True, state=True, bias=True)
+    br = gen.make_branch(B, T, D, act=act, seed=T)
+    dp = rn.DeviceProblem(inp, B, T, D, nb, act)
+    u, h = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32")
+    ring = rn.to_device(gen.ring_from_chrono(inp["state"], pos0), act)
+    sh, y, out = dp.shape(), dp.empty_act(B, T, D), dp.empty_act(B, T, D)
+    n = R.rglru_workspace_bytes(sh, R.OP_FORWARD_MERGE if merge else R.OP_FORWARD)
+    if steps:   # two states, two coefficients per step, the runs' aggregates and (beyond 64 runs) states
+        al, nrun = (lambda v: (v + 255) // 256 * 256), -(-steps // 16)
+        n = 256 + 2 * al(4 * B * D) + 2 * al(4 * B * steps * D) + al(8 * B * nrun * D) + (al(4 * B * nrun * D) if nrun > 64 else 0)
+    ws = dp.empty_f32(n // 4)
+    if merge:
+        R.rglru_forward_merge(sh, dp.params, u, rn.to_device(br, act), h, ring, pos0, 0, out, y, h, ring, ws, n)
+    else:
+        R.rglru_forward(sh, dp.params, u, h, ring, pos0, y, h, ring, ws, n)
+    q = f64(inp)
+    y_ref, hT_ref, st_ref = oracle.forward(q["u"], q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"],
+                                           conv_b=q["conv_b"], h0=q["h0"], state_in=q["state"])
+    assert gen.rel_err(rn.to_host(y), y_ref) < F32
+    assert gen.rel_err(rn.to_host(h), hT_ref) < F32
+    if merge:
+        assert gen.rel_err(rn.to_host(out), oracle.merge(y_ref, br)) < F32
+    np.testing.assert_array_equal(gen.chrono_from_ring(rn.to_host(ring), pos0 + T), st_ref)
+
+
 @pytest.mark.parametrize("B,T,D", [(60, 300, 256), (30, 515, 256), (20, 1030, 256), (1, 4100, 256)])   # 4, 8 and 16 slices, rings that wrap
 @pytest.mark.parametrize("adjoint", [False, True])
 def test_scan_slices(B, T, D, adjoint):
