@@ -256,9 +256,9 @@ __global__ void __launch_bounds__(NTHREADS) cg_fused_kernel(Problem p) {
         const float u0 = un[tt];
         const float v = tt < nt ? fmaf(w0, u0, fmaf(w1, u1, fmaf(w2, u2, fmaf(w3, u3, cbias)))) : 0.f;
         xf[tt * nin + k] = v;
-        const _Float16 vh = (_Float16)v;
+        const _Float16 vh = (_Float16)mfma::f16_range(v);   // (finite past half precision's range: stays finite)
         xh[tt * xsh + k] = vh;
-        xl[tt * xsh + k] = (_Float16)(v - (float)vh);
+        xl[tt * xsh + k] = (_Float16)mfma::f16_range(v - (float)vh);
         u3 = u2;
         u2 = u1;
         u1 = u0;

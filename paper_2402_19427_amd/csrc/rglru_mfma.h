@@ -89,6 +89,10 @@ __device__ __forceinline__ void split_f16(float x0, float x1, unsigned &hi_pk, u
   hi_pk = pack_f16(x0, x1);
   lo_pk = pack_f16(x0 - f16_lo(hi_pk), x1 - f16_hi(hi_pk));
 }
+// finite values stop at the largest half, infinities and NaNs stay
+__device__ __forceinline__ float f16_range(float v) {
+  return fabsf(v) < __builtin_huge_valf() ? __builtin_amdgcn_fmed3f(v, -65504.f, 65504.f) : v;
+}
 // eight bf16 weights (an MFMA fragment as it lies in memory) as half precision
 __device__ __forceinline__ f16x8 w_to_f16(bf16x8 w) {
   const u32x4_t v = __builtin_bit_cast(u32x4_t, w);

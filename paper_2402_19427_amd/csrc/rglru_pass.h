@@ -40,10 +40,7 @@ __device__ __forceinline__ unsigned f16_bits(float v) {   // round to nearest
   return (unsigned)__builtin_bit_cast(unsigned short, (_Float16)v);
 }
 __device__ __forceinline__ unsigned pack_rn(float lo, float hi) { return f16_bits(lo) | (f16_bits(hi) << 16); }
-// the same without overflow: finite values stop at the largest half, infinities and NaNs stay
-__device__ __forceinline__ float f16_range(float v) {
-  return fabsf(v) < __builtin_huge_valf() ? __builtin_amdgcn_fmed3f(v, -65504.f, 65504.f) : v;
-}
+// the same without overflow
 __device__ __forceinline__ unsigned pack_sat(float lo, float hi) { return pack_rn(f16_range(lo), f16_range(hi)); }
 __device__ __forceinline__ float neg_c_softplus(float lam, float c) {   // log of the fully open decay, eq. (3)
   const float z = -lam;
@@ -57,8 +54,9 @@ __device__ __forceinline__ unsigned xcd_id() {
 }
 
 // x = Conv1D(u) for steps [t_lo, t_lo + n) of every sequence as [B][n][D] in half precision, xl (may
-// be null): the low part
-hipError_t launch_conv_rows(const Problem &p, unsigned short *xh, unsigned short *xl, int t_lo, int n, hipStream_t s);
+// be null): the low part. `operand`: xh only feeds products, and finite values past half precision's range stay
+// finite there.
+hipError_t launch_conv_rows(const Problem &p, unsigned short *xh, unsigned short *xl, bool operand, int t_lo, int n, hipStream_t s);
 
 // states entering the runs [B][nrun][D] and after the last one (fin, may be null) from the runs' aggregates
 hipError_t launch_chain_forward(const float2 *agg, const float *init, float *in, float *fin, int B, int D, int nrun,

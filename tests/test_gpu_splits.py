@@ -184,8 +184,8 @@ def test_fp32_forward_state_in_place_and_in_pieces(B, T, bs, nb, steps, merge):
                                            conv_b=q["conv_b"], h0=q["h0"], state_in=q["state"])
     assert gen.rel_err(rn.to_host(y), y_ref) < F32
     assert gen.rel_err(rn.to_host(h), hT_ref) < F32
-    if merge:
-        assert gen.rel_err(rn.to_host(out), oracle.merge(y_ref, br)) < F32
+    if merge:   # the error of y times |GeLU(z)| <= |z|
+        assert np.all(np.abs(rn.to_host(out) - oracle.merge(y_ref, br)) <= F32 * np.abs(br) * (np.abs(y_ref) + np.sqrt(np.mean(y_ref ** 2))))
     np.testing.assert_array_equal(gen.chrono_from_ring(rn.to_host(ring), pos0 + T), st_ref)
 
 
@@ -240,6 +240,48 @@ def test_layer_passes_keep_a_nan_of_a_gate(bs):
     np.testing.assert_array_equal(np.isnan(rn.to_host(y)), np.isnan(y_ref))
     for k in ("db_a", "db_x", "dLambda", "dW_a", "dW_x", "du"):
         np.testing.assert_array_equal(np.isnan(rn.to_host(got[k])), np.isnan(ref[k]), err_msg=k)
+
+
+def _large(inp, t0):
+    """A few inputs past half precision's 65504, through the Conv1D unchanged."""
+    inp["conv_w"][:] = 0.0
+    inp["conv_w"][0] = 1.0
+    inp["conv_b"][:] = 0.0
+    for t, d, v in ((t0, 3, 9e4), (t0, 40, -7e4), (t0 + 9, 17, -1.25e5)):
+        inp["u"][0, t, d] = gen.round_to_act(np.float32([v]), "bf16")[0]
+
+
+@pytest.mark.parametrize("T,hs", [(40, 128), (300, 128), (300, 48)])   # fused forward, passes
+def test_complex_gated_inputs_past_half_precision(T, hs):
+    rn = runner()
+    B, nb, act = 1, 2, "bf16"
+    inp = gen.make_cg_inputs(B, T, 2 * hs * nb, nb, act=act, seed=T + hs, bias=True, dy=True)
+    _large(inp, 20)
+    dp, q = rn.CgDeviceProblem(inp, B, T, 2 * hs * nb, nb, act), f64(inp)
+    w = (q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["theta"])
+    u = rn.to_device(inp["u"], act)
+    y, hT, _ = dp.forward(u)
+    y_ref, hT_ref, _ = oracle.cg_forward(q["u"], *w, conv_w=q["conv_w"])
+    got = dp.backward(u, rn.to_device(inp["dy"], act))
+    ref = oracle.cg_backward(q["u"], *w, q["dy"], conv_w=q["conv_w"])
+    assert gen.rel_err(rn.to_host(y), y_ref) < BF16 and gen.rel_err(rn.to_host(hT), hT_ref) < BF16
+    for k in ref:
+        assert gen.rel_err(rn.to_host(got[k]), ref[k]) < BF16, k
+
+
+def test_layer_passes_stay_finite_past_half_precision():
+    """In the backward of 160-channel blocks x in half precision feeds products only: an x past its range
+    closes or opens gates, it puts no infinity into them. (No reference: with m_t = 0 the oracle has 0 / 0.)"""
+    rn = runner()
+    B, T, bs, nb, act = 1, 300, 160, 2, "bf16"
+    inp = gen.make_inputs(B, T, bs * nb, nb, act=act, seed=7, dy=True, bias=True)
+    _large(inp, 20)
+    dp = rn.DeviceProblem(inp, B, T, bs * nb, nb, act)
+    u = rn.to_device(inp["u"], act)
+    y, _, _ = dp.forward(u)
+    got = dp.backward(u, y, rn.to_device(inp["dy"], act))
+    for k, v in got.items():
+        assert np.all(np.isfinite(rn.to_host(v))), k
 
 
 @pytest.mark.parametrize("bs", [160, 352])
