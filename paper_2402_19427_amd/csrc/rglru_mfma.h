@@ -146,16 +146,27 @@ __device__ __forceinline__ u64 peek(const u64 *slot) {
 __device__ __forceinline__ unsigned rec_epoch(u64 r) { return (unsigned)(r >> 62); }
 __device__ __forceinline__ float rec_A(u64 r) { return __uint_as_float((unsigned)(r >> 32) & 0x3fffffffu); }
 __device__ __forceinline__ float rec_H(u64 r) { return __uint_as_float((unsigned)r); }
-// The same for decays that a caller supplies: products in [0, 1] exactly as above; what a decay
-// outside its range makes of A travels in the codes above 1.0 (0x3f800000) with its sign, exponent
-// and 14 bits of its significand.
-__device__ __forceinline__ void publish_any(u64 *slot, float A, float H, unsigned epoch) {
-  const unsigned w = __float_as_uint(A);
-  publish_word(slot, w <= 0x3f800000u ? w : 0x3f800001u + min(w >> 9, 0x7ffffeu), A == A ? H : A, epoch);
+// The same for decays that a caller supplies: a product outside [0, 1] has no room in the word. It goes to
+// a side ring of the same depth first, and the record holds a code above 1.0 that says so; release and
+// acquire order the two, so the side word needs no mark of its own and no clearing. (Such decays are outside
+// the documented range; the branch costs a compare per record.)
+constexpr unsigned A_ASIDE = 0x3fffffffu;
+__device__ __forceinline__ void publish_any(u64 *slot, unsigned *side, float A, float H, unsigned epoch) {
+  unsigned w = __float_as_uint(A);
+  if (w > 0x3f800000u) {
+    __hip_atomic_store(side, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    w = A_ASIDE;
+  }
+  publish_word(slot, w, H, epoch);
 }
-__device__ __forceinline__ float rec_A_any(u64 r) {
-  const unsigned w = (unsigned)(r >> 32) & 0x3fffffffu;
-  return __uint_as_float(w <= 0x3f800000u ? w : (w - 0x3f800001u) << 9);
+__device__ __forceinline__ float rec_A_any(u64 r, const unsigned *side) {
+  unsigned w = (unsigned)(r >> 32) & 0x3fffffffu;
+  if (w == A_ASIDE) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    w = __hip_atomic_load(side, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  return __uint_as_float(w);
 }
 
 // Where the records of n consecutive tiles k0 .. k0 + n - 1 (in the order they are applied) lie.

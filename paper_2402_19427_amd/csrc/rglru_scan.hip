@@ -95,6 +95,7 @@ struct ScanArgs {
   ScanProblem p;
   int G, ntile, R, ncg;   // time slices, tiles per sequence, record ring depth, channel groups
   u64 *rec;               // [unit][R][256] records, zeroed before launch
+  unsigned *side;         // [unit][R][256] products outside [0, 1] (publish_any)
   int *err;
   int swizzle;
 };
@@ -199,6 +200,7 @@ scan_tiled_kernel(ScanArgs a) {
   const int a_off = arow * XS + hf * 8 + (2 * wv) * 16;   // the wave's own two K-steps
 
   u64 *ring = GMAX > 1 ? a.rec + (size_t)unit * a.R * BS + ch : nullptr;
+  unsigned *side = GMAX > 1 ? a.side + (size_t)unit * a.R * BS + ch : nullptr;
   float carry = p.h0 ? p.h0[(size_t)b * D + d] : 0.f;  // state after this workgroup's previous tile
   // (a workspace that still reports an expired wait of an earlier call: no waiting, NaN throughout)
   int spins = (GMAX > 1 && expired_before(a.err)) ? SPIN_LIMIT : 0;
@@ -233,7 +235,8 @@ scan_tiled_kernel(ScanArgs a) {
 #pragma unroll
       for (int s = 0; s < NREC; ++s) {
         unsigned want;
-        const u64 *slot = ring + (size_t)wk.slot_at(s, want) * BS;
+        const size_t at = (size_t)wk.slot_at(s, want) * BS;
+        const u64 *slot = ring + at;
         const bool has = wk.has(s, a.ntile);
         while (has && rec_epoch(rec[s]) != want && spins < SPIN_LIMIT) {
           ++spins;
@@ -241,7 +244,7 @@ scan_tiled_kernel(ScanArgs a) {
           rec[s] = peek(slot);
         }
         if (spins < SPIN_LIMIT) spins = 0;   // the limit is per wait; an expired wait stays expired
-        const float A = has ? rec_A_any(rec[s]) : 1.f, H = has ? rec_H(rec[s]) : 0.f;
+        const float A = has ? rec_A_any(rec[s], side + at) : 1.f, H = has ? rec_H(rec[s]) : 0.f;
         rH = fmaf(A, rH, H);
         rA *= A;
       }
@@ -328,7 +331,8 @@ scan_tiled_kernel(ScanArgs a) {
     if (GMAX > 1) {
       // the other slices wait for this aggregate, not for the outputs: publish first, then
       // finish the tile parked one iteration ago
-      if (hf == 0) publish_any(ring + slot_of(tile, a.R) * BS, agg[PAR][2], agg[PAR][3], epoch_of(tile, a.R));
+      const size_t at = slot_of(tile, a.R) * BS;
+      if (hf == 0) publish_any(ring + at, side + at, agg[PAR][2], agg[PAR][3], epoch_of(tile, a.R));
       if (held >= 0) resolve(held, std::integral_constant<int, PAR ^ 1>{});
       held = tile;
     } else {
@@ -403,6 +407,15 @@ bool scan_tiled_supported(const ScanProblem &p, bool bf) {
 
 // Workspace: one record ring per unit when the sequences are sliced in time. Sized for the
 // worst case of 256 compute units so that it does not depend on the device.
+// Slots of a unit's rings: the power of two from 5 G on, so that records and side words, 12 bytes a slot,
+// fit the 128 G bytes per channel of ring_bytes for every G up to 16 (R <= 10 G; 8 for G = 1). Fewer than 5 G
+// would not do: the slowest reader of a slot is that far behind its next writer (rglru_mfma.h).
+static int scan_ring_depth(int G) {
+  int R = 8;
+  while (R < 5 * G) R *= 2;
+  return R;
+}
+
 size_t scan_tiled_ws_bytes(int B, int T, int D) {
   const int units = B * (D / BS), ntile = (T + TT - 1) / TT;
   const int G = pick_slices(units, ntile, 256, SCAN_MAX_SLICES);
@@ -419,7 +432,7 @@ hipError_t launch_scan_tiled(const ScanProblem &p, hipStream_t s) {
   int ncu = num_cu();
   if (ncu > 256) ncu = 256;  // the workspace is sized for at most 256 resident workgroups
   a.G = pick_slices(units, a.ntile, ncu, SCAN_MAX_SLICES);
-  a.R = ring_depth(a.G);
+  a.R = scan_ring_depth(a.G);
   const int grid = units * a.G;
   a.swizzle = (a.G > 1 && grid % 8 == 0) ? 1 : 0;
   if (a.G == 1) {
@@ -433,6 +446,7 @@ hipError_t launch_scan_tiled(const ScanProblem &p, hipStream_t s) {
   }
   a.err = (int *)p.ws;
   a.rec = (u64 *)((char *)p.ws + 256);
+  a.side = (unsigned *)(a.rec + (size_t)units * a.R * BS);
   hipError_t e = launch_prep(p.ws, 256 + (size_t)units * a.R * BS * sizeof(u64), s, true);
   if (e != hipSuccess) return e;
   // (an instance asks for GMAX / 2 records per lane half whatever G is)

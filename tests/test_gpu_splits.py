@@ -208,9 +208,9 @@ def test_scan_slices(B, T, D, adjoint):
 
 @pytest.mark.parametrize("B,T", [(20, 1030), (1, 4100)])
 def test_scan_slices_with_decays_outside_their_range(B, T):
-    """Negative decays and decays above one (unscaled input): a slice hands on a product outside [0, 1]
-    with 14 bits of its significand; 2^-14 of a state that shrinks by more than half per tile of 32
-    steps adds up to less than 2^-13, next to the 2^-8 of the stored result (twice that for sums that cancel)."""
+    """Negative decays and decays above one (unscaled input): products outside [0, 1] pass from slice to slice
+    in fp32 too. The state remembers some 30 steps, each with two roundings of 2^-24; twice that for sums that
+    cancel, next to the 2^-8 of the stored result."""
     import paper_2402_19427_amd as R
     rn = runner()
     inp = gen.make_scan_inputs(B, T, 256, act="bf16", seed=B + T)
@@ -220,7 +220,27 @@ def test_scan_slices_with_decays_outside_their_range(B, T):
                     flags=R.SCAN_NO_INPUT_SCALE, act="bf16")
     ref, end_ref = oracle.scan(a, inp["g"], inp["h0"], normalize=False)
     assert gen.rel_err(rn.to_host(h), ref) < 2.0 ** -7
-    assert gen.rel_err(rn.to_host(hT), end_ref) < 2.0 ** -11
+    assert gen.rel_err(rn.to_host(hT), end_ref) < 120 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("B,T,adjoint", [(1, 8192, False), (1, 8192, True), (5, 6000, False), (12, 5000, True)])   # 16, 16, 16 and 10 slices
+def test_scan_slices_with_slowly_growing_products(B, T, adjoint):
+    """Decays barely above one: the product of a tile of 32 steps, 1 + 5.8e-5, must not lose the bits that
+    make the state grow by 1.5 % over the sequence. Each step's decay is an fp32 number beside one, off by
+    2^-23 at most, as is its product: 2^-22 per step."""
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D = 256 if B < 12 else 512
+    inp = gen.make_scan_inputs(B, T, D, act="bf16", seed=B + T)
+    log_a = np.full(inp["a"].shape, gen.round_to_act(np.float32([1.8e-6]), "bf16")[0], np.float32)
+    log_a[:, ::7] = gen.round_to_act(np.float32([-4e-7]), "bf16")[0]
+    g = gen.round_to_act(0.01 * inp["g"], "bf16")
+    flags = R.SCAN_LOG_A | R.SCAN_NO_INPUT_SCALE | (R.SCAN_ADJOINT if adjoint else 0)
+    h, hT = rn.scan(rn.to_device(log_a, "bf16"), rn.to_device(g, "bf16"), rn.to_device(inp["h0"], "f32"), flags=flags, act="bf16")
+    a = np.exp(log_a.astype(np.float64))
+    ref, end_ref = oracle.scan_adjoint(a, g, inp["h0"]) if adjoint else oracle.scan(a, g, inp["h0"], normalize=False)
+    assert gen.rel_err(rn.to_host(h), ref) < 2.0 ** -8 + T * 2.0 ** -22
+    assert gen.rel_err(rn.to_host(hT), end_ref) < T * 2.0 ** -22
 
 
 @pytest.mark.parametrize("bs", [160, 352])
