@@ -128,9 +128,15 @@ __device__ __forceinline__ void *uniform_ptr(const void *q) {
 // from a zero incoming state) of one channel is one 8-byte word, written and read atomically at
 // agent scope without fences: H below, A above. Decays lie in [0, 1], so the sign and the highest
 // exponent bit of A are zero and hold the epoch of the ring slot: no bit of A is given up. (A NaN
-// among the decays loses its mark there: H carries it.) A slot is used again every R tiles by the same
-// workgroup; epochs 1, 2, 3 take turns, a cleared slot has epoch 0, and a reader that follows the
-// ring has always seen the use before the one it waits for. One word for the pair instead of a
+// among the decays loses its mark there: H carries it.) A slot is used again every R tiles, by another
+// workgroup where G does not divide R; epochs 1, 2, 3 take turns and a cleared slot has epoch 0. What a
+// slot can hold when a reader wants tile k is k or, not yet replaced, k - R:
+//   - a workgroup that publishes tile t has resolved its tile t - 2 G, for which it consumed the G - 1
+//     tiles in front: every other workgroup has published one of t - 3 G + 1 .. t - 2 G - 1, has resolved
+//     its own tile 2 G before that, and so needs no tile below t - 5 G + 2 any more. With R >= 5 G tile
+//     t - R has been consumed by all of them;
+//   - the reader itself consumed k - R before, as it resolves its tiles in order.
+// One word for the pair instead of a
 // tagged word each halves the traffic of the exchange, which was what a tile of a finely sliced
 // sequence cost most (0.26 us per record consumed).
 __device__ __forceinline__ void publish_word(u64 *slot, unsigned a30, float H, unsigned epoch) {

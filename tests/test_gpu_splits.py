@@ -243,6 +243,34 @@ def test_scan_slices_with_slowly_growing_products(B, T, adjoint):
     assert gen.rel_err(rn.to_host(hT), end_ref) < T * 2.0 ** -22
 
 
+@pytest.mark.parametrize("G", [3, 5, 7])
+def test_time_slices_that_do_not_divide_the_ring(G):
+    """Rings of 32 and 64 slots over 210 tiles: a slot changes hands between workgroups with every use."""
+    import paper_2402_19427_amd as R
+    rn = runner()
+    B, T, D, act = 1, 6700, 256, "bf16"
+    inp = gen.make_inputs(B, T, D, 1, act=act, seed=G, h0=True, dy=True, bias=True)
+    q = f64(inp)
+    w = (q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"])
+    si = gen.make_scan_inputs(B, T, D, act=act, seed=G)
+    R.rglru_set_max_time_slices(G)
+    try:
+        dp = rn.DeviceProblem(inp, B, T, D, 1, act)
+        u, h0, dhT = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32"), rn.to_device(inp["dhT"], "f32")
+        y, hT, _ = dp.forward(u, h0=h0)
+        got = dp.backward(u, y, rn.to_device(inp["dy"], act), h0=h0, dhT=dhT)
+        h, end = rn.scan(*(rn.to_device(si[k], act) for k in ("a", "g")), rn.to_device(si["h0"], "f32"), act=act)
+    finally:
+        R.rglru_set_max_time_slices(0)
+    y_ref, hT_ref, _ = oracle.forward(q["u"], *w, conv_b=q["conv_b"], h0=q["h0"])
+    ref = oracle.backward(q["u"], *w, q["dy"], conv_b=q["conv_b"], h0=q["h0"], dhT=q["dhT"])
+    h_ref, _ = oracle.scan(si["a"], si["g"], si["h0"])
+    assert gen.rel_err(rn.to_host(y), y_ref) < BF16 and gen.rel_err(rn.to_host(hT), hT_ref) < BF16
+    assert gen.rel_err(rn.to_host(h), h_ref) < 2.0 ** -8
+    for k in ref:
+        assert gen.rel_err(rn.to_host(got[k]), ref[k]) < BF16, k
+
+
 @pytest.mark.parametrize("bs", [160, 352])
 def test_layer_passes_keep_a_nan_of_a_gate(bs):
     """A NaN in one channel's gate reaches every gradient it reaches in the oracle, and no other."""
