@@ -1045,7 +1045,7 @@ hipError_t launch_cg_backward_pass(const Problem &p, hipStream_t s) {
     hipLaunchKernelGGL(cg_dgrad_kernel, dim3(grid8(d.total)), dim3(256), C_LDS, s, d);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = launch_conv_adjoint(p, dx, true, nullptr, (float *)(ws + q.off_partC), s)) != hipSuccess) return e;
+  if ((e = launch_conv_adjoint(p, dx, (float *)(ws + q.off_partC), s)) != hipSuccess) return e;
   {
     KernelTimer kt("cg_wgrad_kernel", s);
     CgWgradArgs w;
@@ -1057,7 +1057,7 @@ hipError_t launch_cg_backward_pass(const Problem &p, hipStream_t s) {
   }
   FinishArgs f;
   f.partW = (const float *)(ws + q.off_partW); f.partA = (const float *)(ws + q.off_partA);
-  f.partC = (const float *)(ws + q.off_partC); f.sc = nullptr;
+  f.partC = (const float *)(ws + q.off_partC); f.sc = nullptr; f.edge = nullptr;
   f.S = q.S; f.nA = p.B * q.n128; f.nrA = 4; f.DA = p.D / 2; f.nC = p.B * q.n256; f.D = p.D; f.nb = p.nb;
   f.bb = (size_t)p.bs * 2 * p.bs;
   f.dW[0] = p.g.dW_a; f.dW[1] = p.g.dW_x;

@@ -62,17 +62,20 @@ hipError_t launch_conv_rows(const Problem &p, unsigned short *xh, unsigned short
 hipError_t launch_chain_forward(const float2 *agg, const float *init, float *in, float *fin, int B, int D, int nrun,
                                 hipStream_t s);
 
-// The adjoint of the Conv1D (conv_adjoint_kernel): du, and partial sums [B][ceil(T / 256)][5][D]; dx in
-// half precision times S (sc[2] = 1 / S), or in fp32 (sc null)
-hipError_t launch_conv_adjoint(const Problem &p, const void *dx, bool fp32, const float *sc, float *part, hipStream_t s);
+// The adjoint of the Conv1D (conv_adjoint_kernel): du, and partial sums [B][ceil(T / 256)][5][D]
+hipError_t launch_conv_adjoint(const Problem &p, const float *dx, float *part, hipStream_t s);
 
 // Partial sums in a fixed order: dW from S slices of [g][gate][bb] (times sc[2] if sc), rowsA from nA
-// rows of nrA vectors of DA channels, rowsC from nC rows of five vectors of D channels
+// rows of nrA vectors of DA channels, rowsC from nC rows of five vectors of D channels; with `edge` (S dx of the
+// first and last three rows of every tile of 256, [B][nrt][6][D]) the rows of du that two tiles share
 struct FinishArgs {
   const float *partW, *partA, *partC, *sc;
   int S, nA, nrA, DA, nC, D, nb;
   size_t bb;             // elements of one gate matrix of a block (a multiple of 4)
   float *dW[2], *rowsA[4], *rowsC[5];
+  const float *edge, *conv_w;
+  unsigned short *du;
+  int B, T, nrt;
 };
 hipError_t launch_finish(const FinishArgs &a, hipStream_t s);
 

@@ -345,3 +345,38 @@ def test_layer_passes_round_what_they_store(bs):
     got = dp.backward(u, y, rn.to_device(inp["dy"], act))
     ref = oracle.backward(q["u"], *(q[k] for k in ("W_a", "W_x", "b_a", "b_x", "Lambda", "conv_w")), q["dy"], conv_b=q["conv_b"])
     assert np.linalg.norm(rn.to_host(got["dconv_b"]) - ref["dconv_b"]) < 2.0 ** -11 * np.linalg.norm(ref["dconv_b"])
+
+
+def _smooth(B, T, bs, nb, seed):
+    """Gates and decay that do not depend on the input, an upstream gradient and inputs that do not change
+    over time: the adjoints vary slowly from step to step."""
+    D = bs * nb
+    inp = gen.make_inputs(B, T, D, nb, act="bf16", seed=seed, dy=True)
+    inp["W_a"][:] = 0.0
+    inp["W_x"][:] = 0.0
+    inp["b_a"][:] = 0.25
+    inp["b_x"][:] = 0.25
+    inp["Lambda"][:] = -np.log(np.expm1(0.001 / (8.0 / (1.0 + np.exp(-0.25)))))   # a = exp(-0.001)
+    for k in ("u", "dy"):
+        inp[k][:] = inp[k][:, :1]
+    return inp
+
+
+@pytest.mark.parametrize("T,bs,nb", [(600, 160, 2), (300, 240, 1), (600, 352, 8), (513, 64, 4), (300, 48, 16)])
+def test_input_gradient_is_a_difference_of_adjoints(T, bs, nb):
+    """Conv1D taps 1, -1: du is the difference of two neighbours that agree to one part in 200 and more.
+    dx is a chain of eight fp32 operations on adjoints that are summed over runs of 64 steps (64 roundings of
+    2^-24, then 8 more): 72 2^-24 of dx; half precision anywhere in between would leave 2^-12."""
+    rn = runner()
+    B, act, D = 2, "bf16", bs * nb
+    inp = _smooth(B, T, bs, nb, T + bs)
+    inp["conv_w"][:] = 0.0
+    inp["conv_w"][0], inp["conv_w"][1] = 1.0, -1.0
+    dp, q = rn.DeviceProblem(inp, B, T, D, nb, act), f64(inp)
+    w = [q[k] for k in ("W_a", "W_x", "b_a", "b_x", "Lambda", "conv_w")]
+    u = rn.to_device(inp["u"], act)
+    y, _, _ = dp.forward(u)
+    got = rn.to_host(dp.backward(u, y, rn.to_device(inp["dy"], act))["du"])
+    ref = oracle.backward(q["u"], *w, q["dy"])["du"]
+    dx = np.abs(np.cumsum(ref[:, ::-1], axis=1)[:, ::-1])   # dx_t = du_t + dx_{t+1}
+    assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 72 * 2.0 ** -24 * dx)
