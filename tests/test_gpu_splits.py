@@ -380,3 +380,20 @@ def test_input_gradient_is_a_difference_of_adjoints(T, bs, nb):
     ref = oracle.backward(q["u"], *w, q["dy"])["du"]
     dx = np.abs(np.cumsum(ref[:, ::-1], axis=1)[:, ::-1])   # dx_t = du_t + dx_{t+1}
     assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 72 * 2.0 ** -24 * dx)
+
+
+@pytest.mark.parametrize("bs,nb", [(128, 2), (160, 2), (240, 1)])
+def test_gates_logits_keep_their_bits(bs, nb):
+    """A gate that is open to the same degree in every step and channel: an error of its logit is the same in
+    all terms of db_x. r (1 - r) follows it one to one; fp32 leaves 2^-21 at a logit of 8, a few roundings
+    of the adjoint (bounded as above by 72 2^-24) and the hardware's exponentials (2^-20)."""
+    rn = runner()
+    B, T, act, D = 1, 300, "bf16", bs * nb   # (one sequence: terms of one sign)
+    inp = _smooth(B, T, bs, nb, bs)
+    inp["b_x"][:] = 8.0039
+    dp, q = rn.DeviceProblem(inp, B, T, D, nb, act), f64(inp)
+    u = rn.to_device(inp["u"], act)
+    y, _, _ = dp.forward(u)
+    got = rn.to_host(dp.backward(u, y, rn.to_device(inp["dy"], act))["db_x"])
+    ref = oracle.backward(q["u"], *(q[k] for k in ("W_a", "W_x", "b_a", "b_x", "Lambda", "conv_w")), q["dy"])["db_x"]
+    assert np.all(np.abs(got - ref) <= 2.0 ** -16 * np.abs(ref))
