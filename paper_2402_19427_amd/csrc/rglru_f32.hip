@@ -293,7 +293,8 @@ int chunk_that_fits(int B, int T, int D, size_t bytes) {
 }  // namespace
 
 size_t forward_f32_ws_bytes(int B, int T, int D) {
-  const size_t most = 256 + 2 * align256((size_t)4 * B * D) + ((size_t)128 << 20), all = plan(B, T, D).total;
+  // (the cap is the general kernels', whose scratch has one state: the second cell comes out of the pieces)
+  const size_t most = 256 + align256((size_t)4 * B * D) + ((size_t)128 << 20), all = plan(B, T, D).total;
   return all < most ? all : most;
 }
 bool forward_f32_supported(const Problem &p, bool bf) {
