@@ -191,21 +191,20 @@ size_t general_forward_bytes(const rglru_shape *s) {
   return s->act_dtype == RGLRU_F32 && s->T >= 1 ? std::max(n, forward_f32_ws_bytes(s->B, s->T, s->D)) : n;
 }
 
+// The least a backward call has to bring: the generic kernels are the fallback of the passes, for loosely
+// aligned pointers and for a workspace laid out before there were passes (on a few rows of a wide block
+// their partial sums and weight copies take more than everything the generic kernels need).
+size_t least_backward_bytes(const rglru_shape *s) {
+  if (s->act_dtype == RGLRU_BF16 && s->D / s->num_blocks == 256 && (size_t)s->T * s->D * 4 < ((size_t)1 << 32))
+    return backward_mfma_ws_bytes(s->B, s->T, s->D, s->num_blocks);
+  return std::max(backward_generic_ws_bytes(s->B, s->T, s->D, s->num_blocks),
+                  backward_pass_shape(s) ? narrow_backward_bytes(s) : 0);
+}
+
 size_t workspace_need(const rglru_shape *s, int op) {
   switch (op) {
     case RGLRU_OP_BACKWARD:
-      if (s->act_dtype == RGLRU_BF16 && s->D / s->num_blocks == 256 &&
-          (size_t)s->T * s->D * 4 < ((size_t)1 << 32))
-        return backward_mfma_ws_bytes(s->B, s->T, s->D, s->num_blocks);
-      {
-        // (the generic kernels remain the fallback for loosely aligned pointers)
-        size_t n = backward_generic_ws_bytes(s->B, s->T, s->D, s->num_blocks);
-        if (backward_pass_shape(s)) {
-          n = std::max(n, backward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks));
-          n = std::max(n, narrow_backward_bytes(s));
-        }
-        return n;
-      }
+      return std::max(least_backward_bytes(s), backward_pass_shape(s) ? backward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks) : 0);
     case RGLRU_OP_SCAN:
       if (s->act_dtype == RGLRU_BF16 && s->D % 256 == 0 && s->T >= 1)
         return scan_tiled_ws_bytes(s->B, s->T, s->D);
@@ -313,7 +312,7 @@ int backward_checks(const rglru_shape *shape, const rglru_params *params, const 
   CHECK(check_ptr(grads->dconv_w, "grads.dconv_w", 4, shape->conv_width != 0));
   CHECK(check_ptr(grads->dconv_b, "grads.dconv_b", 4, false));
   if (with_workspace)
-    CHECK(check_workspace(workspace, workspace_bytes, workspace_need(shape, RGLRU_OP_BACKWARD)));
+    CHECK(check_workspace(workspace, workspace_bytes, least_backward_bytes(shape)));
   return RGLRU_OK;
 }
 }  // namespace
@@ -839,7 +838,7 @@ int rglru_backward_merge(const rglru_shape *shape, const rglru_params *params, c
   CHECK(check_ptr(y, "y", as, true));
   CHECK(check_ptr(dout, "dout", as, true));
   CHECK(check_ptr(dbranch, "dbranch", as, true));
-  CHECK(check_workspace(workspace, workspace_bytes, workspace_need(shape, RGLRU_OP_BACKWARD_MERGE)));
+  CHECK(check_workspace(workspace, workspace_bytes, merge_dy_bytes(shape) + least_backward_bytes(shape)));
   if (dbranch == y || dbranch == u || dbranch == du)
     return fail(RGLRU_ERR_INVALID_ARG, "dbranch must not alias y, u or du");
   // the rest of the arguments are checked by rglru_backward before anything is launched:
@@ -957,7 +956,7 @@ int rglru_cg_backward(const rglru_shape *shape, const rglru_cg_params *params, c
   CHECK(check_ptr(grads->dtheta, "grads.dtheta", 4, true));
   CHECK(check_ptr(grads->dconv_w, "grads.dconv_w", 4, shape->conv_width != 0));
   CHECK(check_ptr(grads->dconv_b, "grads.dconv_b", 4, false));
-  CHECK(check_workspace(workspace, workspace_bytes, workspace_need(shape, RGLRU_OP_CG_BACKWARD)));
+  CHECK(check_workspace(workspace, workspace_bytes, cg_backward_ws_bytes(shape->B, shape->T, shape->D, shape->num_blocks)));
   Problem q;
   memset(&q, 0, sizeof(q));
   fill_cg_params(q, shape, params);

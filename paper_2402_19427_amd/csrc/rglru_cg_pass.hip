@@ -16,6 +16,8 @@
 // cache).
 #include "rglru_pass.h"
 
+#include <algorithm>
+
 namespace rglru {
 using namespace pass;
 
@@ -912,9 +914,13 @@ BwdPlan plan_bwd(int B, int T, int D, int nb) {
   size_t off = 0;
   q.off_xh = off; off += n2;
   q.off_xl = off; off += n2;
-  q.off_pq = off; off += 2 * n2;
   q.off_dph = off; off += n2;
   q.off_dpl = off; off += n2;
+  q.off_partA = off; off += al256((size_t)B * q.n128 * 4 * H * 4);
+  q.off_partC = off; off += al256((size_t)B * q.n256 * 5 * D * 4);
+  // from here on what the weight gradients' pass needs no more: its partial sums take the same room
+  q.off_partW = off;
+  q.off_pq = off; off += 2 * n2;
   q.off_dx = off; off += 2 * n2;
   q.off_w = off; off += al256((size_t)nb * hs * hs * 8);
   q.off_wt = off; off += al256((size_t)nb * hs * hs * 8);
@@ -922,9 +928,7 @@ BwdPlan plan_bwd(int B, int T, int D, int nb) {
   q.off_aggr = off; off += al256(sub * 16);
   q.off_hin = off; off += al256(sub * 8);
   q.off_ein = off; off += al256(sub * 8);
-  q.off_partA = off; off += al256((size_t)B * q.n128 * 4 * H * 4);
-  q.off_partC = off; off += al256((size_t)B * q.n256 * 5 * D * 4);
-  q.off_partW = off; off += al256((size_t)q.S * nb * 4 * hs * hs * 4);
+  off = std::max(off, q.off_partW + al256((size_t)q.S * nb * 4 * hs * hs * 4));
   q.total = off;
   return q;
 }
@@ -994,7 +998,8 @@ size_t cg_backward_pass_ws_bytes(int B, int T, int D, int nb) {
   return shape_ok(B, T, D, D / 2 / nb) ? plan_bwd(B, T, D, nb).total : 0;
 }
 bool cg_backward_pass_supported(const Problem &p) {
-  return shape_ok(p.B, p.T, p.D, p.bs) && aligned16(p) && (uintptr_t)p.du % 8 == 0;
+  return shape_ok(p.B, p.T, p.D, p.bs) && aligned16(p) && (uintptr_t)p.du % 8 == 0 &&
+         p.ws_bytes >= plan_bwd(p.B, p.T, p.D, p.nb).total;
 }
 hipError_t launch_cg_backward_pass(const Problem &p, hipStream_t s) {
   hipError_t e;

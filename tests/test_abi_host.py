@@ -347,3 +347,10 @@ def test_workspace_sizes_for_narrower_gate_blocks():
     for sh in (R.make_shape(8, 2048, 2560, 16, R.F32), R.make_shape(8, 2048, 2560, 64, R.BF16)):   # (bs 40)
         n = R.rglru_workspace_bytes(sh, R.OP_FORWARD)
         assert 0 < n <= 256 + 8 * 2560 * 4 + 2 * (64 << 20) + 1024 and n % 256 == 0
+
+
+@pytest.mark.parametrize("shape,op,was", [((1, 1, 2048, 1), "OP_BACKWARD", 33734912), ((1, 1, 4096, 2), "OP_BACKWARD", 67469568),
+                                          ((1, 1, 5632, 4), "OP_BACKWARD_MERGE", 63957248), ((32, 1, 2048, 64), "OP_BACKWARD", 4722944)])
+def test_backward_workspace_stays_what_it_was_for_few_rows(shape, op, was):
+    """A few rows of a wide block: the partial sums of the weight gradients take the room of what they no longer need."""
+    assert R.rglru_workspace_bytes(R.make_shape(*shape, R.BF16), getattr(R, op)) <= was

@@ -397,3 +397,54 @@ def test_gates_logits_keep_their_bits(bs, nb):
     got = rn.to_host(dp.backward(u, y, rn.to_device(inp["dy"], act))["db_x"])
     ref = oracle.backward(q["u"], *(q[k] for k in ("W_a", "W_x", "b_a", "b_x", "Lambda", "conv_w")), q["dy"])["db_x"]
     assert np.all(np.abs(got - ref) <= 2.0 ** -16 * np.abs(ref))
+
+
+@pytest.mark.parametrize("B,T,bs,nb,size", [(1, 1, 16, 16, 55552), (1, 1, 2048, 1, 33734912), (2, 40, 160, 2, None)])
+def test_backward_in_a_workspace_laid_out_before_the_passes(B, T, bs, nb, size):
+    """size: what the call asked for then; the general kernels take over where the passes do not fit it."""
+    import paper_2402_19427_amd as R
+    import torch
+    rn = runner()
+    D, act = bs * nb, "bf16"
+    inp = gen.make_inputs(B, T, D, nb, act=act, seed=bs, h0=True, dy=True, bias=True)
+    dp = rn.DeviceProblem(inp, B, T, D, nb, act)
+    u, h0, dy = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32"), rn.to_device(inp["dy"], act)
+    y, _, _ = dp.forward(u, h0=h0)
+    sh = dp.shape()
+    n = R.rglru_workspace_bytes(sh, R.OP_BACKWARD)
+    size = size or n
+    g = dp.alloc_grads()
+    pg = R.make_param_grads(*[g[k] for k in ("dW_a", "dW_x", "db_a", "db_x", "dLambda", "dconv_w", "dconv_b")])
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+    du, dh0 = dp.empty_act(B, T, D), dp.empty_f32(B, D)
+    R.rglru_backward(sh, dp.params, u, h0, None, 0, y, dy, None, du, dh0, pg, ws, size, None)
+    q = f64(inp)
+    ref = oracle.backward(q["u"], q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"], q["dy"], conv_b=q["conv_b"],
+                          h0=q["h0"])
+    for k, v in dict(g, du=du, dh0=dh0).items():
+        assert gen.rel_err(rn.to_host(v), ref[k]) < BF16, k
+
+
+@pytest.mark.parametrize("B,T,hs,nb,size", [(1, 17, 256, 1, 753664), (2, 17, 256, 2, 1966080)])
+def test_complex_gated_backward_in_a_workspace_laid_out_before_the_passes(B, T, hs, nb, size):
+    import paper_2402_19427_amd as R
+    import torch
+    rn = runner()
+    D, act = 2 * hs * nb, "bf16"
+    inp = gen.make_cg_inputs(B, T, D, nb, act=act, seed=hs, h0=True, dy=True)
+    cg = rn.CgDeviceProblem(inp, B, T, D, nb, act)
+    u, h0, dy = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32"), rn.to_device(inp["dy"], act)
+    need = R.rglru_workspace_bytes(cg.shape(), R.OP_CG_BACKWARD)
+    assert size < need
+    f32 = lambda *s: torch.empty(*s, dtype=torch.float32, device="cuda:0")
+    g = dict(dW_a=f32(nb, hs, 2 * hs), dW_x=f32(nb, hs, 2 * hs), db_a=f32(D // 2), db_x=f32(D // 2), dLambda=f32(D // 2),
+             dtheta=f32(D // 2), dconv_w=f32(4, D), dconv_b=f32(D))
+    pg = R.make_cg_param_grads(*g.values())
+    ws, du, dh0 = torch.empty(size, dtype=torch.uint8, device="cuda:0"), torch.empty_like(u), f32(B, D)
+    R.rglru_cg_backward(cg.shape(), cg.params, u, h0, None, 0, dy, None, du, dh0, pg, ws, size, None)
+    c = f64(inp)
+    ref = oracle.cg_backward(c["u"], c["W_a"], c["W_x"], c["b_a"], c["b_x"], c["Lambda"], c["theta"], c["dy"], conv_w=c["conv_w"],
+                             h0=c["h0"])
+    for k, v in dict(g, du=du, dh0=dh0).items():
+        if k in ref and ref[k] is not None and k != "dconv_b":
+            assert gen.rel_err(rn.to_host(v), ref[k]) < BF16, k
