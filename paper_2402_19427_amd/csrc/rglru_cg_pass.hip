@@ -88,6 +88,12 @@ __global__ void __launch_bounds__(256) cg_prep_kernel(CgPrepArgs a) {
   }
 }
 
+// n8 pieces of eight bf16 values to a 16-byte aligned place
+__global__ void __launch_bounds__(256) realign_kernel(const unsigned short *src, u32x4 *dst, size_t n8) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n8) dst[i] = *(const u32x4_at2 *)(src + i * 8);
+}
+
 // ------------------------------------------------------------------------ 2. gates
 struct CgGatesArgs {
   Problem p;                       // T: steps of the chunk in hand
@@ -419,8 +425,8 @@ __global__ void __launch_bounds__(256) cg_apply_kernel(CgApplyArgs a) {
         s[c] = make_float2(fmaf(gain, xr, t.x), fmaf(gain, xi, t.y));
       }
       unsigned short *o = y + (size_t)(r0 + e) * D;
-      *(unsigned *)o = pack_bf16(s[0].x, s[1].x);
-      *(unsigned *)(o + H) = pack_bf16(s[0].y, s[1].y);
+      *(u32_at2 *)o = pack_bf16(s[0].x, s[1].x);
+      *(u32_at2 *)(o + H) = pack_bf16(s[0].y, s[1].y);
     }
   }
   if (a.hT)
@@ -852,11 +858,6 @@ CgGatesArgs gates_args(const Problem &p, int T) {
   a.agg = a.aggf = a.aggr = nullptr;
   return a;
 }
-bool aligned16(const Problem &p) {
-  const uintptr_t all = (uintptr_t)p.W_a | (uintptr_t)p.W_x | (uintptr_t)p.u | (uintptr_t)p.dy | (uintptr_t)p.state_in |
-                        (uintptr_t)p.conv_w | (uintptr_t)p.conv_b;
-  return all % 16 == 0;
-}
 bool shape_ok(int B, int T, int D, int hs) {
   return hs % 16 == 0 && hs >= 16 && T >= 1 && B <= 65535 && (size_t)(T + PR) * D * 4 < ((size_t)1 << 31) &&
          (T + 127) / 128 <= 65535 && (size_t)B * ((T + PR - 1) / PR) * ((size_t)D / 16) < ((size_t)1 << 28);
@@ -943,7 +944,7 @@ size_t cg_forward_pass_ws_bytes(int B, int T, int D, int nb) {
 // With one run a sequence starts from h0 itself and three launches do; the passes are for sequences
 // of more than a run (the fused and general kernels are faster on a few tiles).
 bool cg_forward_pass_supported(const Problem &p) {
-  return p.T > RUN && shape_ok(p.B, p.T, p.D, p.bs) && aligned16(p) && (uintptr_t)p.y % 4 == 0 && p.ws && (uintptr_t)p.ws % 256 == 0 &&
+  return p.T > RUN && shape_ok(p.B, p.T, p.D, p.bs) && p.ws && (uintptr_t)p.ws % 256 == 0 &&
          p.ws_bytes >= plan_fwd(p.B, p.T < PR ? p.T : PR, p.D, p.nb).total;
 }
 hipError_t launch_cg_forward_pass(const Problem &p, hipStream_t s) {
@@ -997,15 +998,28 @@ hipError_t launch_cg_forward_pass(const Problem &p, hipStream_t s) {
 size_t cg_backward_pass_ws_bytes(int B, int T, int D, int nb) {
   return shape_ok(B, T, D, D / 2 / nb) ? plan_bwd(B, T, D, nb).total : 0;
 }
-bool cg_backward_pass_supported(const Problem &p) {
-  return shape_ok(p.B, p.T, p.D, p.bs) && aligned16(p) && (uintptr_t)p.du % 8 == 0 &&
-         p.ws_bytes >= plan_bwd(p.B, p.T, p.D, p.nb).total;
+// The staging of dy wants 16-byte aligned rows: any other dy is copied first, behind the plan (the size
+// reported for the call is the general kernels' where those need more, 24 bytes per element against 18).
+static size_t dy_copy_bytes(const Problem &p) {
+  return (uintptr_t)p.dy % 16 == 0 ? 0 : al256((size_t)p.B * p.T * p.D * 2);
 }
-hipError_t launch_cg_backward_pass(const Problem &p, hipStream_t s) {
+bool cg_backward_pass_supported(const Problem &p) {
+  return shape_ok(p.B, p.T, p.D, p.bs) && p.ws_bytes >= plan_bwd(p.B, p.T, p.D, p.nb).total + dy_copy_bytes(p);
+}
+hipError_t launch_cg_backward_pass(const Problem &call, hipStream_t s) {
   hipError_t e;
   if ((e = configure()) != hipSuccess) return e;
+  Problem p = call;
   const BwdPlan q = plan_bwd(p.B, p.T, p.D, p.nb);
   char *ws = (char *)p.ws;
+  if (dy_copy_bytes(p)) {
+    KernelTimer kt("realign_kernel", s);
+    const size_t n8 = (size_t)p.B * p.T * p.D / 8;
+    hipLaunchKernelGGL(realign_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, (const unsigned short *)call.dy,
+                       (u32x4 *)(ws + q.total), n8);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    p.dy = ws + q.total;
+  }
   unsigned short *xh = (unsigned short *)(ws + q.off_xh), *xl = (unsigned short *)(ws + q.off_xl),
                  *dph = (unsigned short *)(ws + q.off_dph), *dpl = (unsigned short *)(ws + q.off_dpl),
                  *w16 = (unsigned short *)(ws + q.off_w), *wt = (unsigned short *)(ws + q.off_wt);

@@ -14,6 +14,10 @@ constexpr unsigned OOB = 0x80000000u;   // buffer offset past every range: loads
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+// the same at any address a bf16 tensor may have (global memory takes such accesses; aligned ones cost the same)
+typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
+typedef u32x2 u32x2_at2 __attribute__((aligned(2)));
+typedef unsigned u32_at2 __attribute__((aligned(2)));
 
 // 16 bytes per lane from global memory into 1 KB of LDS at the wave-uniform address dst
 __device__ __forceinline__ void lds16(__amdgpu_buffer_rsrc_t rs, unsigned char *dst, unsigned vo, unsigned so) {

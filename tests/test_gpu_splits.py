@@ -448,3 +448,54 @@ def test_complex_gated_backward_in_a_workspace_laid_out_before_the_passes(B, T, 
     for k, v in dict(g, du=du, dh0=dh0).items():
         if k in ref and ref[k] is not None and k != "dconv_b":
             assert gen.rel_err(rn.to_host(v), ref[k]) < BF16, k
+
+
+def _at(t, off):
+    """The tensor's values `off` elements behind a 256-byte boundary."""
+    import torch
+    room = torch.empty(t.numel() + 128, dtype=t.dtype, device=t.device)
+    out = room[off:off + t.numel()].view(t.shape)
+    out.copy_(t)
+    return out
+
+
+@pytest.mark.parametrize("off", [1, 2, 4])
+def test_complex_gated_passes_at_any_alignment(off):
+    """u, dy, the carried ring and the Conv1D's parameters off the 16-byte grid: the matrix-core passes, the same results."""
+    import paper_2402_19427_amd as R
+    import torch
+    rn = runner()
+    B, T, hs, nb, act = 2, 300, 64, 2, "bf16"
+    D = 2 * hs * nb
+    inp = gen.make_cg_inputs(B, T, D, nb, act=act, seed=off, h0=True, state=True, bias=True, dy=True)
+    cg = rn.CgDeviceProblem(inp, B, T, D, nb, act)
+    u, dy, h0 = rn.to_device(inp["u"], act), rn.to_device(inp["dy"], act), rn.to_device(inp["h0"], "f32")
+    ring = rn.to_device(gen.ring_from_chrono(inp["state"], 4), act)
+    f32 = lambda *s: torch.empty(*s, dtype=torch.float32, device="cuda:0")
+    sh = cg.shape()
+
+    def call(off):
+        at = lambda t: _at(t, off)
+        held = [at(cg.t[k]) for k in ("W_a", "W_x", "b_a", "b_x", "Lambda", "theta", "conv_w", "conv_b")]   # (params hold addresses)
+        params = R.make_cg_params(*held)
+        g = dict(dW_a=f32(nb, hs, 2 * hs), dW_x=f32(nb, hs, 2 * hs), db_a=f32(D // 2), db_x=f32(D // 2), dLambda=f32(D // 2),
+                 dtheta=f32(D // 2), dconv_w=f32(4, D), dconv_b=f32(D))
+        out = dict(y=at(torch.zeros_like(u)), hT=f32(B, D), ring=at(torch.zeros_like(ring)), du=at(torch.zeros_like(u)), dh0=f32(B, D))
+        uu, dd, rr = at(u), at(dy), at(ring)
+        n = R.rglru_workspace_bytes(sh, R.OP_CG_FORWARD)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        R.rglru_timing_enable(True)
+        R.rglru_cg_forward(sh, params, uu, h0, rr, 4, out["y"], out["hT"], out["ring"], ws, n, None)
+        n = R.rglru_workspace_bytes(sh, R.OP_CG_BACKWARD)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        R.rglru_cg_backward(sh, params, uu, h0, rr, 4, dd, None, out["du"], out["dh0"], R.make_cg_param_grads(*g.values()), ws, n, None)
+        torch.cuda.synchronize()
+        names = [R.rglru_timing_get(i)[0] for i in range(R.rglru_timing_count())]
+        R.rglru_timing_enable(False)
+        return dict(g, **out), names
+
+    want, _ = call(0)
+    got, names = call(off)
+    assert "cg_apply_kernel" in names and "cg_wgrad_kernel" in names and "cg_dgrad_kernel" in names, names
+    for k in want:
+        np.testing.assert_array_equal(rn.to_host(got[k]), rn.to_host(want[k]), err_msg=k)
