@@ -197,14 +197,15 @@ size_t general_forward_bytes(const rglru_shape *s) {
 size_t least_backward_bytes(const rglru_shape *s) {
   if (s->act_dtype == RGLRU_BF16 && s->D / s->num_blocks == 256 && (size_t)s->T * s->D * 4 < ((size_t)1 << 32))
     return backward_mfma_ws_bytes(s->B, s->T, s->D, s->num_blocks);
-  return std::max(backward_generic_ws_bytes(s->B, s->T, s->D, s->num_blocks),
-                  backward_pass_shape(s) ? narrow_backward_bytes(s) : 0);
+  return backward_generic_ws_bytes(s->B, s->T, s->D, s->num_blocks);
 }
 
 size_t workspace_need(const rglru_shape *s, int op) {
   switch (op) {
     case RGLRU_OP_BACKWARD:
-      return std::max(least_backward_bytes(s), backward_pass_shape(s) ? backward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks) : 0);
+      return !backward_pass_shape(s) ? least_backward_bytes(s)
+                                     : std::max({least_backward_bytes(s), narrow_backward_bytes(s),
+                                                 backward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks)});
     case RGLRU_OP_SCAN:
       if (s->act_dtype == RGLRU_BF16 && s->D % 256 == 0 && s->T >= 1)
         return scan_tiled_ws_bytes(s->B, s->T, s->D);

@@ -117,8 +117,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int b = gb % p.B, g = gb / p.B;
   const int D = p.D, H = D / 2, T = p.T, hs = p.bs, t0 = rt * PR, tw = t0 + wv * RUN;
   const unsigned row_bytes = (unsigned)D * 2;
-  const size_t seq = (size_t)b * T * D, seq_bytes = (size_t)T * row_bytes;
-  const __amdgpu_buffer_rsrc_t xh_rs = buf(a.xh + seq, seq_bytes), xl_rs = buf(a.xl + seq, seq_bytes);
+  // (every buffer starts at the tile: 32-bit offsets whatever the length of the sequence)
+  const size_t row0 = (size_t)b * T + t0, first = row0 * D, nrow = T - t0 < PR ? T - t0 : PR, tile_bytes = nrow * row_bytes;
+  const __amdgpu_buffer_rsrc_t xh_rs = buf(a.xh + first, tile_bytes), xl_rs = buf(a.xl + first, tile_bytes);
   const size_t wn = (size_t)hs * 2 * hs;
   const __amdgpu_buffer_rsrc_t w_rs[2] = {buf(a.w16 + (size_t)g * wn, wn * 2), buf(a.w16 + ((size_t)p.nb + g) * wn, wn * 2)};
   const int lrow = lane >> 2;
@@ -135,7 +136,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       const int i = wv + 4 * m;
-      const unsigned so = (unsigned)(t0 + 16 * i) * row_bytes + ka;
+      const unsigned so = (unsigned)(16 * i) * row_bytes + ka;
       lds16(xh_rs, s + i * 1024, va, so);
       lds16(xl_rs, s + CST_A + i * 1024, va, so);
     }
@@ -210,9 +211,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
       v[2 * n + 1] = w[1];
     }
   };
-  const __amdgpu_buffer_rsrc_t dy_rs = buf((const unsigned short *)(BWD ? p.dy : (const void *)a.xh) + seq, seq_bytes);
-  const size_t HT = (size_t)T * H;
-  const __amdgpu_buffer_rsrc_t p_rs = buf(a.pq + (size_t)b * HT, HT * 4), q_rs = buf(a.pq + ((size_t)p.B + b) * HT, HT * 4);
+  const __amdgpu_buffer_rsrc_t dy_rs = buf((const unsigned short *)(BWD ? p.dy : (const void *)a.xh) + first, tile_bytes);
+  const __amdgpu_buffer_rsrc_t p_rs = buf(a.pq + row0 * H, nrow * H * 4),
+                               q_rs = buf(a.pq + ((size_t)p.B * T + row0) * H, nrow * H * 4);
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) {
     if (cb >= ncb) break;
@@ -228,11 +229,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     float2 At = make_float2(1.f, 0.f), Et = make_float2(0.f, 0.f);
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
-      const int tr = tw + rb * 32;
+      const int tr = tw + rb * 32, lr = wv * RUN + rb * 32;   // first step, first row of the tile
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the previous block's reads are done
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
-        const unsigned so = (unsigned)(tr + 8 * m) * row_bytes;
+        const unsigned so = (unsigned)(lr + 8 * m) * row_bytes;
         lds16(xh_rs, tile + m * 1024, e_vo, so);
         lds16(xl_rs, tile + 4096 + m * 1024, e_vo, so);
         if (BWD) lds16(dy_rs, tile + 8192 + m * 1024, e_vo, so);
@@ -241,7 +242,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int r = 0; r < 16; ++r) {
         acc[0][rb][cb][r] += ba;
         acc[1][rb][cb][r] += bx;
-        const unsigned so = (unsigned)(tr + r) * (unsigned)H * 4;
+        const unsigned so = (unsigned)(lr + r) * (unsigned)H * 4;
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[0][rb][cb][r]), p_rs, o_vo, so, 0);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[1][rb][cb][r]), q_rs, o_vo, so, 0);
       }
@@ -465,18 +466,20 @@ __global__ void __launch_bounds__(256) cg_adjoint_kernel(CgAdjArgs a) {
   float s_ba = 0.f, s_bx = 0.f, s_lam = 0.f, s_th = 0.f;
   if (tr < T) {
     const unsigned row_bytes = (unsigned)D * 2;
-    const size_t seq = (size_t)b * T * D, seq_bytes = (size_t)T * row_bytes, HT = (size_t)T * H;
-    const __amdgpu_buffer_rsrc_t xh_rs = buf(a.xh + seq, seq_bytes), xl_rs = buf(a.xl + seq, seq_bytes),
-                                 dy_rs = buf((const unsigned short *)p.dy + seq, seq_bytes),
-                                 p_rs = buf(a.pq + (size_t)b * HT, HT * 4), q_rs = buf(a.pq + ((size_t)p.B + b) * HT, HT * 4),
-                                 h_rs = buf(a.dph + seq, seq_bytes), l_rs = buf(a.dpl + seq, seq_bytes),
-                                 x_rs = buf(a.dx + seq, seq_bytes * 2);
+    // (every buffer starts at the wave's rows)
+    const size_t row0 = (size_t)b * T + tr, first = row0 * D, nrow = T - tr < 32 ? T - tr : 32, bytes = nrow * row_bytes;
+    const __amdgpu_buffer_rsrc_t xh_rs = buf(a.xh + first, bytes), xl_rs = buf(a.xl + first, bytes),
+                                 dy_rs = buf((const unsigned short *)p.dy + first, bytes),
+                                 p_rs = buf(a.pq + row0 * H, nrow * H * 4),
+                                 q_rs = buf(a.pq + ((size_t)p.B * T + row0) * H, nrow * H * 4),
+                                 h_rs = buf(a.dph + first, bytes), l_rs = buf(a.dpl + first, bytes),
+                                 x_rs = buf(a.dx + first, bytes * 2);
     unsigned char *tile = smem + wv * CA_TILE;
     const int erow = lane >> 3, ec = (lane & 7) ^ ((erow & 3) * 2), ecol = h0c + (ec & 3) * 8;
     const unsigned e_vo = ecol < H ? (unsigned)erow * row_bytes + (unsigned)((ec >> 2) * H + ecol) * 2 : OOB;
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-      const unsigned so = (unsigned)(tr + 8 * m) * row_bytes;
+      const unsigned so = (unsigned)(8 * m) * row_bytes;
       lds16(xh_rs, tile + m * 1024, e_vo, so);
       lds16(xl_rs, tile + 4096 + m * 1024, e_vo, so);
       lds16(dy_rs, tile + 8192 + m * 1024, e_vo, so);
@@ -485,7 +488,7 @@ __global__ void __launch_bounds__(256) cg_adjoint_kernel(CgAdjArgs a) {
     float pv[16], qv[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const unsigned so = (unsigned)(tr + r) * (unsigned)H * 4;
+      const unsigned so = (unsigned)r * (unsigned)H * 4;
       pv[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(p_rs, g_vo, so, 0));
       qv[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(q_rs, g_vo, so, 0));
     }
@@ -559,7 +562,7 @@ __global__ void __launch_bounds__(256) cg_adjoint_kernel(CgAdjArgs a) {
       if (in) eps = cmul(make_float2(av[r].x, -av[r].y), dl);
       unsigned hi_pk, lo_pk;
       split_bf16(dpv, dqv, hi_pk, lo_pk);
-      const unsigned so = (unsigned)(tr + r) * row_bytes;
+      const unsigned so = (unsigned)r * row_bytes;
       __builtin_amdgcn_raw_buffer_store_b16((short)(hi_pk & 0xffffu), h_rs, o_vo, so, 0);
       __builtin_amdgcn_raw_buffer_store_b16((short)(hi_pk >> 16), h_rs, o_vo, so + (unsigned)hs * 2, 0);
       __builtin_amdgcn_raw_buffer_store_b16((short)(lo_pk & 0xffffu), l_rs, o_vo, so, 0);
@@ -610,9 +613,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int b = gb % p.B, g = gb / p.B;
   const int D = p.D, H = D / 2, T = p.T, hs = p.bs, t0 = rt * PR, tw = t0 + wv * RUN;
   const unsigned row2 = (unsigned)D * 2, wrow = (unsigned)hs * 4;
-  const size_t seq = (size_t)b * T * D;
-  const __amdgpu_buffer_rsrc_t h_rs = buf(a.dph + seq, (size_t)T * row2), l_rs = buf(a.dpl + seq, (size_t)T * row2),
-                               x_rs = buf(a.dx + seq, (size_t)T * row2 * 2),
+  const size_t first = ((size_t)b * T + t0) * D, bytes = (size_t)(T - t0 < PR ? T - t0 : PR) * row2;
+  const __amdgpu_buffer_rsrc_t h_rs = buf(a.dph + first, bytes), l_rs = buf(a.dpl + first, bytes), x_rs = buf(a.dx + first, bytes * 2),
                                w_rs = buf(a.wt + ((size_t)g * 2 * hs + part * hs) * 2 * hs, (size_t)hs * wrow);
   const int lrow = lane >> 2;
   const int ca = (lane & 3) ^ (((lrow >> 1) & 1) | ((wv & 1) << 1)), cb_ = (lane & 3) ^ ((lrow >> 1) & 3);
@@ -624,7 +626,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       const int i = wv + 4 * m;
-      const unsigned so = (unsigned)(t0 + 16 * i) * row2 + (unsigned)kc * 64;
+      const unsigned so = (unsigned)(16 * i) * row2 + (unsigned)kc * 64;
       lds16(h_rs, s + i * 1024, a_vo, so);
       lds16(l_rs, s + CST_A + i * 1024, a_vo, so);
     }
@@ -681,7 +683,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int cb = 0; cb < 4; ++cb) {
       const int kk = ct * 128 + cb * 32 + j;
       const unsigned vo = kk < hs ? (unsigned)(part * H + g * hs + kk) * 4 + (unsigned)(hf * 16) * row2 * 2 : OOB;
-      const unsigned so = (unsigned)(tw + rb * 32) * row2 * 2;
+      const unsigned so = (unsigned)(wv * RUN + rb * 32) * row2 * 2;
       float v[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) v[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(x_rs, vo, so + r * row2 * 2, 0));
@@ -859,7 +861,7 @@ CgGatesArgs gates_args(const Problem &p, int T) {
   return a;
 }
 bool shape_ok(int B, int T, int D, int hs) {
-  return hs % 16 == 0 && hs >= 16 && T >= 1 && B <= 65535 && (size_t)(T + PR) * D * 4 < ((size_t)1 << 31) &&
+  return hs % 16 == 0 && hs >= 16 && T >= 1 && B <= 65535 && (size_t)PR * D * 4 < ((size_t)1 << 31) &&
          (T + 127) / 128 <= 65535 && (size_t)B * ((T + PR - 1) / PR) * ((size_t)D / 16) < ((size_t)1 << 28);
 }
 

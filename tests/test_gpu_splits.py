@@ -499,3 +499,62 @@ def test_complex_gated_passes_at_any_alignment(off):
     assert "cg_apply_kernel" in names and "cg_wgrad_kernel" in names and "cg_dgrad_kernel" in names, names
     for k in want:
         np.testing.assert_array_equal(rn.to_host(got[k]), rn.to_host(want[k]), err_msg=k)
+
+
+def _long_case(rn, cg, T, D, nb, seed):
+    """A sequence of T steps with decays that forget within a few hundred steps, made on the GPU."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    act = lambda t: t.to(torch.bfloat16)
+    normal = lambda *s, k=1.0: torch.randn(*s, generator=g, device="cuda") * k
+    W, bs = (D // 2, D // 2 // nb) if cg else (D, D // nb)
+    nin = 2 * bs if cg else bs
+    t = dict(W_a=act(normal(nb, bs, nin, k=nin ** -0.5)), W_x=act(normal(nb, bs, nin, k=nin ** -0.5)), b_a=normal(W, k=0.1),
+             b_x=normal(W, k=0.1), Lambda=torch.full((W,), 2.0, device="cuda"), conv_w=normal(4, D, k=0.5), conv_b=normal(D, k=0.1))
+    if cg:
+        t["theta"] = normal(W, k=0.1)
+    return t, act(normal(1, T, D)), act(normal(1, T, D))
+
+
+@pytest.mark.parametrize("cg,T,D,nb", [(False, 210240, 2560, 16), (True, 131200, 4096, 16)])
+def test_passes_on_sequences_past_32_bit_offsets(cg, T, D, nb):
+    """fp32 intermediates of more than 2^31 bytes a sequence: the passes run, and what they give at the start, around the
+    2^31 bytes and at the end is what a short call gives on the steps around it (a decay of 0.6 on average, so that
+    512 steps more on either side leave nothing of what is missing)."""
+    import paper_2402_19427_amd as R
+    import torch
+    rn = runner()
+    t, u, dy = _long_case(rn, cg, T, D, nb, 7)
+    keys = ("W_a", "W_x", "b_a", "b_x", "Lambda") + (("theta",) if cg else ()) + ("conv_w", "conv_b")
+    params = (R.make_cg_params if cg else R.make_params)(*[t[k] for k in keys])
+
+    def call(u, dy):
+        n = u.shape[1]
+        sh = R.make_shape(1, n, D, nb, R.BF16)
+        f32 = lambda *s: torch.empty(*s, dtype=torch.float32, device="cuda:0")
+        g = {k: torch.empty_like(t[k], dtype=torch.float32) for k in keys}
+        y, hT, ring, du, dh0 = torch.empty_like(u), f32(1, D), torch.empty(1, 3, D, dtype=u.dtype, device="cuda:0"), torch.empty_like(u), f32(1, D)
+        ops = (R.OP_CG_FORWARD, R.OP_CG_BACKWARD) if cg else (R.OP_FORWARD, R.OP_BACKWARD)
+        nf, nw = (R.rglru_workspace_bytes(sh, o) for o in ops)
+        ws = torch.empty(max(nf, nw, 256), dtype=torch.uint8, device="cuda:0")
+        R.rglru_timing_enable(True)
+        if cg:
+            R.rglru_cg_forward(sh, params, u, None, None, 0, y, hT, ring, ws, nf, None)
+            R.rglru_cg_backward(sh, params, u, None, None, 0, dy, None, du, dh0, R.make_cg_param_grads(*g.values()), ws, nw, None)
+        else:
+            R.rglru_forward(sh, params, u, None, None, 0, y, hT, ring, ws, nf, None)
+            R.rglru_backward(sh, params, u, None, None, 0, y, dy, None, du, dh0, R.make_param_grads(*g.values()), ws, nw, None)
+        torch.cuda.synchronize()
+        names = [R.rglru_timing_get(i)[0] for i in range(R.rglru_timing_count())]
+        R.rglru_timing_enable(False)
+        return y, du, names
+
+    y, du, names = call(u, dy)
+    assert ("cg_wgrad_kernel" if cg else "wgrad_pass_kernel") in names and (not cg or "cg_apply_kernel" in names), names
+    at = (1 << 31) // (4 * D)
+    for lo, hi in ((0, 300), (at - 150, at + 150), (T - 300, T)):
+        a, b = max(lo - 512, 0), min(hi + 512, T)
+        ys, dus, _ = call(u[:, a:b].contiguous(), dy[:, a:b].contiguous())
+        for got, want in ((y, ys), (du, dus)):
+            got, want = got[:, lo:hi].float(), want[:, lo - a:hi - a].float()
+            assert torch.isfinite(got).all() and ((got - want).norm() / want.norm()).item() < BF16, (lo, hi)
