@@ -962,7 +962,7 @@ hipError_t launch_cg_forward_pass(const Problem &p, hipStream_t s) {
   for (int t_lo = 0; t_lo < p.T; t_lo += n) {
     const int m = p.T - t_lo < n ? p.T - t_lo : n;
     const bool last = t_lo + m == p.T;
-    if ((e = launch_conv_rows(p, xh, xl, true, t_lo, m, s)) != hipSuccess) return e;
+    if ((e = launch_conv_rows(p, xh, xl, t_lo, m, s)) != hipSuccess) return e;
     CgGatesArgs a = gates_args(p, m);
     a.xh = xh; a.xl = xl; a.w16 = w16; a.pq = pq;
     a.nrun = (m + RUN - 1) / RUN;
@@ -1027,7 +1027,7 @@ hipError_t launch_cg_backward_pass(const Problem &call, hipStream_t s) {
                  *w16 = (unsigned short *)(ws + q.off_w), *wt = (unsigned short *)(ws + q.off_wt);
   float *pq = (float *)(ws + q.off_pq), *dx = (float *)(ws + q.off_dx);
   if ((e = launch_prep(p, w16, wt, s)) != hipSuccess) return e;
-  if ((e = launch_conv_rows(p, xh, xl, true, 0, p.T, s)) != hipSuccess) return e;
+  if ((e = launch_conv_rows(p, xh, xl, 0, p.T, s)) != hipSuccess) return e;
   CgGatesArgs a = gates_args(p, p.T);
   a.xh = xh; a.xl = xl; a.w16 = w16; a.pq = pq;
   a.nrun = q.nsub;

@@ -14,6 +14,7 @@ constexpr unsigned OOB = 0x80000000u;   // buffer offset past every range: loads
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 // the same at any address a bf16 tensor may have (global memory takes such accesses; aligned ones cost the same)
 typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
 typedef u32x2 u32x2_at2 __attribute__((aligned(2)));
@@ -58,9 +59,8 @@ __device__ __forceinline__ unsigned xcd_id() {
 }
 
 // x = Conv1D(u) for steps [t_lo, t_lo + n) of every sequence as [B][n][D] in half precision, xl (may
-// be null): the low part. `operand`: xh only feeds products, and finite values past half precision's range stay
-// finite there.
-hipError_t launch_conv_rows(const Problem &p, unsigned short *xh, unsigned short *xl, bool operand, int t_lo, int n, hipStream_t s);
+// be null): the low part. Finite values past half precision's range stop at its end in xh.
+hipError_t launch_conv_rows(const Problem &p, unsigned short *xh, unsigned short *xl, int t_lo, int n, hipStream_t s);
 
 // states entering the runs [B][nrun][D] and after the last one (fin, may be null) from the runs' aggregates
 hipError_t launch_chain_forward(const float2 *agg, const float *init, float *in, float *fin, int B, int D, int nrun,

@@ -558,3 +558,27 @@ def test_passes_on_sequences_past_32_bit_offsets(cg, T, D, nb):
         for got, want in ((y, ys), (du, dus)):
             got, want = got[:, lo:hi].float(), want[:, lo - a:hi - a].float()
             assert torch.isfinite(got).all() and ((got - want).norm() / want.norm()).item() < BF16, (lo, hi)
+
+
+@pytest.mark.parametrize("T,bs,nb", [(300, 352, 8), (300, 64, 4), (50, 512, 1)])
+def test_layer_forward_past_half_precision(T, bs, nb):
+    """x past half precision's range leaves the gates of its block finite and enters i_t x_t as it is. (The rows of W of the
+    channels it arrives in are zero, so that b_t stays inside half precision there. In the products x stops at 65504: one such
+    x per step, at most 1.6 % past it, moves a logit p by 0.016 p and a gate by 0.016 max |p| sigma'(p) = 2^-8 at most.)"""
+    rn = runner()
+    D, act = bs * nb, "bf16"
+    inp = gen.make_inputs(1, T, D, nb, act=act, seed=bs, bias=True)
+    inp["conv_w"][:], inp["conv_b"][:] = 0.0, 0.0
+    inp["conv_w"][0] = 1.0
+    for t, d, v in ((20, 3, 66048.0), (24, 40, -66560.0), (29, 17, -66048.0)):   # (bf16 values)
+        inp["u"][0, t, d] = v
+    for d in (3, 17, 40):
+        inp["W_a"][0, d], inp["W_x"][0, d], inp["b_x"][d] = 0.0, 0.0, -3.0
+    dp = rn.DeviceProblem(inp, 1, T, D, nb, act)
+    y, hT, _ = dp.forward(rn.to_device(inp["u"], act))
+    q = f64(inp)
+    ref, hT_ref, _ = oracle.forward(q["u"], q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"], conv_b=q["conv_b"])
+    y = rn.to_host(y)
+    few = np.isin(np.arange(D), (3, 17, 40))
+    for got, want in ((y[..., few], ref[..., few]), (y[..., ~few], ref[..., ~few]), (rn.to_host(hT), hT_ref)):
+        assert gen.rel_err(got, want) < BF16
