@@ -43,14 +43,16 @@
  * (Appendix A prints softplus(+Lambda); that contradicts a = sigma(Lambda) of Section 2.4,
  * which is what this library follows.)
  *
- * Which kernels run (bf16 storage): gate blocks of 256 channels, or of a multiple of 16 channels
+ * Which kernels run. bf16 storage: gate blocks of 256 channels, or of a multiple of 16 channels
  * from 128 to 240 (e.g. Section 4.1's 16 blocks at width 2560 = 160 channels), run on the fused
- * matrix-core kernels in every call. Any other multiple of 16 (e.g. 352 and 512 channels at
- * widths 5632 and 8192): rglru_forward runs as three matrix-core passes through the workspace
- * (widths that are a multiple of 256), decode steps on a matrix-core kernel of their own
- * (blocks up to 768 channels), the backward as matrix-core passes as well. All other block
- * sizes up to 2048 and fp32 storage run on generic kernels that give the same results far
- * more slowly.
+ * matrix-core kernels in the forward and in decode steps, and so does the backward of 256. The
+ * forward of any other multiple of 16 (e.g. 352 and 512 channels at widths 5632 and 8192; widths
+ * that are a multiple of 256) and the backward of every multiple of 16 but 256 run as matrix-core
+ * passes through the workspace, parallel over time; decode steps of blocks up to 768 channels on
+ * matrix-core or vector-unit kernels of their own. fp32 storage: the forward of multiples of 16 up
+ * to 512 channels runs on the fp32 matrix cores. All other block sizes up to 2048, and the backward
+ * in fp32 storage, run on generic kernels that give the same results far more slowly. So does a
+ * call of the real layer in bf16 whose tensors do not lie on 16-byte boundaries.
  * rglru_workspace_bytes() accounts for all of it.
  */
 #ifndef RGLRU_H

@@ -10,8 +10,8 @@
 // sums over the 32 lanes by a butterfly that leaves lane l with output l. A block's Conv1D ring has
 // one reader, which also replaces the oldest slot - unless the block is wider than the 256 outputs a
 // workgroup has (8 waves of 32): then several workgroups share it and the ring is written by a
-// kernel of its own. With the merge at B1 D2560 in 10 blocks a step goes from 8.9 to 8.1 us (a launch of
-// nothing takes 3.9), at B1 D5632 in 16 blocks from 17.3 to 10.3.
+// kernel of its own. With the merge at B1 D2560 in 10 blocks a call takes 6.2 us against 8.9 on the kernel
+// for tiles (a launch of nothing takes 3.9), at B1 D5632 in 16 blocks 7.5 against 10.9.
 #include "rglru_gelu.h"
 #include "rglru_mfma.h"
 
@@ -182,10 +182,12 @@ void launch_t(const SmallArgs &a, dim3 grid, int threads, hipStream_t s) {
 }  // namespace
 
 // A block of up to 256 channels takes one workgroup of 8 waves and about 160 registers per sequence, one
-// per CU: up to 256 of them run at once (8.0 us against 9.2 for the tiled kernel with the merge, 7.8
-// against 8.3 without it), with more the second round costs more than it saves (10.8 against 8.5).
-// A wider block's four-wave workgroups go two to a CU: 10.3 us at one sequence, 11.0 with 512 workgroups;
-// the kernel for tiles takes 11.6 to 12.8 from there on.
+// per CU: up to 256 of them run at once (B16 D4096 in 16 blocks, 256 workgroups: 6.3 us against 8.1 on the
+// kernel for tiles, with the merge 6.8 against 8.9), with more the second round costs more than it saves
+// (B20, 320 workgroups: 10.2 against 8.1, with the merge 10.6 against 8.9).
+// A wider block's four-wave workgroups go two to a CU: 10.3 us with 480 workgroups (B10, 352 channels)
+// against 10.9 on the kernel for tiles, 11.0 with 512 (B8, 512 channels) against 11.3; 12.7 against 10.9 with 528
+// (B11) and 13.7 against 11.2 with 576 (B9).
 bool decode_small_supported(const Problem &p, bool bf) {
   const uintptr_t all = (uintptr_t)p.W_a | (uintptr_t)p.W_x | (uintptr_t)p.u | (uintptr_t)p.state_out |
                         (uintptr_t)p.hT | (uintptr_t)p.y | (uintptr_t)p.conv_w | (uintptr_t)p.conv_b |
