@@ -52,7 +52,9 @@
  * matrix-core or vector-unit kernels of their own. fp32 storage: the forward of multiples of 16 up
  * to 512 channels runs on the fp32 matrix cores. All other block sizes up to 2048, and the backward
  * in fp32 storage, run on generic kernels that give the same results far more slowly. So does a
- * call of the real layer in bf16 whose tensors do not lie on 16-byte boundaries.
+ * bf16 call of the fused kernels, the forward in passes or the decode kernels whose tensors do not
+ * lie on 16-byte boundaries (h0 and hT of the former two may); the passes of the backward and those of the
+ * complex-gated variant take any alignment.
  * rglru_workspace_bytes() accounts for all of it.
  */
 #ifndef RGLRU_H

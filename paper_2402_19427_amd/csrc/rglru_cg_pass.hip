@@ -88,12 +88,6 @@ __global__ void __launch_bounds__(256) cg_prep_kernel(CgPrepArgs a) {
   }
 }
 
-// n8 pieces of eight bf16 values to a 16-byte aligned place
-__global__ void __launch_bounds__(256) realign_kernel(const unsigned short *src, u32x4 *dst, size_t n8) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n8) dst[i] = *(const u32x4_at2 *)(src + i * 8);
-}
-
 // ------------------------------------------------------------------------ 2. gates
 struct CgGatesArgs {
   Problem p;                       // T: steps of the chunk in hand
@@ -1015,11 +1009,7 @@ hipError_t launch_cg_backward_pass(const Problem &call, hipStream_t s) {
   const BwdPlan q = plan_bwd(p.B, p.T, p.D, p.nb);
   char *ws = (char *)p.ws;
   if (dy_copy_bytes(p)) {
-    KernelTimer kt("realign_kernel", s);
-    const size_t n8 = (size_t)p.B * p.T * p.D / 8;
-    hipLaunchKernelGGL(realign_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, (const unsigned short *)call.dy,
-                       (u32x4 *)(ws + q.total), n8);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_realign(call.dy, ws + q.total, (size_t)p.B * p.T * p.D, s)) != hipSuccess) return e;
     p.dy = ws + q.total;
   }
   unsigned short *xh = (unsigned short *)(ws + q.off_xh), *xl = (unsigned short *)(ws + q.off_xl),

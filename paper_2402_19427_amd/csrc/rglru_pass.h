@@ -62,6 +62,9 @@ __device__ __forceinline__ unsigned xcd_id() {
 // be null): the low part. Finite values past half precision's range stop at its end in xh.
 hipError_t launch_conv_rows(const Problem &p, unsigned short *xh, unsigned short *xl, int t_lo, int n, hipStream_t s);
 
+// n bf16 values (a multiple of 8) at any alignment, copied to a 16-byte aligned place
+hipError_t launch_realign(const void *src, void *dst, size_t n, hipStream_t s);
+
 // states entering the runs [B][nrun][D] and after the last one (fin, may be null) from the runs' aggregates
 hipError_t launch_chain_forward(const float2 *agg, const float *init, float *in, float *fin, int B, int D, int nrun,
                                 hipStream_t s);

@@ -582,3 +582,58 @@ def test_layer_forward_past_half_precision(T, bs, nb):
     few = np.isin(np.arange(D), (3, 17, 40))
     for got, want in ((y[..., few], ref[..., few]), (y[..., ~few], ref[..., ~few]), (rn.to_host(hT), hT_ref)):
         assert gen.rel_err(got, want) < BF16
+
+
+@pytest.mark.parametrize("T,bs,nb,off", [(300, 160, 8, 1), (300, 160, 8, 4), (300, 352, 8, 1), (50, 352, 8, 2)])
+@pytest.mark.parametrize("merge", [False, True])
+def test_layer_passes_at_any_alignment(T, bs, nb, off, merge):
+    """Tensors of the backward off the 16-byte grid, and states of the forward off the 8-byte grid: the passes, the same
+    results. (The backward's u and dy without the merge stay on the grid: nothing but the passes' own size is asked for.)"""
+    import paper_2402_19427_amd as R
+    import torch
+    rn = runner()
+    B, D, act = 2, bs * nb, "bf16"
+    inp = gen.make_inputs(B, T, D, nb, act=act, seed=bs, h0=True, state=True, bias=True, dy=True)
+    dp = rn.DeviceProblem(inp, B, T, D, nb, act)
+    u, dy, h0 = rn.to_device(inp["u"], act), rn.to_device(inp["dy"], act), rn.to_device(inp["h0"], "f32")
+    br = rn.to_device(gen.make_branch(B, T, D, act=act, seed=3), act)
+    ring = rn.to_device(gen.ring_from_chrono(inp["state"], 4), act)
+    f32 = lambda *s: torch.empty(*s, dtype=torch.float32, device="cuda:0")
+    sh = dp.shape()
+    wide = bs > 256
+
+    def call(off):
+        at = lambda t: _at(t, off)
+        par = [at(getattr(dp, k)) for k in ("W_a", "W_x", "b_a", "b_x", "Lambda", "conv_w", "conv_b")]
+        fpar, bpar = dp.params, R.make_params(*par)
+        g = dp.alloc_grads()
+        pg = R.make_param_grads(*[g[k] for k in ("dW_a", "dW_x", "db_a", "db_x", "dLambda", "dconv_w", "dconv_b")])
+        hh = _at(h0, 1 if off else 0)
+        out = dict(y=torch.empty_like(u), hT=_at(torch.zeros_like(h0), 1 if off else 0), ring=torch.empty_like(ring),
+                   du=at(torch.zeros_like(u)), dh0=f32(B, D))
+        names = []
+        R.rglru_timing_enable(True)
+        n = R.rglru_workspace_bytes(sh, R.OP_FORWARD)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        R.rglru_forward(sh, fpar, u, hh, ring, 4, out["y"], out["hT"], out["ring"], ws, n, None)
+        torch.cuda.synchronize()
+        names += [R.rglru_timing_get(i)[0] for i in range(R.rglru_timing_count())]
+        R.rglru_timing_enable(True)
+        yy, rr, dd, bb = at(out["y"]), at(ring), at(dy) if merge else dy, at(br)
+        n = R.rglru_workspace_bytes(sh, R.OP_BACKWARD_MERGE if merge else R.OP_BACKWARD)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        if merge:
+            out["dbranch"] = at(torch.zeros_like(u))
+            R.rglru_backward_merge(sh, bpar, u, bb, hh, rr, 4, 0, yy, dd, None, out["du"], out["dbranch"], out["dh0"], pg, ws, n, None)
+        else:
+            R.rglru_backward(sh, bpar, u, hh, rr, 4, yy, dd, None, out["du"], out["dh0"], pg, ws, n, None)
+        torch.cuda.synchronize()
+        names += [R.rglru_timing_get(i)[0] for i in range(R.rglru_timing_count())]
+        R.rglru_timing_enable(False)
+        return dict(g, **out), names
+
+    want, _ = call(0)
+    got, names = call(off)
+    assert "adjoint_kernel" in names and "wgrad_pass_kernel" in names and (not wide or "apply_kernel" in names), names
+    for k in want:
+        np.testing.assert_array_equal(rn.to_host(got[k]), rn.to_host(want[k]), err_msg=k)
