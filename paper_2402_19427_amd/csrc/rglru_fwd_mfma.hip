@@ -181,7 +181,8 @@ __device__ __forceinline__ u32x4 merge8(const u32x4 yv, const u32x4 bv) {
   return o;
 }
 
-// GMAX = 1: one workgroup per (sequence, block); GMAX = 4 / 8 / 16: 2..4 / 5..8 / 9..16 time slices
+// GMAX = 1: one workgroup per (sequence, block); GMAX = 4 / 8 / 16: 2..4 / 5..8 / 9..16 time slices; 5: 2..4 slices of
+// narrower blocks with the merge, few tiles each
 // MERGE = 0: y is the output; 1 / 2: the recurrent block's merge (Section 2.3) as epilogue,
 // out = y * GeLU(branch) with GeLU = z Phi(z) / its tanh form, y itself written only if asked for
 // PAD: gate blocks narrower than 256 channels (a multiple of 16, Section 4.1's 16 blocks at
@@ -246,10 +247,12 @@ fwd_mfma_kernel(FwdArgs a) {
   // Measured best per instance (us, at neighbouring counts, B8 T2048 D2560 unless noted): 256-channel
   // blocks, 2-4 slices 9 / 10 / 11 -> 107 / 104 / 128, with the merge 8 / 9 / 10 -> 133 / 132 / 132;
   // 5-8 slices (B4) 6 / 8 / 9 -> 67 / 64 / 66, with the merge 6 / 7 / 8 -> 81 / 80 / 78; 9-16 slices
-  // (B1) 4 / 6 / 8 -> 38 / 37 / 40. 160-channel blocks (clamped addresses cost registers) 2 / 4 / 6 ->
-  // 142 / 138 / 174, with the merge 2 / 4 / 6 -> 183 / 177 / 188.
+  // (B1) 4 / 6 / 8 -> 38 / 37 / 40. 160-channel blocks (clamped addresses cost registers), 2-4 slices: what is
+  // resident is fetched before the first tile, so that few tiles per workgroup want few. 2 / 4: B8 T2048 134 / 134, B4
+  // T256 20.4 / 21.6, B1 T64 14.5 / 15.5; with the merge 0 / 2 / 4: 179 / 174 / 174, 22.4 / 23.2 / 23.9, 14.8 / 15.6 / 16.0
+  // (with y kept as well 4 is 8 us better than 2 at the first): an instance of its own for few tiles, GMAX 5.
   constexpr int NRES_256 = GMAX == 1 ? (MERGE ? 11 : 13) : GMAX == 4 ? (MERGE ? 9 : 10) : GMAX == 8 ? 8 : (MERGE ? 4 : 6);
-  constexpr int NRES_PAD = GMAX == 1 ? (MERGE ? 9 : 11) : GMAX == 4 ? 4 : GMAX == 8 ? (MERGE ? 2 : 0) : (MERGE ? 0 : 2);
+  constexpr int NRES_PAD = GMAX == 1 ? (MERGE ? 9 : 11) : GMAX == 4 ? (MERGE || PACKED ? 4 : 2) : GMAX == 5 ? 0 : GMAX == 8 ? (MERGE ? 2 : 0) : (MERGE ? 0 : 2);
   constexpr int NRES_U = PAD ? NRES_PAD : NRES_256;
   // (the masks of packed sequences take registers of their own)
   // (the aggregate pass stages no outputs)
@@ -1308,6 +1311,10 @@ hipError_t launch_forward_mfma(const Problem &p, hipStream_t s) {
   }
   a.err = (int *)p.ws;
   a.rec = (u64 *)((char *)p.ws + 256);
+  // (0 resident K-steps against 4, with the merge, tiles per workgroup 4: 34.3 / 34.7 us at B4 T512, 34.5 / 34.7 at B8 T256; 5.3: 44.9 /
+  // 44.8 at B5 T512; 8: 55.9 / 55.2 at B4 T1024)
+  if (p.bs != BS && p.merge && a.G <= 4 && a.ntile <= 4 * a.G)
+    return p.merge == 1 ? launch_tmp<5, 1, true>(a, grid, FWD_LDS, s) : launch_tmp<5, 2, true>(a, grid, FWD_LDS, s);
   return a.G <= 4 ? launch_t<4>(a, grid, FWD_LDS, s)
        : a.G <= 8 ? launch_t<8>(a, grid, FWD_LDS, s)
                   : launch_t<16>(a, grid, FWD_LDS, s);

@@ -637,3 +637,21 @@ def test_layer_passes_at_any_alignment(T, bs, nb, off, merge):
     assert "adjoint_kernel" in names and "wgrad_pass_kernel" in names and (not wide or "apply_kernel" in names), names
     for k in want:
         np.testing.assert_array_equal(rn.to_host(got[k]), rn.to_host(want[k]), err_msg=k)
+
+
+@pytest.mark.parametrize("B,T", [(1, 33), (8, 64), (8, 512), (8, 513), (16, 256), (16, 257)])   # at most 4 tiles per workgroup, and one more
+@pytest.mark.parametrize("tanh", [False, True])
+def test_merge_of_narrow_blocks_in_few_tiles(B, T, tanh):
+    """The merge as an epilogue against the same call with a merge kernel behind the plain forward: the same bits."""
+    import paper_2402_19427_amd as R
+    rn = runner()
+    bs, nb, act = 160, 8, "bf16"
+    D = bs * nb
+    inp = gen.make_inputs(B, T, D, nb, act=act, seed=B + T, h0=True, bias=True)
+    dp = rn.DeviceProblem(inp, B, T, D, nb, act)
+    u, h0, br = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32"), rn.to_device(gen.make_branch(B, T, D, act=act, seed=1), act)
+    flags = R.MERGE_GELU_TANH if tanh else 0
+    got = dp.forward_merge(u, br, h0=h0, flags=flags, keep_y=True)
+    want = dp.forward_merge(u, br, h0=h0, flags=flags | R.MERGE_SEPARATE, keep_y=True)
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(rn.to_host(a), rn.to_host(b))
