@@ -7,7 +7,6 @@
 #include <cstdio>
 #include <cstring>
 
-#include "rglru_internal.h"
 #include "rglru_mfma.h"
 
 using namespace rglru;
@@ -202,10 +201,11 @@ size_t least_backward_bytes(const rglru_shape *s) {
 
 size_t workspace_need(const rglru_shape *s, int op) {
   switch (op) {
-    case RGLRU_OP_BACKWARD:
+    case RGLRU_OP_BACKWARD:   // (the tiles take more than the passes where rows are few)
       return !backward_pass_shape(s) ? least_backward_bytes(s)
                                      : std::max({least_backward_bytes(s), narrow_backward_bytes(s),
-                                                 backward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks)});
+                                                 backward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks),
+                                                 backward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, false, false)});
     case RGLRU_OP_SCAN:
       if (s->act_dtype == RGLRU_BF16 && s->D % 256 == 0 && s->T >= 1)
         return scan_tiled_ws_bytes(s->B, s->T, s->D);
@@ -412,22 +412,29 @@ int rglru_workspace_status(const rglru_shape *shape, int op, const void *workspa
       forward_on_general_kernels(shape))
     return RGLRU_OK;                // the general kernels never wait on each other (their scratch is optional)
   if (!workspace) return fail(RGLRU_ERR_INVALID_ARG, "workspace is NULL");
-  size_t off = 0;   // forward and scan keep the flag in the first word
+  size_t off = 0;   // the flag is the first word
   if ((op == RGLRU_OP_FORWARD || op == RGLRU_OP_FORWARD_MERGE) &&
       !forward_mfma_block(shape->D / shape->num_blocks))
     return RGLRU_OK;                // the passes of the other block sizes do not wait on each other
-  if (bwd) {
-    if (shape->act_dtype == RGLRU_BF16 && shape->D / shape->num_blocks == 256 &&
-        (size_t)shape->T * shape->D * 4 < ((size_t)1 << 32))
-      off = backward_mfma_flag_offset(shape->B, shape->T, shape->D, shape->num_blocks);
-    else
-      return RGLRU_OK;              // neither the passes nor the generic kernels wait on each other
-    if (op == RGLRU_OP_BACKWARD_MERGE) off += merge_dy_bytes(shape);
+  // A backward has a status word if it ran on kernels that wait for each other, and that depends on more than the
+  // shape; the others leave data of their own there, which is never the sixteen bytes of the mark.
+  const bool marked = bwd && !(shape->act_dtype == RGLRU_BF16 && shape->D / shape->num_blocks == 256 &&
+                               (size_t)shape->T * shape->D * 4 < ((size_t)1 << 32));
+  if (bwd && marked && shape->act_dtype != RGLRU_BF16) return RGLRU_OK;
+  unsigned word[4] = {0u, 0u, 0u, 0u};
+  const unsigned mark[4] = {RGLRU_EXPIRED_WORDS};
+  bool expired = false;
+  // (with the merge: at the start of the whole workspace, or behind dy where dy is formed first)
+  for (const size_t at : {off, op == RGLRU_OP_BACKWARD_MERGE ? merge_dy_bytes(shape) : off}) {
+    e = hipMemcpy(word, (const char *)workspace + at, sizeof(word), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
+    if ((marked || at != off || op == RGLRU_OP_BACKWARD_MERGE) ? memcmp(word, mark, sizeof(mark)) == 0 : word[0] != 0) {
+      expired = true;
+      off = at;
+      break;
+    }
   }
-  int flag = 0;
-  e = hipMemcpy(&flag, (const char *)workspace + off, sizeof(flag), hipMemcpyDeviceToHost);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
-  if (flag != 0) {
+  if (expired) {
     // reported once: the word is cleared, so that the next call on this workspace starts afresh
     e = hipMemset((char *)const_cast<void *>(workspace) + off, 0, 16);
     if (e != hipSuccess) return hip_fail(e, "hipMemset");
@@ -654,7 +661,9 @@ int backward_run(const rglru_shape *shape, const rglru_params *params, const voi
   q.ws = workspace; q.ws_bytes = workspace_bytes;
   const bool bf = shape->act_dtype == RGLRU_BF16;
   hipError_t e;
-  if (backward_mfma_supported(q, bf)) {
+  if (backward_tile_supported(q, bf)) {
+    e = launch_backward_tile(q, (hipStream_t)stream);
+  } else if (backward_mfma_supported(q, bf)) {
     e = launch_backward_mfma(q, (hipStream_t)stream);
   } else if (backward_pass_supported(q, bf)) {
     e = launch_backward_pass(q, (hipStream_t)stream);
@@ -667,8 +676,7 @@ int backward_run(const rglru_shape *shape, const rglru_params *params, const voi
     // lies inside the scratch the generic kernels have just used: leave it cleared
     if (e == hipSuccess && bf && shape->D / shape->num_blocks == 256 &&
         (size_t)shape->T * shape->D * 4 < ((size_t)1 << 32))
-      e = launch_clear((char *)workspace + backward_mfma_flag_offset(shape->B, shape->T, shape->D, shape->num_blocks),
-                       16, (hipStream_t)stream);
+      e = launch_clear(workspace, 16, (hipStream_t)stream);
   }
   if (e != hipSuccess) return hip_fail(e, "backward launch");
   g_err[0] = 0;
@@ -708,7 +716,9 @@ int rglru_backward_packed(const rglru_shape *shape, const rglru_params *params, 
   q.ws = workspace; q.ws_bytes = workspace_bytes;
   const bool bf = shape->act_dtype == RGLRU_BF16;
   hipError_t e;
-  if (reset && backward_mfma_supported(q, bf)) {
+  if (backward_tile_supported(q, bf)) {
+    e = launch_backward_tile(q, (hipStream_t)stream);
+  } else if (reset && backward_mfma_supported(q, bf)) {
     e = launch_backward_mfma(q, (hipStream_t)stream);   // the fused kernels take the boundaries as bit masks
   } else {
     e = launch_backward_generic(q, bf, (hipStream_t)stream);
@@ -716,8 +726,7 @@ int rglru_backward_packed(const rglru_shape *shape, const rglru_params *params, 
     // scratch the general kernels have just used: leave it cleared
     if (e == hipSuccess && bf && shape->D / shape->num_blocks == 256 &&
         (size_t)shape->T * shape->D * 4 < ((size_t)1 << 32))
-      e = launch_clear((char *)workspace + backward_mfma_flag_offset(shape->B, shape->T, shape->D, shape->num_blocks),
-                       16, (hipStream_t)stream);
+      e = launch_clear(workspace, 16, (hipStream_t)stream);
   }
   if (e != hipSuccess) return hip_fail(e, "backward launch");
   g_err[0] = 0;
@@ -864,8 +873,9 @@ int rglru_backward_merge(const rglru_shape *shape, const rglru_params *params, c
   q.merge = (flags & RGLRU_MERGE_GELU_TANH) ? 2 : 1; q.branch = branch; q.dbranch = dbranch;
   q.ws = workspace; q.ws_bytes = workspace_bytes;
   hipError_t e;
-  if (shape->D / shape->num_blocks != 256 && backward_pass_supported(q, bf)) {
-    e = launch_backward_pass(q, (hipStream_t)stream);
+  const bool tiles = backward_tile_supported(q, bf);
+  if (tiles || (shape->D / shape->num_blocks != 256 && backward_pass_supported(q, bf))) {
+    e = tiles ? launch_backward_tile(q, (hipStream_t)stream) : launch_backward_pass(q, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "backward launch");
     g_err[0] = 0;
     return RGLRU_OK;

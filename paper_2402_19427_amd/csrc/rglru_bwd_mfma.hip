@@ -627,8 +627,8 @@ struct PrepArgs {
   const unsigned short *Wa, *Wx;
   unsigned short *WTa, *WTx;
   uint4 *wxf;
-  uint4 *zero;
-  size_t n16;   // 16-byte words to clear
+  uint4 *status, *zero;
+  size_t n16;   // 16-byte words to clear at `zero`, in front of them the status word's 256 bytes
   float *sc;    // the scale of the upstream gradient, from the partial maxima behind it
   int nb;
 };
@@ -659,7 +659,8 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(PrepArgs a) {
     return;
   }
   const size_t i = (size_t)(blockIdx.x - nT) * 256 + threadIdx.x;
-  if (i < a.n16) a.zero[i] = cleared_word(a.zero, i, true);
+  if (i < 16) a.status[i] = cleared_word(a.status, i, true);
+  if (i < a.n16) a.zero[i] = make_uint4(0u, 0u, 0u, 0u);
   if (i < (size_t)a.nb * BS * BS / 8) {
     const int lane = (int)(i & 63), ks = (int)((i >> 6) & 15), wv = (int)((i >> 10) & 7), g = (int)(i >> 13);
     const int hf = lane >> 5, j = lane & 31;
@@ -1355,7 +1356,7 @@ BwdPlan plan_backward(int B, int T, int D, int nb, int ncu, bool packed = false)
   if (S > steps / 8) S = steps / 8 > 0 ? steps / 8 : 1;
   q.S = (int)S;
   const size_t N2 = al256((size_t)B * T * D * 2), wbytes = al256((size_t)nb * BS * BS * 2);
-  size_t off = 0;
+  size_t off = 256;   // the status word
   q.off_dp = off; off += N2;
   q.off_dq = off; off += N2;
   q.off_dx = off; off += al256((size_t)B * ((T + 3) / 4) * D * 8);
@@ -1363,7 +1364,7 @@ BwdPlan plan_backward(int B, int T, int D, int nb, int ncu, bool packed = false)
   q.off_wtx = off; off += wbytes;
   q.off_wxf = off; off += wbytes;
   q.off_sc = off; off += SCALE_CELL_BYTES;
-  q.off_rec = off; off += al256(256 + (size_t)q.units * q.R * BS * sizeof(u64));
+  q.off_rec = off; off += al256((size_t)q.units * q.R * BS * sizeof(u64));
   q.off_partA = off; off += al256((size_t)B * q.G * 3 * D * 4);
   q.off_partC = off; off += al256((size_t)B * q.C * 5 * D * 4);
   q.off_partW = off; off += al256((size_t)q.S * 2 * nb * BS * BS * 4);
@@ -1392,12 +1393,6 @@ size_t backward_mfma_ws_bytes(int B, int T, int D, int nb) {
 
 size_t backward_mfma_packed_ws_bytes(int B, int T, int D, int nb) {
   return plan_backward(B, T, D, nb, 256, true).total;
-}
-
-size_t backward_mfma_flag_offset(int B, int T, int D, int nb) {
-  int ncu = num_cu();
-  if (ncu > 256) ncu = 256;
-  return plan_backward(B, T, D, nb, ncu).off_rec;   // the plan the launch uses
 }
 
 template <typename K>
@@ -1463,8 +1458,8 @@ hipError_t launch_backward_mfma(const Problem &p, hipStream_t s) {
   a.p = p;
   a.rmask = packed ? masks : nullptr;
   a.G = q.G; a.ntile = q.ntile; a.R = q.R;
-  a.err = (int *)(ws + q.off_rec);
-  a.rec = (u64 *)(ws + q.off_rec + 256);
+  a.err = (int *)ws;
+  a.rec = (u64 *)(ws + q.off_rec);
   a.dpo = (unsigned short *)(ws + q.off_dp);
   a.dqo = (unsigned short *)(ws + q.off_dq);
   a.dxo = (unsigned char *)(ws + q.off_dx);
@@ -1474,8 +1469,8 @@ hipError_t launch_backward_mfma(const Problem &p, hipStream_t s) {
   a.swizzle = (q.G > 1 && grid % 8 == 0) ? 1 : 0;
   a.wxf = (const unsigned short *)(ws + q.off_wxf);
   // the records only exist (and need clearing) when sequences are sliced in time; the status
-  // word in front of them is cleared in any case (a later health check reads it)
-  const size_t clear = q.G > 1 ? 256 + (size_t)q.units * q.R * BS * sizeof(u64) : 256;
+  // word is cleared in any case (a later health check reads it)
+  const size_t clear = q.G > 1 ? (size_t)q.units * q.R * BS * sizeof(u64) : 0;
   {
     PrepArgs pa;
     pa.Wa = (const unsigned short *)p.W_a; pa.Wx = (const unsigned short *)p.W_x;
@@ -1483,9 +1478,10 @@ hipError_t launch_backward_mfma(const Problem &p, hipStream_t s) {
     pa.wxf = (uint4 *)(ws + q.off_wxf);
     pa.zero = (uint4 *)(ws + q.off_rec);
     pa.n16 = clear / 16;
+    pa.status = (uint4 *)ws;
     pa.nb = p.nb;
     pa.sc = sc;
-    const size_t nfrag = (size_t)p.nb * BS * BS / 8, n = pa.n16 > nfrag ? pa.n16 : nfrag;
+    const size_t nfrag = (size_t)p.nb * BS * BS / 8, n = pa.n16 > nfrag ? pa.n16 : nfrag;   // (more than the status word's 16)
     KernelTimer kt("bwd_prep_kernel", s);
     hipLaunchKernelGGL(bwd_prep_kernel, dim3((unsigned)(128 * p.nb + (n + 255) / 256 + 1)), dim3(256), 0, s, pa);
   }

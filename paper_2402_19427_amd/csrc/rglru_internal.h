@@ -160,6 +160,10 @@ bool backward_pass_shape(const rglru_shape *s);
 bool backward_pass_supported(const Problem &p, bool bf);   // (p.merge: with the merge's adjoint folded in)
 size_t backward_pass_ws_bytes(int B, int T, int D, int nb);
 hipError_t launch_backward_pass(const Problem &p, hipStream_t s);
+// Backward in tiles (rglru_bwd_fused.hip), for the block sizes that have an instance; takes the merge and packed rows
+bool backward_tile_supported(const Problem &p, bool bf);
+size_t backward_tile_ws_bytes(int B, int T, int D, int nb, bool packed, bool merge);   // 0: no instance
+hipError_t launch_backward_tile(const Problem &p, hipStream_t s);
 bool decode_wide_supported(const Problem &p, bool bf);
 hipError_t launch_decode_wide(const Problem &p, hipStream_t s);
 
@@ -181,7 +185,6 @@ hipError_t launch_decode_mfma(const Problem &p, hipStream_t s);
 bool backward_mfma_supported(const Problem &p, bool bf);
 size_t backward_mfma_ws_bytes(int B, int T, int D, int nb);
 size_t backward_mfma_packed_ws_bytes(int B, int T, int D, int nb);   // with the boundary masks of packed sequences (Problem.reset)
-size_t backward_mfma_flag_offset(int B, int T, int D, int nb);   // byte offset of the timeout flag
 hipError_t launch_backward_mfma(const Problem &p, hipStream_t s);
 
 // Scale of the upstream gradient. Gradients are linear in dy: kernels that keep adjoints in half

@@ -31,6 +31,28 @@ __device__ __forceinline__ u32x2 lds_tr(const unsigned char *at) {   // 4 rows x
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void *base, size_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(base), 0, (unsigned)bytes, 0x00020000);
 }
+// byte offset of a place in LDS
+__device__ __forceinline__ unsigned lds_offset(const unsigned char *p) {
+  return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
+}
+// A buffer descriptor as the four words it is (buf() makes the opaque form of the same).
+__device__ __forceinline__ u32x4 buf_words(const void *base, size_t bytes) {
+  const u64 v = (u64)uniform_ptr(base);
+  return u32x4{(unsigned)v, (unsigned)(v >> 32) & 0xffffu, (unsigned)__builtin_amdgcn_readfirstlane((unsigned)bytes), 0x00020000u};
+}
+// The same load written out, for kernels that keep it in flight across LDS reads: behind the builtin the compiler
+// takes any LDS read for one of what it fetches and waits for all of it there. Whoever reads the data waits with an
+// s_waitcnt of its own. (No register is written. The compiler does not count the load: its waits for older or
+// younger loads then wait for more than they need, never for less.)
+// NT: a stream that passes once through the L2s.
+template <bool NT>
+__device__ __forceinline__ void lds16(const u32x4 &rs, unsigned dst, unsigned vo, unsigned so) {   // dst: byte offset in LDS
+  const unsigned at = __builtin_amdgcn_readfirstlane(dst), off = __builtin_amdgcn_readfirstlane(so);
+  if (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" :: "s"(at), "v"(vo), "s"(rs), "s"(off) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(at), "v"(vo), "s"(rs), "s"(off) : "memory");
+}
 // every wave's direct-to-LDS loads have landed (they count as vector-memory loads) and every wave is here
 __device__ __forceinline__ void stage_barrier() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -74,7 +96,7 @@ hipError_t launch_conv_adjoint(const Problem &p, const float *dx, float *part, h
 
 // Partial sums in a fixed order: dW from S slices of [g][gate][bb] (times sc[2] if sc), rowsA from nA
 // rows of nrA vectors of DA channels, rowsC from nC rows of five vectors of D channels; with `edge` (S dx of the
-// first and last three rows of every tile of 256, [B][nrt][6][D]) the rows of du that two tiles share
+// first and last three rows of every tile, [B][nrt][6][D]) the rows of du that two tiles share
 struct FinishArgs {
   const float *partW, *partA, *partC, *sc;
   int S, nA, nrA, DA, nC, D, nb;
@@ -83,6 +105,9 @@ struct FinishArgs {
   const float *edge, *conv_w;
   unsigned short *du;
   int B, T, nrt;
+  int rows = PR;               // rows per tile of `edge`
+  const uint4 *rmask = nullptr;   // packed sequences: boundary masks per 32 steps (as launch_reset_masks leaves them)
+  int nmask = 0;
 };
 hipError_t launch_finish(const FinishArgs &a, hipStream_t s);
 

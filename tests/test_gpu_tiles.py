@@ -1,0 +1,102 @@
+"""The backward in tiles (rglru_bwd_fused.h): tile edges, block sizes either side of a wave's 32 channels, the merge,
+packed rows, time slices, against the float64 oracle; 2^-6 as for the other bf16 kernels (8-bit results, 11-bit products)."""
+import struct
+
+import numpy as np
+import pytest
+
+import oracle
+import rglru_inputs as gen
+
+pytestmark = pytest.mark.gpu
+BF16 = 2.0 ** -6
+
+
+def runner():
+    from paper_2402_19427_amd import runner as rn
+    return rn
+
+
+def f64(inp):
+    return {k: (None if v is None else np.asarray(v, np.float64)) for k, v in inp.items()}
+
+
+def names_of(R):
+    return [R.rglru_timing_get(i)[0] for i in range(R.rglru_timing_count())]
+
+
+@pytest.mark.parametrize("B,T,bs,nb,slices", [
+    (1, 1, 128, 1, 0), (2, 31, 144, 2, 0), (1, 33, 160, 1, 0), (3, 32, 176, 1, 1), (1, 63, 192, 2, 0), (2, 64, 208, 1, 0),
+    (1, 65, 240, 1, 0), (2, 128, 256, 1, 1), (1, 129, 256, 2, 3), (1, 97, 272, 1, 0), (1, 640, 352, 1, 5), (2, 95, 384, 1, 0),
+    (1, 160, 432, 1, 2), (1, 2100, 160, 1, 0)])
+@pytest.mark.parametrize("how", ["plain", "merge", "tanh", "packed"])
+def test_tiles(B, T, bs, nb, slices, how):
+    import torch
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D, act, pos0 = bs * nb, "bf16", 7
+    inp = gen.make_inputs(B, T, D, nb, act=act, seed=T + bs, h0=True, state=True, dy=True, bias=True)
+    dp, q = rn.DeviceProblem(inp, B, T, D, nb, act), f64(inp)
+    u, h0, dhT = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32"), rn.to_device(inp["dhT"], "f32")
+    ring, dy = rn.to_device(gen.ring_from_chrono(inp["state"], pos0), act), rn.to_device(inp["dy"], act)
+    w = (q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"])
+    kw = dict(conv_b=q["conv_b"], h0=q["h0"], state_in=q["state"])
+    dev = dict(h0=h0, state_in=ring, pos0=pos0)
+    # (room for the tiles at every size: what the calls ask for is what each had before there were tiles, and short
+    # packed rows then run on the general kernels)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0")
+    dp.workspace = lambda shape, op: (ws, ws.numel())
+    R.rglru_set_max_time_slices(slices)
+    try:
+        if how == "packed":
+            reset = gen.make_resets(B, T, seed=bs, mean_len=20)
+            rs = torch.from_numpy(reset).cuda()
+            y, _, _ = dp.forward_packed(u, rs, **dev)
+            R.rglru_timing_enable(True)
+            got = dp.backward_packed(u, rs, y, dy, dhT=dhT, **dev)
+            ref = oracle.backward(q["u"], *w, q["dy"], dhT=q["dhT"], reset=reset, **kw)
+        elif how == "plain":
+            y, _, _ = dp.forward(u, **dev)
+            R.rglru_timing_enable(True)
+            got = dp.backward(u, y, dy, dhT=dhT, **dev)
+            ref = oracle.backward(q["u"], *w, q["dy"], dhT=q["dhT"], **kw)
+        else:
+            br, flags = gen.make_branch(B, T, D, act=act, seed=T), R.MERGE_GELU_TANH if how == "tanh" else 0
+            brd = rn.to_device(br, act)
+            _, y, _, _ = dp.forward_merge(u, brd, flags=flags, **dev)
+            R.rglru_timing_enable(True)
+            got = dp.backward_merge(u, brd, y, dy, dhT=dhT, flags=flags, **dev)
+            ref = oracle.backward_merge(q["u"], br, *w, q["dy"], dhT=q["dhT"], approx=how == "tanh", **kw)
+        names = names_of(R)
+    finally:
+        R.rglru_timing_enable(False)
+        R.rglru_set_max_time_slices(0)
+    merged = how in ("merge", "tanh")
+    assert ("tile_prep_kernel" in names) == (not merged or bs <= 352), names   # (LDS does not hold wider tiles with the merge)
+    for k in ref:
+        assert gen.rel_err(rn.to_host(got[k]), ref[k]) < BF16, k
+
+
+@pytest.mark.parametrize("bs", [160, 256])
+def test_a_mark_in_front_of_the_tiles_is_reported_once(bs):
+    """The mark an expired wait leaves (planted from the host): sliced calls return NaN until it has been reported."""
+    import torch
+    import paper_2402_19427_amd as R
+    rn = runner()
+    B, T, act = 1, 700, "bf16"
+    inp = gen.make_inputs(B, T, bs, 1, act=act, seed=3, dy=True)
+    dp = rn.DeviceProblem(inp, B, T, bs, 1, act)
+    u, dy = rn.to_device(inp["u"], act), rn.to_device(inp["dy"], act)
+    y, _, _ = dp.forward(u)
+    ok = dp.backward(u, y, dy)
+    ws, _ = dp.workspace(dp.shape(), R.OP_BACKWARD)
+    ws[:16] = torch.tensor(list(struct.pack("<4I", 0x4c474c52, 0x58452d55, 0x45524950, 0xb3d3b3ad)), dtype=torch.uint8, device="cuda:0")
+    bad = dp.backward(u, y, dy)
+    assert torch.isnan(bad["du"].float()).all()
+    with pytest.raises(R.RglruError) as e:
+        R.rglru_workspace_status(dp.shape(), R.OP_BACKWARD, ws)
+    assert e.value.code == R.ERR_TIMEOUT
+    R.rglru_workspace_status(dp.shape(), R.OP_BACKWARD, ws)
+    again = dp.backward(u, y, dy)
+    for k in ok:
+        assert torch.equal(again[k], ok[k]), k
