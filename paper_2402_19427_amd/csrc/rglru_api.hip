@@ -113,8 +113,12 @@ int check_workspace(const void *ws, size_t have, size_t need) {
 // the forward on the general kernels can do without scratch (one pass, serial in time): a missing
 // or short workspace is not an error there, a misaligned one is
 bool forward_on_general_kernels(const rglru_shape *s);
-int check_forward_workspace(const rglru_shape *s, const void *ws, size_t have, size_t need) {
-  if (!forward_on_general_kernels(s)) return check_workspace(ws, have, need);
+size_t fused_forward_bytes(const rglru_shape *s, bool packed);
+size_t workspace_need(const rglru_shape *s, int op);
+int check_forward_workspace(const rglru_shape *s, const void *ws, size_t have, int op) {
+  if (!forward_on_general_kernels(s))
+    return check_workspace(ws, have, forward_mfma_block(s->D / s->num_blocks) ? fused_forward_bytes(s, op == RGLRU_OP_FORWARD_PACKED)
+                                                                                : workspace_need(s, op));
   if (ws && !aligned(ws, 256)) return fail(RGLRU_ERR_INVALID_ARG, "workspace is not 256-byte aligned");
   return RGLRU_OK;
 }
@@ -199,6 +203,16 @@ size_t least_backward_bytes(const rglru_shape *s) {
   return backward_generic_ws_bytes(s->B, s->T, s->D, s->num_blocks);
 }
 
+// What the fused forward of a shape takes: the least a call has to bring. For gate blocks of 128 - 240 channels the
+// tiles may take more (all weights in half precision, not those of one gate), which the size query asks for.
+size_t fused_forward_bytes(const rglru_shape *s, bool packed) {
+  return forward_mfma_ws_bytes(s->B, s->T, s->D, s->num_blocks) + (packed ? forward_mfma_mask_bytes(s->B, s->T) : 0);
+}
+size_t forward_bytes(const rglru_shape *s, bool packed) {
+  const size_t n = fused_forward_bytes(s, packed);
+  if (s->D / s->num_blocks == 256) return n;
+  return std::max(n, forward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, packed, !packed, n));
+}
 size_t workspace_need(const rglru_shape *s, int op) {
   switch (op) {
     case RGLRU_OP_BACKWARD:   // (the tiles take more than the passes where rows are few)
@@ -212,7 +226,7 @@ size_t workspace_need(const rglru_shape *s, int op) {
       return 0;
     case RGLRU_OP_FORWARD_PACKED:   // the fused kernel's own scratch, then the boundary masks
       if (s->act_dtype == RGLRU_BF16 && forward_mfma_block(s->D / s->num_blocks) && s->T >= 1)
-        return forward_mfma_ws_bytes(s->B, s->T, s->D, s->num_blocks) + forward_mfma_mask_bytes(s->B, s->T);
+        return forward_bytes(s, true);
       return general_forward_bytes(s);
     case RGLRU_OP_BACKWARD_PACKED: {   // fused kernels for blocks of 256 channels (the general kernels remain the
                                        // fallback for loosely aligned pointers), the general kernels otherwise
@@ -234,7 +248,7 @@ size_t workspace_need(const rglru_shape *s, int op) {
     case RGLRU_OP_FORWARD_MERGE:
     case RGLRU_OP_FORWARD:
       if (s->act_dtype == RGLRU_BF16 && forward_mfma_block(s->D / s->num_blocks) && s->T >= 1)
-        return forward_mfma_ws_bytes(s->B, s->T, s->D, s->num_blocks);
+        return forward_bytes(s, false);
       if (s->act_dtype == RGLRU_BF16 && forward_wide_block(s->D / s->num_blocks) && s->T >= 1 &&
           s->D % 256 == 0 && (size_t)s->B * s->T * s->D * 2 < ((size_t)1 << 31))
         return forward_wide_ws_bytes(s->B, s->T, s->D, s->num_blocks);
@@ -321,9 +335,11 @@ int backward_checks(const rglru_shape *shape, const rglru_params *params, const 
 namespace {
 // the forward over whole sequences on the fastest kernels that take the shape; y and the new
 // ring state are written
-int forward_dispatch(const Problem &q, bool bf, hipStream_t s) {
+int forward_dispatch(const Problem &q, bool bf, size_t asked, hipStream_t s) {
   hipError_t e;
-  if (forward_mfma_supported(q, bf)) {
+  if (forward_tile_supported(q, bf, asked)) {
+    e = launch_forward_tile(q, asked, s);
+  } else if (forward_mfma_supported(q, bf)) {
     e = launch_forward_mfma(q, s);  // writes the new ring state itself
   } else if (forward_wide_supported(q, bf) && q.ws &&
              q.ws_bytes >= forward_wide_ws_bytes(q.B, q.T, q.D, q.nb)) {
@@ -413,13 +429,11 @@ int rglru_workspace_status(const rglru_shape *shape, int op, const void *workspa
     return RGLRU_OK;                // the general kernels never wait on each other (their scratch is optional)
   if (!workspace) return fail(RGLRU_ERR_INVALID_ARG, "workspace is NULL");
   size_t off = 0;   // the flag is the first word
-  if ((op == RGLRU_OP_FORWARD || op == RGLRU_OP_FORWARD_MERGE) &&
-      !forward_mfma_block(shape->D / shape->num_blocks))
-    return RGLRU_OK;                // the passes of the other block sizes do not wait on each other
-  // A backward has a status word if it ran on kernels that wait for each other, and that depends on more than the
-  // shape; the others leave data of their own there, which is never the sixteen bytes of the mark.
-  const bool marked = bwd && !(shape->act_dtype == RGLRU_BF16 && shape->D / shape->num_blocks == 256 &&
-                               (size_t)shape->T * shape->D * 4 < ((size_t)1 << 32));
+  // A backward, or a forward of other block sizes than the fused kernel's, has a status word if it ran on kernels that
+  // wait for each other, and that depends on more than the shape; the others leave data of their own there, which is never the sixteen bytes of the mark.
+  const bool fwd_passes = (op == RGLRU_OP_FORWARD || op == RGLRU_OP_FORWARD_MERGE) && !forward_mfma_block(shape->D / shape->num_blocks);
+  const bool marked = fwd_passes || (bwd && !(shape->act_dtype == RGLRU_BF16 && shape->D / shape->num_blocks == 256 &&
+                               (size_t)shape->T * shape->D * 4 < ((size_t)1 << 32)));
   if (bwd && marked && shape->act_dtype != RGLRU_BF16) return RGLRU_OK;
   unsigned word[4] = {0u, 0u, 0u, 0u};
   const unsigned mark[4] = {RGLRU_EXPIRED_WORDS};
@@ -487,7 +501,7 @@ int rglru_forward(const rglru_shape *shape, const rglru_params *params, const vo
   CHECK(check_ptr(hT, "hT", 4, false));
   CHECK(check_ptr(conv_state_in, "conv_state_in", as, false));
   CHECK(check_ptr(conv_state_out, "conv_state_out", as, false));
-  CHECK(check_forward_workspace(shape, workspace, workspace_bytes, workspace_need(shape, RGLRU_OP_FORWARD)));
+  CHECK(check_forward_workspace(shape, workspace, workspace_bytes, RGLRU_OP_FORWARD));
 
   Problem q;
   memset(&q, 0, sizeof(q));
@@ -498,7 +512,7 @@ int rglru_forward(const rglru_shape *shape, const rglru_params *params, const vo
   q.ws = workspace; q.ws_bytes = workspace_bytes;
   const bool bf = shape->act_dtype == RGLRU_BF16;
   hipStream_t s = (hipStream_t)stream;
-  CHECK(forward_dispatch(q, bf, s));
+  CHECK(forward_dispatch(q, bf, workspace_need(shape, RGLRU_OP_FORWARD), s));
   g_err[0] = 0;
   return RGLRU_OK;
 }
@@ -518,7 +532,7 @@ int rglru_forward_packed(const rglru_shape *shape, const rglru_params *params, c
   CHECK(check_ptr(hT, "hT", 4, false));
   CHECK(check_ptr(conv_state_in, "conv_state_in", as, false));
   CHECK(check_ptr(conv_state_out, "conv_state_out", as, false));
-  CHECK(check_forward_workspace(shape, workspace, workspace_bytes, workspace_need(shape, RGLRU_OP_FORWARD_PACKED)));
+  CHECK(check_forward_workspace(shape, workspace, workspace_bytes, RGLRU_OP_FORWARD_PACKED));
 
   Problem q;
   memset(&q, 0, sizeof(q));
@@ -530,7 +544,10 @@ int rglru_forward_packed(const rglru_shape *shape, const rglru_params *params, c
   const bool bf = shape->act_dtype == RGLRU_BF16;
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
-  if (forward_mfma_supported(q, bf)) {
+  const size_t asked = workspace_need(shape, RGLRU_OP_FORWARD_PACKED);
+  if (forward_tile_supported(q, bf, asked)) {
+    e = launch_forward_tile(q, asked, s);
+  } else if (forward_mfma_supported(q, bf)) {
     e = launch_forward_mfma(q, s);   // the fused kernel takes the boundaries as bit masks per tile
   } else if (forward_f32_supported(q, bf)) {   // (no boundaries given: the plain forward)
     e = launch_forward_f32(q, s);
@@ -752,7 +769,7 @@ int rglru_forward_merge(const rglru_shape *shape, const rglru_params *params, co
   CHECK(check_ptr(hT, "hT", 4, false));
   CHECK(check_ptr(conv_state_in, "conv_state_in", as, false));
   CHECK(check_ptr(conv_state_out, "conv_state_out", as, false));
-  CHECK(check_forward_workspace(shape, workspace, workspace_bytes, workspace_need(shape, RGLRU_OP_FORWARD_MERGE)));
+  CHECK(check_forward_workspace(shape, workspace, workspace_bytes, RGLRU_OP_FORWARD_MERGE));
   if (shape->T > 0 && (out == y || out == branch || out == u))
     return fail(RGLRU_ERR_INVALID_ARG, "out must not alias y, branch or u");
 
@@ -769,8 +786,10 @@ int rglru_forward_merge(const rglru_shape *shape, const rglru_params *params, co
   hipError_t e;
   q.merge = tanh_form ? 2 : 1; q.branch = branch; q.out = out; q.y = y;
   const bool fused = forward_mfma_supported(q, bf) && forward_mfma_merge_fused(q);
-  if (!(flags & RGLRU_MERGE_SEPARATE) && (fused || forward_f32_supported(q, bf))) {
-    e = fused ? launch_forward_mfma(q, s) : launch_forward_f32(q, s);
+  const size_t asked = workspace_need(shape, RGLRU_OP_FORWARD_MERGE);
+  const bool tiles = forward_tile_supported(q, bf, asked);
+  if (!(flags & RGLRU_MERGE_SEPARATE) && (tiles || fused || forward_f32_supported(q, bf))) {
+    e = tiles ? launch_forward_tile(q, asked, s) : fused ? launch_forward_mfma(q, s) : launch_forward_f32(q, s);
     if (e != hipSuccess) return hip_fail(e, "forward launch");
     g_err[0] = 0;
     return RGLRU_OK;
@@ -778,7 +797,7 @@ int rglru_forward_merge(const rglru_shape *shape, const rglru_params *params, co
   // without the fused epilogue: y goes to its own buffer, or through `out` when it is not kept
   q.merge = 0;
   q.y = y ? y : out;
-  CHECK(forward_dispatch(q, bf, s));
+  CHECK(forward_dispatch(q, bf, workspace_need(shape, RGLRU_OP_FORWARD), s));
   e = launch_merge_forward(q.y, branch, out, (size_t)shape->B * shape->T * shape->D, bf, tanh_form, s);
   if (e != hipSuccess) return hip_fail(e, "merge launch");
   g_err[0] = 0;
@@ -988,3 +1007,8 @@ int rglru_cg_backward(const rglru_shape *shape, const rglru_cg_params *params, c
 }
 
 }  // extern "C"
+
+size_t rglru::forward_least_bytes(const rglru_shape *s) {
+  return s->act_dtype == RGLRU_BF16 && forward_mfma_block(s->D / s->num_blocks) && s->T >= 1 ? fused_forward_bytes(s, false)
+                                                                                                : workspace_need(s, RGLRU_OP_FORWARD);
+}

@@ -13,6 +13,11 @@
 //   du and the tap sums, the Conv1D's adjoint
 // so that logits, dxd and dx never leave the registers; what the weight gradients need (x, S dp, S dq)
 // leaves as it lies in LDS, time fastest, which is what they contract over.
+// B 16 T 4096, 16 blocks of 256 channels: 1.15 ms for what took two kernels 1.62 ms (gates and adjoints 1.09, products
+// and Conv1D 0.53), 1.64 GB read and 2.1 GB written, which is what goes in and out, 3.9 and 2.3 GB before. Bound by the
+// vector unit (busy 60 % of the time: some 60 instructions per element, 10 of them transcendental) and what two waves
+// per SIMD cannot hide of the barriers around the two products. Tiles of 64 steps where registers allow two waves
+// per SIMD to hold them (halves the weights' way from L2), of 32 elsewhere.
 //
 // Layouts. Each wave owns a region of LDS: U (u as it comes, 64 bytes a row and four rows in front; then S dq as
 // [channel][step]), X (x as [channel][step]; then S dp; then du), Y, DY (y and dy as they come), with the merge B
@@ -45,11 +50,13 @@ struct FusedArgs {
 };
 
 constexpr int V_PLAIN = 0, V_MERGE = 1, V_MERGE_TANH = 2, V_PACKED = 3;
-template <int MT, int VAR>
+template <int MT, int VAR, bool TIGHT = false>
 struct Lds {
   static constexpr bool MERGE = VAR == V_MERGE || VAR == V_MERGE_TANH;
   static constexpr int TM = 32 * MT;
-  static constexpr int UROWS = TM + 16;   // (the loads come in sixteens; TM + 4 are used)
+  // The loads come in sixteens; TM + 4 rows are used. TIGHT: there is no room for the others (512 channels: 16 waves in
+  // 160 KB), and their lanes are switched off.
+  static constexpr int UROWS = TM + (TIGHT ? 4 : 16);
   static constexpr int U = 0, X = UROWS * 64, Y = X + TM * 64, DY = Y + (MERGE ? UROWS : TM) * 64, B = DY + TM * 64,
                        C = B + (MERGE ? TM * 64 : 0);   // constants of the wave's channels: 12 floats each
   static constexpr int P = X, Q = U;     // S dp, S dq: where x and u lay
@@ -101,7 +108,8 @@ __device__ __forceinline__ void cvt_f16x8(const float (&v)[8], unsigned (&o)[4])
 template <int NCT, int MT, int VAR, int WPE, int PD, int K>
 __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) bwd_tile_kernel(FusedArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  typedef Lds<MT, VAR> L;
+  constexpr bool TIGHT = NCT == 16;
+  typedef Lds<MT, VAR, TIGHT> L;
   constexpr bool MERGE = L::MERGE, PACKED = VAR == V_PACKED, KEEP = K >= 1, KEEPA = K >= 2;
   constexpr int TM = L::TM, NKS = 2 * NCT;
   const Problem &p = a.p;
@@ -170,7 +178,7 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
 
   // ---- a tile's inputs, straight into the wave's own rows of LDS (nothing else reads them, so that a wave waits for
   // its own loads only). NU loads of u, NY of y, TM / 16 of dy, as many of the other branch.
-  constexpr int NU = L::UROWS / 16, NY = MERGE ? NU : TM / 16;
+  constexpr int NU = TM / 16 + 1, NY = MERGE ? NU : TM / 16;
   constexpr int LOAD_U = 1, LOAD_Y = 2;
   auto load_tile = [&](int tile, int which) __attribute__((always_inline)) {
     const int t0 = tile * TM, back = t0 > 0 ? 4 : 0;
@@ -186,7 +194,8 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
       lds16<true>(rs, dst, lead, 0);
 #pragma unroll
       for (int m = 1; m < NU; ++m)
-        lds16<true>(rs, dst + m * 1024, m == NU - 1 && l >= 16 ? OOB : ld_vo, (unsigned)(16 * m - 4 + back) * row2);
+        if (!TIGHT || m < NU - 1) lds16<true>(rs, dst + m * 1024, m == NU - 1 && l >= 16 ? OOB : ld_vo, (unsigned)(16 * m - 4 + back) * row2);
+        else if (l < 16) lds16<true>(rs, dst + m * 1024, ld_vo, (unsigned)(16 * m - 4 + back) * row2);
     };
     auto rows = [&](const void *src, unsigned dst) __attribute__((always_inline)) {
       const u32x4 rs = buf_words((const unsigned short *)src + (seq + t0) * D, (size_t)nrow * row2);
@@ -693,7 +702,7 @@ struct Instance {
 };
 template <int NCT, int MT, int VAR, int WPE, int PD, int K>
 Instance instance() {
-  constexpr int lds = NCT * Lds<MT, VAR>::REGION, by_lds = 160 * 1024 / lds, by_waves = 4 * WPE / NCT;
+  constexpr int lds = NCT * Lds<MT, VAR, NCT == 16>::REGION, by_lds = 160 * 1024 / lds, by_waves = 4 * WPE / NCT;
   if constexpr (lds <= 160 * 1024) return {(const void *)bwd_tile_kernel<NCT, MT, VAR, WPE, PD, K>, NCT, MT, lds, by_lds < by_waves ? by_lds : by_waves};
   else return {nullptr, 0, 0, 0, 0};   // (the widest blocks with the merge)
 }

@@ -1,5 +1,5 @@
 // The backward in tiles (see rglru_bwd_fused.h): preparation, weight gradients, dispatch.
-#include "rglru_bwd_fused.h"
+#include "rglru_fwd_tile.h"
 
 #include <algorithm>
 #include <atomic>
@@ -22,7 +22,7 @@ struct PrepArgs {
   int nb, bs, nct;
 };
 __global__ void __launch_bounds__(256) tile_prep_kernel(PrepArgs a) {
-  if (blockIdx.x == gridDim.x - 1) {
+  if (a.sc && blockIdx.x == gridDim.x - 1) {
     scale_from_parts(a.sc, 4);
     return;
   }
@@ -31,7 +31,7 @@ __global__ void __launch_bounds__(256) tile_prep_kernel(PrepArgs a) {
   if (i < a.nrec) a.rec[i] = make_uint4(0u, 0u, 0u, 0u);
   const int nks = 2 * a.nct;
   const size_t per = (size_t)a.nb * a.nct * nks * 2 * 64;
-  if (i >= 2 * per) return;
+  if (i >= (a.wd ? 2 * per : per)) return;
   const bool tr = i >= per;
   size_t f = tr ? i - per : i;
   const int lane = (int)(f & 63);
@@ -52,7 +52,8 @@ __global__ void __launch_bounds__(256) tile_prep_kernel(PrepArgs a) {
 }
 
 // Partial maxima of |dout GeLU(branch)| and |dhT|, one per workgroup of SCALE_PARTS (as absmax_kernel
-// leaves them for a dy handed in): 16 bytes of both per lane, four pairs in flight.
+// leaves them for a dy handed in): 16 bytes of both per lane, four pairs in flight. Read at the rate of memory
+// (B 8 T 2048, 2560 channels: 48 us, 168 MB).
 template <bool TANH>
 __global__ void __launch_bounds__(256) absmax_merge_kernel(const u32x4 *dout, const u32x4 *branch, size_t n8, const float *w, size_t nw,
                                                            unsigned *parts) {
@@ -93,6 +94,10 @@ __global__ void __launch_bounds__(256) absmax_merge_kernel(const u32x4 *dout, co
 // workgroup of four waves, 64 x 128 each. Both operands lie time fastest, so that a fragment is one 16-byte
 // read; stages of 32 steps (256 + 128 rows of 64 bytes, pieces permuted by the row) by direct-to-LDS loads,
 // three buffers, two stages in flight (a counted wait: each wave loads six pieces of 16 rows per stage).
+// Bound by the operands' way into LDS: 24 KB per stage for 32 products of a wave. B 16 T 4096, 16 blocks of 256
+// channels: 437 us (0.63 PFLOP/s; 476 as it was, with x formed again from u); 780 with the loads marked streaming:
+// neighbouring workgroups share rows and want them in L2. Blocks that do not fill 256 x 128 pay for the rest: 160
+// channels use 39 % of their products.
 constexpr int WT_A = 256 * 64, WT_B = 128 * 64, WT_STAGE = WT_A + WT_B, WT_LDS = 3 * WT_STAGE;
 static_assert(WT_LDS <= 80 * 1024, "two workgroups per CU");
 struct WgradArgs {
@@ -224,23 +229,6 @@ Plan make_plan(int B, int T, int D, int nb, bool packed, const Instance &in, siz
   q.total = off + std::max(first, q.S * one);
   return q;
 }
-// these kernels ask for more than the default LDS limit; told once per instance
-hipError_t configure(const Instance &in) {
-  static std::atomic<const void *> done[64];
-  for (auto &d : done) {
-    const void *k = d.load();
-    if (k == in.kernel) return hipSuccess;
-    if (k) continue;
-    hipError_t e = hipFuncSetAttribute(in.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, in.lds);
-    if (e == hipSuccess) e = big_lds(tile_wgrad_kernel, WT_LDS);
-    if (e != hipSuccess) return e;
-    const void *none = nullptr;
-    if (d.compare_exchange_strong(none, in.kernel)) return hipSuccess;
-    if (none == in.kernel) return hipSuccess;
-  }
-  return hipFuncSetAttribute(in.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, in.lds);
-}
-int compute_units() { return std::min(num_cu(), 256); }
 
 // What is staged 16 bytes at a time lies on that grid or is copied there first, behind the plan; blocks of other sizes
 // than the fused kernels' bring the room for that whatever their tensors' alignment is, so that results do not
@@ -257,6 +245,36 @@ bool shape_ok(int B, int T, int D, int nb) {
 }
 
 }  // namespace
+
+// these kernels ask for more than the default LDS limit; told once per instance
+hipError_t fused::configure(const Instance &in) {
+  static std::atomic<const void *> done[128];
+  for (auto &d : done) {
+    const void *k = d.load();
+    if (k == in.kernel) return hipSuccess;
+    if (k) continue;
+    hipError_t e = hipFuncSetAttribute(in.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, in.lds);
+    if (e != hipSuccess) return e;
+    const void *none = nullptr;
+    if (d.compare_exchange_strong(none, in.kernel)) return hipSuccess;
+    if (none == in.kernel) return hipSuccess;
+  }
+  return hipFuncSetAttribute(in.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, in.lds);
+}
+int fused::compute_units() { return std::min(num_cu(), 256); }
+
+hipError_t fused::launch_tile_prep(const Problem &p, int nct, u32x4 *wg, u32x4 *wd, void *status, void *rec, size_t nrec, float *sc, hipStream_t s) {
+  KernelTimer kt("tile_prep_kernel", s);
+  PrepArgs a;
+  a.W[0] = (const unsigned short *)p.W_a; a.W[1] = (const unsigned short *)p.W_x;
+  a.wg = wg; a.wd = wd;
+  a.zero = (uint4 *)status; a.n16 = 16;
+  a.rec = (uint4 *)rec; a.nrec = nrec;
+  a.sc = sc; a.nb = p.nb; a.bs = p.bs; a.nct = nct;
+  const size_t frags = (size_t)p.nb * nct * nct * 4 * 64 * (wd ? 2 : 1), m = std::max(std::max(frags, nrec), (size_t)16);
+  hipLaunchKernelGGL(tile_prep_kernel, dim3((unsigned)((m + 255) / 256 + (sc ? 1 : 0))), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
 
 bool backward_tile_supported(const Problem &p, bool bf) {
   if (!bf || p.dy_lo || !shape_ok(p.B, p.T, p.D, p.nb) || (uintptr_t)p.ws % 16 != 0) return false;
@@ -302,28 +320,16 @@ hipError_t launch_backward_tile(const Problem &call, hipStream_t s) {
   }
   uint4 *masks = (uint4 *)(ws + q.off_masks);
   if (p.reset && (e = launch_reset_masks(p.reset, masks, nullptr, p.B, p.T, s)) != hipSuccess) return e;
-  {
-    KernelTimer kt("tile_prep_kernel", s);
-    // the status word; and the records, behind the weights
-    PrepArgs a;
-    a.W[0] = (const unsigned short *)p.W_a; a.W[1] = (const unsigned short *)p.W_x;
-    a.wg = (u32x4 *)(ws + q.off_w); a.wd = (u32x4 *)(ws + q.off_w + q.wbytes);
-    a.zero = (uint4 *)ws; a.n16 = 16;
-    a.rec = (uint4 *)(ws + q.off_rec);
-    a.nrec = q.G > 1 ? (size_t)p.B * p.nb * q.R * q.nct * 32 * sizeof(u64) / 16 : 0;
-    a.sc = sc; a.nb = p.nb; a.bs = p.bs; a.nct = q.nct;
-    const size_t frags = 2 * q.wbytes / 16;
-    const size_t m = std::max(std::max(frags, a.nrec), (size_t)16);
-    hipLaunchKernelGGL(tile_prep_kernel, dim3((unsigned)((m + 255) / 256 + 1)), dim3(256), 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
+  u32x4 *wg = (u32x4 *)(ws + q.off_w), *wd = (u32x4 *)(ws + q.off_w + q.wbytes);
+  const size_t nrec = q.G > 1 ? (size_t)p.B * p.nb * q.R * q.nct * 32 * sizeof(u64) / 16 : 0;
+  if ((e = launch_tile_prep(p, q.nct, wg, wd, ws, ws + q.off_rec, nrec, sc, s)) != hipSuccess) return e;
   FusedArgs a;
   a.p = p;
   a.G = q.G; a.ntile = q.ntile; a.R = q.R;
   a.total = (unsigned)(p.B * p.nb * q.G);
   a.rec = (u64 *)(ws + q.off_rec);
   a.err = (int *)ws;
-  a.wg = (const u32x4 *)(ws + q.off_w); a.wd = (const u32x4 *)(ws + q.off_w + q.wbytes);
+  a.wg = wg; a.wd = wd;
   a.xT = (unsigned short *)(ws + q.off_x); a.pqT = (unsigned short *)(ws + q.off_pq);
   a.sc = sc;
   a.partA = (float *)(ws + q.off_partA); a.partC = (float *)(ws + q.off_partC);
@@ -336,6 +342,11 @@ hipError_t launch_backward_tile(const Problem &call, hipStream_t s) {
     if ((e = hipLaunchKernel(in.kernel, dim3(grid8(a.total)), dim3(in.waves * 64), args, in.lds, s)) != hipSuccess) return e;
   }
   {
+    static std::atomic<bool> configured{false};
+    if (!configured.load()) {
+      if ((e = big_lds(tile_wgrad_kernel, WT_LDS)) != hipSuccess) return e;
+      configured.store(true);
+    }
     KernelTimer kt("wgrad_pass_kernel", s);
     WgradArgs w;
     w.pqT = a.pqT; w.xT = a.xT; w.part = (float *)(ws + q.off_partW);

@@ -164,6 +164,12 @@ hipError_t launch_backward_pass(const Problem &p, hipStream_t s);
 bool backward_tile_supported(const Problem &p, bool bf);
 size_t backward_tile_ws_bytes(int B, int T, int D, int nb, bool packed, bool merge);   // 0: no instance
 hipError_t launch_backward_tile(const Problem &p, hipStream_t s);
+// Forward in tiles (rglru_fwd_tile.hip), for the block sizes that have an instance; takes the merge and packed rows.
+// asked: the workspace the call asks for
+size_t forward_tile_ws_bytes(int B, int T, int D, int nb, bool packed, bool merge, size_t room);   // 0: no instance
+bool forward_tile_supported(const Problem &p, bool bf, size_t asked);
+hipError_t launch_forward_tile(const Problem &p, size_t asked, hipStream_t s);
+size_t forward_least_bytes(const rglru_shape *shape);   // what rglru_forward has to be given at least
 bool decode_wide_supported(const Problem &p, bool bf);
 hipError_t launch_decode_wide(const Problem &p, hipStream_t s);
 

@@ -1,4 +1,4 @@
-"""The backward in tiles (rglru_bwd_fused.h): tile edges, block sizes either side of a wave's 32 channels, the merge,
+"""The kernels in tiles (rglru_bwd_fused.h, rglru_fwd_tile.h): tile edges, block sizes either side of a wave's 32 channels, the merge,
 packed rows, time slices, against the float64 oracle; 2^-6 as for the other bf16 kernels (8-bit results, 11-bit products)."""
 import struct
 
@@ -28,7 +28,7 @@ def names_of(R):
 @pytest.mark.parametrize("B,T,bs,nb,slices", [
     (1, 1, 128, 1, 0), (2, 31, 144, 2, 0), (1, 33, 160, 1, 0), (3, 32, 176, 1, 1), (1, 63, 192, 2, 0), (2, 64, 208, 1, 0),
     (1, 65, 240, 1, 0), (2, 128, 256, 1, 1), (1, 129, 256, 2, 3), (1, 97, 272, 1, 0), (1, 640, 352, 1, 5), (2, 95, 384, 1, 0),
-    (1, 160, 432, 1, 2), (1, 2100, 160, 1, 0)])
+    (1, 160, 432, 1, 2), (1, 2100, 160, 1, 0), (1, 33, 512, 1, 0), (2, 129, 496, 1, 2)])
 @pytest.mark.parametrize("how", ["plain", "merge", "tanh", "packed"])
 def test_tiles(B, T, bs, nb, slices, how):
     import torch
@@ -75,6 +75,55 @@ def test_tiles(B, T, bs, nb, slices, how):
     assert ("tile_prep_kernel" in names) == (not merged or bs <= 352), names   # (LDS does not hold wider tiles with the merge)
     for k in ref:
         assert gen.rel_err(rn.to_host(got[k]), ref[k]) < BF16, k
+
+
+@pytest.mark.parametrize("B,T,bs,nb,slices", [
+    (1, 1, 128, 1, 0), (2, 33, 128, 2, 0), (1, 129, 144, 2, 0), (1, 700, 160, 2, 3), (2, 160, 176, 1, 0), (1, 191, 192, 1, 1),
+    (1, 257, 208, 1, 0), (1, 3000, 256, 2, 0), (3, 319, 256, 1, 4), (1, 320, 240, 1, 0), (1, 2, 320, 4, 0), (2, 31, 384, 2, 0),
+    (1, 97, 448, 4, 2), (1, 64, 480, 8, 0), (1, 33, 512, 1, 0)])
+@pytest.mark.parametrize("how", ["plain", "merge", "tanh", "packed"])
+def test_forward_tiles(B, T, bs, nb, slices, how):
+    """The forward: y, the merge's product, the last state and the ring handed on, in place."""
+    import torch
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D, act, pos0 = bs * nb, "bf16", 5
+    if how == "packed" and bs > 256:
+        pytest.skip("packed rows of such blocks run on the general kernels")
+    inp = gen.make_inputs(B, T, D, nb, act=act, seed=T + bs, h0=True, state=True, bias=True)
+    dp, q = rn.DeviceProblem(inp, B, T, D, nb, act), f64(inp)
+    u, h0 = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32")
+    ring = rn.to_device(gen.ring_from_chrono(inp["state"], pos0), act)
+    w = (q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"])
+    kw = dict(conv_b=q["conv_b"], h0=q["h0"], state_in=q["state"])
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0")
+    dp.workspace = lambda shape, op: (ws, ws.numel())
+    R.rglru_set_max_time_slices(slices)
+    R.rglru_timing_enable(True)
+    try:
+        out = None
+        if how == "packed":
+            reset = gen.make_resets(B, T, seed=bs, mean_len=20)
+            y, hT, st = dp.forward_packed(u, torch.from_numpy(reset).cuda(), h0=h0, state_in=ring, pos0=pos0)
+            want = oracle.forward(q["u"], *w, reset=reset, **kw)
+        elif how == "plain":
+            y, hT, st = dp.forward(u, h0=h0, state_in=ring, pos0=pos0)
+            want = oracle.forward(q["u"], *w, **kw)
+        else:
+            br, flags = gen.make_branch(B, T, D, act=act, seed=T), R.MERGE_GELU_TANH if how == "tanh" else 0
+            out, y, hT, st = dp.forward_merge(u, rn.to_device(br, act), flags=flags, h0=h0, state_in=ring, pos0=pos0)
+            want = oracle.forward(q["u"], *w, **kw)
+        names = names_of(R)
+    finally:
+        R.rglru_timing_enable(False)
+        R.rglru_set_max_time_slices(0)
+    if D % 256 == 0 or bs <= 256:
+        assert ("tile_prep_kernel" in names) == (bs <= 480), names
+    assert gen.rel_err(rn.to_host(y), want[0]) < BF16
+    assert gen.rel_err(rn.to_host(hT), want[1]) < BF16
+    np.testing.assert_array_equal(rn.to_host(st), gen.ring_from_chrono(np.asarray(want[2], np.float32), pos0 + T))
+    if out is not None:
+        assert gen.rel_err(rn.to_host(out), oracle.merge(want[0], br, approx=how == "tanh")) < BF16
 
 
 @pytest.mark.parametrize("bs", [160, 256])
