@@ -53,7 +53,7 @@ __global__ void __launch_bounds__(256) tile_prep_kernel(PrepArgs a) {
 
 // Partial maxima of |dout GeLU(branch)| and |dhT|, one per workgroup of SCALE_PARTS (as absmax_kernel
 // leaves them for a dy handed in): 16 bytes of both per lane, four pairs in flight. Read at the rate of memory
-// (B 8 T 2048, 2560 channels: 48 us, 168 MB).
+// (B 8 T 2048, 2560 channels: 39 us, 168 MB, 4.3 TB/s).
 template <bool TANH>
 __global__ void __launch_bounds__(256) absmax_merge_kernel(const u32x4 *dout, const u32x4 *branch, size_t n8, const float *w, size_t nw,
                                                            unsigned *parts) {
@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(256) absmax_merge_kernel(const u32x4 *dout, co
 // read; stages of 32 steps (256 + 128 rows of 64 bytes, pieces permuted by the row) by direct-to-LDS loads,
 // three buffers, two stages in flight (a counted wait: each wave loads six pieces of 16 rows per stage).
 // Bound by the operands' way into LDS: 24 KB per stage for 32 products of a wave. B 16 T 4096, 16 blocks of 256
-// channels: 437 us (0.63 PFLOP/s; 476 as it was, with x formed again from u); 780 with the loads marked streaming:
+// channels: 346 us (0.79 PFLOP/s; 490 as it was, with x formed again from u); twice that with the loads marked streaming:
 // neighbouring workgroups share rows and want them in L2. Blocks that do not fill 256 x 128 pay for the rest: 160
 // channels use 39 % of their products.
 constexpr int WT_A = 256 * 64, WT_B = 128 * 64, WT_STAGE = WT_A + WT_B, WT_LDS = 3 * WT_STAGE;
