@@ -45,6 +45,7 @@ def algorithmic_costs(B, T, D, nb, B_dec):
         # u_t, 3 ring slots read + 1 written, h read + written, y_t, weights
         "decode_mfma_kernel": dict(bytes=(2 + 6 + 2 + 4 + 4 + 2) * B_dec * D + w_bytes + vec,
                                    flops=4 * bs * B_dec * D),
+        "apply_kernel": dict(bytes=4 * N + w_bytes + vec + 10 * B * D, flops=gemm),   # the forward in tiles
         # the backward in tiles: u, y, dy in, du out; the gates and dx (adjoint_kernel), dW out (wgrad_pass_kernel)
         "adjoint_kernel": dict(bytes=8 * N + w_bytes + vec + 8 * B * D, flops=2 * gemm),
         "wgrad_pass_kernel": dict(bytes=2 * nb * bs * bs * 4, flops=gemm),
