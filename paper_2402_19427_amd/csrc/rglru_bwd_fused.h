@@ -318,8 +318,13 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
     };
     float xk[KEEP ? MT : 1][16];
     const bool ragged = (int)nrow < TM;
-    int valid = (int)nrow - hf * 16;   // of this lane's steps (of row block 0)
-    asm volatile("" : "+v"(valid));
+    auto left = [&]() __attribute__((always_inline)) { return (int)nrow - (lane_again() >> 5) * 16; };   // of this lane's steps (of row block 0)
+    // pairs of 16-bit values of a lane's steps: nothing of those past the end
+    auto cut = [&](unsigned (&v)[8], int rb) __attribute__((always_inline)) {
+      const int valid = left() - rb * 32;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = valid - 2 * e > 1 ? v[e] : valid - 2 * e == 1 ? v[e] & 0xffffu : 0u;
+    };
 #pragma unroll
     for (int rb = 0; rb < MT; ++rb) {
       unsigned uu[10], pk[8];
@@ -340,12 +345,15 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
         for (int e = 0; e < 4; ++e) pk[4 * h + e] = o[e];
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (ragged)   // nothing of the steps past the end
+      if (ragged) {
+        cut(pk, rb);
+        if constexpr (KEEP) {
+          const int valid = left();
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int left = valid - rb * 32 - 2 * e;
-          pk[e] = left > 1 ? pk[e] : left == 1 ? pk[e] & 0xffffu : 0u;
+          for (int r = 0; r < 16; ++r)
+            if (r + rb * 32 >= valid) xk[rb][r] = 0.f;
         }
+      }
       put16(my + L::X, rb, pk);
     }
     // ---- the upstream gradient (with the merge: dy = dout GeLU(branch) in fp32, dbranch = dout y GeLU'(branch))
@@ -388,7 +396,8 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
     // ---- gate pre-activations
     f32x16 accp[MT], accq[MT];
     const f32x4 con = *(const f32x4 *)(my + L::C + j * 48);
-    const float bp = con[0], bq = con[1], kdn = con[2], kd = kdn * LOG2E;
+    // (kd: within what the 2^-126 of a gate held closed still takes to nothing)
+    const float bp = con[0], bq = con[1], kdn = con[2], kd = kdn * LOG2E < -1e30f ? -1e30f : kdn * LOG2E;
 #pragma unroll
     for (int rb = 0; rb < MT; ++rb)
 #pragma unroll
@@ -396,13 +405,16 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
         accp[rb][r] = bp;
         accq[rb][r] = bq;
       }
-    // (steps past the end: a closed gate, a_t = 1 and m_t = 0, lets eps pass and adds nothing)
-    if (ragged)
+    // Steps past the end: a closed gate, a_t = 1 and m_t = 0, lets eps pass; with x and h_{t-1} taken as zero there they add
+    // nothing, whatever the sequence's last inputs (which the Conv1D reaches back to) and its last state are
+    if (ragged) {
+      const int valid = left();
 #pragma unroll
       for (int rb = 0; rb < MT; ++rb)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           if (r + rb * 32 >= valid) accp[rb][r] = -__builtin_huge_valf();
+    }
     {
       f16x8 fa[2][MT];
 #pragma unroll
@@ -518,6 +530,9 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
         rows_of(my + L::Y, rb, 0, 4, yv);
         rows_of(my + L::DY, rb, 0, 4, dyv);
       }
+      if (ragged) cut(yv, rb);
+      int valid = 0;
+      if constexpr (!KEEP) valid = left();
       if (rb == 0) {   // the next tile's y and dy (and branch): in front of a stretch that needs nothing from memory
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (tile - G >= 0) load_tile(tile - G, LOAD_Y);
@@ -529,7 +544,7 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
       for (int r = 15; r >= 0; --r) {
         float xv;
         if constexpr (KEEP) xv = xk[rb][r];
-        else xv = conv(ul[rb], tap2, cbias2, rb, r);
+        else xv = r + rb * 32 < valid ? conv(ul[rb], tap2, cbias2, rb, r) : 0.f;
         const float rv = __builtin_amdgcn_rcpf(1.f + ep[rb][r]), l2 = kd * rv;
         float av;
         if constexpr (KEEPA) av = ak[rb][r];

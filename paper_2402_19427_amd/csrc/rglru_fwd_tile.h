@@ -184,8 +184,7 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
     }
     // ---- Conv1D
     const bool ragged = (int)nrow < TM;
-    int valid = (int)nrow - hf * 16;   // of this lane's steps (of row block 0)
-    asm volatile("" : "+v"(valid));
+    auto left = [&]() __attribute__((always_inline)) { return (int)nrow - (lane_again() >> 5) * 16; };   // of this lane's steps (of row block 0)
     float x[MT][16];
     unsigned pk[MT][8];
     {
@@ -217,10 +216,12 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
           for (int e = 0; e < 4; ++e) pk[rb][4 * h + e] = o[e];
           __builtin_amdgcn_sched_barrier(0);
         }
-        if (ragged)   // nothing of the steps past the end
+        if (ragged) {   // nothing of the steps past the end
+          const int valid = left();
 #pragma unroll
           for (int r = 0; r < 16; ++r)
             if (r + rb * 32 >= valid) x[rb][r] = 0.f;
+        }
       }
     }
     lds_barrier();   // (every wave has read the last tile's x)
@@ -231,7 +232,8 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
     // ---- gate pre-activations
     f32x16 accp[MT], accq[MT];
     const f32x4 con = *(const f32x4 *)(my + L::C + j * 48);
-    const float kd = con[2] * LOG2E;
+    // (finite, so that times the r_t = 0 of a closed gate it is 0 and not a NaN)
+    const float kd = con[2] * LOG2E < -3e38f ? -3e38f : con[2] * LOG2E;
 #pragma unroll
     for (int rb = 0; rb < MT; ++rb)
 #pragma unroll
@@ -239,13 +241,6 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
         accp[rb][r] = con[0];
         accq[rb][r] = con[1];
       }
-    // (steps past the end: a closed gate, a_t = 1 and m_t = 0, leaves the state untouched)
-    if (ragged)
-#pragma unroll
-      for (int rb = 0; rb < MT; ++rb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (r + rb * 32 >= valid) accp[rb][r] = -__builtin_huge_valf();
     {
       f16x8 fa[2][MT];
 #pragma unroll
@@ -264,6 +259,16 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
         if (ks + PD < NKS) load_w(ks + PD);
         __builtin_amdgcn_sched_barrier(0);
       }
+    }
+    // Steps past the end: closed gates, a_t = 1 and m_t = i_t = 0, leave the state untouched. (Set behind the products:
+    // the Conv1D reaches back into the sequence there, and an infinity among its last inputs would come through.)
+    if (ragged) {
+      const int valid = left();
+#pragma unroll
+      for (int rb = 0; rb < MT; ++rb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (r + rb * 32 >= valid) accp[rb][r] = accq[rb][r] = -__builtin_huge_valf();
     }
     // the next tile's inputs, in front of the longest stretch that needs nothing from memory
     unsigned br[MERGE ? MT : 1][8];

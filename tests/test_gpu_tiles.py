@@ -149,3 +149,94 @@ def test_a_mark_in_front_of_the_tiles_is_reported_once(bs):
     again = dp.backward(u, y, dy)
     for k in ok:
         assert torch.equal(again[k], ok[k]), k
+
+
+@pytest.mark.parametrize("bs,nb,T", [(128, 2, 33), (160, 2, 161), (192, 2, 130), (240, 2, 321), (256, 2, 321), (384, 2, 289), (448, 4, 333)])
+@pytest.mark.parametrize("how", ["plain", "merge", "packed"])
+def test_state_behind_infinite_last_inputs(bs, nb, T, how):
+    """T is no multiple of the tile: the Conv1D of the steps past the end still sees the last inputs. The state handed on is that of
+    the last step whatever they hold (one infinity per block, in its first and in its last step of reach; a decay of zero):
+    y in more digits, so that the two differ by half an ulp of bf16."""
+    import torch
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D, act = bs * nb, "bf16"
+    inp = gen.make_inputs(1, T, D, nb, act=act, seed=T + bs, h0=True, bias=True)
+    inp["u"][0, T - 1, 3] = np.inf
+    inp["u"][0, T - 3, bs + 5] = -np.inf
+    inp["Lambda"][7] = -1e38
+    dp = rn.DeviceProblem(inp, 1, T, D, nb, act)
+    u, h0 = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32")
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0")
+    dp.workspace = lambda shape, op: (ws, ws.numel())
+    R.rglru_timing_enable(True)
+    try:
+        if how == "packed":
+            y, hT, _ = dp.forward_packed(u, torch.from_numpy(gen.make_resets(1, T, seed=bs, mean_len=20)).cuda(), h0=h0)
+        elif how == "plain":
+            y, hT, _ = dp.forward(u, h0=h0)
+        else:
+            _, y, hT, _ = dp.forward_merge(u, rn.to_device(gen.make_branch(1, T, D, act=act, seed=1), act), h0=h0)
+        torch.cuda.synchronize()
+        names = names_of(R)
+    finally:
+        R.rglru_timing_enable(False)
+    assert "tile_prep_kernel" in names, names
+    last, hT = rn.to_host(y)[0, -1].astype(np.float64), rn.to_host(hT)[0].astype(np.float64)
+    ok = np.isfinite(last)
+    assert ok.sum() >= D - 2
+    np.testing.assert_array_equal(np.isfinite(hT), ok)
+    assert (np.abs(hT[ok] - last[ok]) <= np.abs(hT[ok]) * 2.0 ** -8 + 1e-37).all()
+
+
+@pytest.mark.parametrize("bs,nb,T", [(112, 2, 33), (160, 2, 70), (256, 2, 97), (352, 2, 50), (416, 1, 33), (512, 1, 45)])
+@pytest.mark.parametrize("how", ["plain", "merge", "packed"])
+def test_backward_of_a_ragged_tile_ignores_what_lies_past_the_end(bs, nb, T, how):
+    """The last y would be h_{t-1} of the first step past the end only (with the merge of dbranch's last step, too): not a bit may depend
+    on it. And the Conv1D past the end, infinite here where no step inside the sequence is, adds nothing to any gradient: the channel's gates
+    are closed (i_t x_t stays below 2), and the one gradient that takes its inputs as they are is left out."""
+    import torch
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D, act = bs * nb, "bf16"
+    inp = gen.make_inputs(1, T, D, nb, act=act, seed=T + bs, dy=True, bias=True)
+    c = 5
+    inp["u"][0, T - 1, c] = gen.round_to_act(np.array([3e38], np.float32), act)[0]
+    inp["conv_w"][:, c] = (0.25, 4.0, 0.0, 0.0)
+    inp["W_a"][0, c], inp["W_x"][0, c], inp["b_x"][c] = 0.0, 0.0, -100.0
+    dp = rn.DeviceProblem(inp, 1, T, D, nb, act)
+    u, dy, dhT = rn.to_device(inp["u"], act), rn.to_device(inp["dy"], act), rn.to_device(inp["dhT"], "f32")
+    y = rn.to_device(np.random.default_rng(bs).standard_normal((1, T, D), dtype=np.float32), act)
+    br = rn.to_device(gen.make_branch(1, T, D, act=act, seed=T), act)
+    reset = torch.from_numpy(gen.make_resets(1, T, seed=bs, mean_len=20)).cuda()
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0")
+    dp.workspace = lambda shape, op: (ws, ws.numel())
+
+    def call(y):
+        R.rglru_timing_enable(True)
+        try:
+            if how == "plain":
+                g = dp.backward(u, y, dy, dhT=dhT)
+            elif how == "packed":
+                g = dp.backward_packed(u, reset, y, dy, dhT=dhT)
+            else:
+                g = dp.backward_merge(u, br, y, dy, dhT=dhT)
+                g["dbranch"] = g["dbranch"][:, :-1]
+            torch.cuda.synchronize()
+            assert "tile_prep_kernel" in names_of(R)
+        finally:
+            R.rglru_timing_enable(False)
+        return {k: v.cpu() for k, v in g.items() if v is not None}
+
+    if how == "merge" and bs > 352:
+        pytest.skip("LDS does not hold the merge of such blocks")
+    want = call(y)
+    for k, v in want.items():
+        v = v.float()
+        if k == "dconv_w":
+            v = torch.cat((v[:, :c], v[:, c + 1:]), 1)
+        assert torch.isfinite(v).all(), k
+    y[0, -1] = float("inf")
+    got = call(y)
+    for k in want:
+        assert torch.equal(got[k], want[k]), k
