@@ -10,7 +10,7 @@ using namespace fused;
 namespace {
 
 // ------------------------------------------------------------------------ preparation
-// Weights in half precision (exact for bf16 weights from 6.1e-5 up) in matrix-fragment order,
+// Weights in half precision (exact for bf16 weights from 6.1e-5 up, finite ones stop at 65504) in matrix-fragment order,
 // [nb][wave][K-step][gate][lane][8]: as they are (rows of W, for the gates) and transposed (for dx), zero
 // past the block; the status word and the record rings cleared; the last workgroup forms the scale.
 struct PrepArgs {
@@ -46,7 +46,7 @@ __global__ void __launch_bounds__(256) tile_prep_kernel(PrepArgs a) {
     for (int e = 0; e < 8; ++e) v[e] = tr ? src[(size_t)(k0 + e) * a.bs + c] : src[(size_t)c * a.bs + k0 + e];
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      o[e] = pack_rn(__uint_as_float((unsigned)v[2 * e] << 16), __uint_as_float((unsigned)v[2 * e + 1] << 16));
+      o[e] = pack_sat(__uint_as_float((unsigned)v[2 * e] << 16), __uint_as_float((unsigned)v[2 * e + 1] << 16));
   }
   (tr ? a.wd : a.wg)[tr ? i - per : i] = o;
 }

@@ -81,7 +81,7 @@ __global__ void __launch_bounds__(256) cg_prep_kernel(CgPrepArgs a) {
   const int gate = i >= per;
   const size_t o = i - (gate ? per : 0);
   const unsigned short w = (gate ? a.Wx : a.Wa)[o];
-  a.w16[i] = (unsigned short)f16_bits(__uint_as_float((unsigned)w << 16));
+  a.w16[i] = (unsigned short)f16_bits(f16_range(__uint_as_float((unsigned)w << 16)));   // (finite weights stop at 65504)
   if (a.wt) {
     const int k = (int)(o % (2 * a.hs)), j = (int)(o / (2 * a.hs) % a.hs), g = (int)(o / (2 * a.hs) / a.hs);
     a.wt[((size_t)g * 2 * a.hs + k) * 2 * a.hs + gate * a.hs + j] = w;

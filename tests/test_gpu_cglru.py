@@ -133,3 +133,29 @@ def test_cg_at_the_paper_s_block_shape_full_width():
     print("errors:", {k: float("%.3g" % v) for k, v in errs.items()})
     for k in ref:
         assert errs[k] < TOL[act], (k, errs)
+
+
+@pytest.mark.parametrize("hs,nb,T", [(48, 2, 40), (128, 2, 70)])
+def test_weights_past_half_precision(hs, nb, T):
+    """Finite weights stop at 65504 in the products: where they meet inputs of zero, nothing comes of them (an infinity would be a
+    NaN). The oracle's results with weights that end there, at the tolerance of the bf16 kernels in tiles and passes."""
+    rn = runner()
+    D, act, tol = 2 * hs * nb, "bf16", 2.0 ** -6
+    inp = gen.make_cg_inputs(1, T, D, nb, act=act, seed=hs, h0=True, dy=True, bias=True)
+    for k, v in (("W_a", 1e5), ("W_x", -3e38)):
+        inp[k][0, 9, 4] = gen.round_to_act(np.array([v], np.float32), act)[0]
+    inp["u"][:, :, 4], inp["conv_b"][4] = 0.0, 0.0
+    dp = rn.CgDeviceProblem(inp, 1, T, D, nb, act)
+    u, h0, dy = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32"), rn.to_device(inp["dy"], act)
+    y, hT, _ = dp.forward(u, h0=h0)
+    got = dp.backward(u, dy, h0=h0)
+    q = {k: (None if v is None else np.asarray(v, np.float64)) for k, v in inp.items()}
+    w = (np.clip(q["W_a"], -65504, 65504), np.clip(q["W_x"], -65504, 65504), q["b_a"], q["b_x"], q["Lambda"], q["theta"])
+    kw = dict(conv_w=q["conv_w"], conv_b=q["conv_b"], h0=q["h0"])
+    want, ref = oracle.cg_forward(q["u"], *w, **kw), oracle.cg_backward(q["u"], *w, q["dy"], **kw)
+    assert gen.rel_err(rn.to_host(y), want[0]) < tol and gen.rel_err(rn.to_host(hT), want[1]) < tol
+    for k in ref:
+        a, b = rn.to_host(got[k]), ref[k]
+        if k in ("du", "dh0", "dconv_w", "dconv_b"):   # (the channel such a weight leads to on a scale of its own)
+            a, b = a[..., np.arange(D) != 4], b[..., np.arange(D) != 4]
+        assert gen.rel_err(a, b) < tol, k

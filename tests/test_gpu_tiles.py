@@ -240,3 +240,31 @@ def test_backward_of_a_ragged_tile_ignores_what_lies_past_the_end(bs, nb, T, how
     got = call(y)
     for k in want:
         assert torch.equal(got[k], want[k]), k
+
+
+@pytest.mark.parametrize("bs,nb,T", [(64, 4, 40), (128, 2, 40), (160, 2, 140), (256, 1, 300), (352, 8, 40), (512, 1, 40)])
+def test_weights_past_half_precision(bs, nb, T):
+    """Finite weights stop at 65504 in the products (here they meet inputs of zero, where an infinity would be a NaN): the
+    oracle's results with weights that end there."""
+    rn = runner()
+    D, act = bs * nb, "bf16"
+    inp = gen.make_inputs(1, T, D, nb, act=act, seed=bs, h0=True, dy=True, bias=True)
+    for k, v in (("W_a", 1e5), ("W_x", -3e38)):
+        inp[k][0, 9, 4] = gen.round_to_act(np.array([v], np.float32), act)[0]
+    inp["u"][:, :, 4], inp["conv_b"][4] = 0.0, 0.0
+    dp = rn.DeviceProblem(inp, 1, T, D, nb, act)
+    u, h0, dy = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32"), rn.to_device(inp["dy"], act)
+    y, hT, _ = dp.forward(u, h0=h0)
+    got = dp.backward(u, y, dy, h0=h0)
+    q = f64(inp)
+    w = (np.clip(q["W_a"], -65504, 65504), np.clip(q["W_x"], -65504, 65504), q["b_a"], q["b_x"], q["Lambda"], q["conv_w"])
+    want = oracle.forward(q["u"], *w, conv_b=q["conv_b"], h0=q["h0"])
+    ref = oracle.backward(q["u"], *w, q["dy"], conv_b=q["conv_b"], h0=q["h0"])
+    assert gen.rel_err(rn.to_host(y), want[0]) < BF16 and gen.rel_err(rn.to_host(hT), want[1]) < BF16
+    for k in ref:   # (the channel such a weight leads to and the others on scales of their own)
+        a, b = rn.to_host(got[k]), ref[k]
+        if k in ("dW_a", "dW_x"):
+            assert gen.rel_err(a, b) < BF16, k
+            continue
+        for at in (np.arange(D) == 4, np.arange(D) != 4):
+            assert gen.rel_err(a[..., at], b[..., at]) < BF16, k
