@@ -76,15 +76,6 @@ __device__ __forceinline__ void both_halves(float v, float &lo, float &up) {
   lo = __uint_as_float(r[0]);
   up = __uint_as_float(r[1]);
 }
-// A 16-byte store whose data registers are left alone for two cycles. (Seen here: four lanes of sixteen of a store
-// held what the vector instruction right behind it wrote into one of its data registers, a copy the compiler had put there.)
-template <int AUX>
-__device__ __forceinline__ void store16(const u32x4 &v, const __amdgpu_buffer_rsrc_t &rs, unsigned vo, unsigned so) {
-  __builtin_amdgcn_raw_buffer_store_b128(v, rs, vo, so, AUX);
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_nop 1");
-  __builtin_amdgcn_sched_barrier(0);
-}
 // e^-v for a logit v, kept below infinity (1 / (1 + e^-v) times e^-v is then 1 where the gate is closed) but not a NaN
 __device__ __forceinline__ float gate_exp(float v) {
   return __builtin_amdgcn_exp2f(__builtin_elementwise_minimum(-LOG2E * v, 126.f));

@@ -489,12 +489,12 @@ fwd_mfma_kernel(FwdArgs a) {
       const u32x4 v1 = *(const u32x4 *)(otile + (row + 16) * OT + chunk * 8);
       const u32x4 o0 = merge8<MERGE>(v0, bq0), o1 = merge8<MERGE>(v1, bq1);
       if (row < nrows) {
-        __builtin_amdgcn_raw_buffer_store_b128(v0, y_rsrc, yw_voff, soff, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(o0, out_rsrc, yw_voff, soff, 0);
+        store16<0>(v0, y_rsrc, yw_voff, soff);
+        store16<0>(o0, out_rsrc, yw_voff, soff);
       }
       if (row + 16 < nrows) {
-        __builtin_amdgcn_raw_buffer_store_b128(v1, y_rsrc, yw_voff, soff + 16 * row_bytes, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(o1, out_rsrc, yw_voff, soff + 16 * row_bytes, 0);
+        store16<0>(v1, y_rsrc, yw_voff, soff + 16 * row_bytes);
+        store16<0>(o1, out_rsrc, yw_voff, soff + 16 * row_bytes);
       }
     } else {
       store_staged_tile(otile, lane, y_rsrc, yw_voff, (unsigned)(t * TT) * row_bytes, row_bytes, T - t * TT);
@@ -944,7 +944,7 @@ decode_mfma_kernel(DecArgs a) {
       lo4[e] = lo_pk;
     }
     // slot pos mod 3 == slot (pos-3) mod 3
-    __builtin_amdgcn_raw_buffer_store_b128(ru[i][0], ring_rsrc, ring_vo[i], PERSEQ ? 0u : (unsigned)s3 * row2, 0);
+    store16<0>(ru[i][0], ring_rsrc, ring_vo[i], PERSEQ ? 0u : (unsigned)s3 * row2);
     *(u32x4 *)(xs + (lr + 16 * i) * XS + 8 * lc) = hi4;
     *(u32x4 *)(xs + XT_ELEMS + (lr + 16 * i) * XS + 8 * lc) = lo4;
   }

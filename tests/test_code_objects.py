@@ -1,0 +1,67 @@
+"""The built library's device code, disassembled: distances between instructions that the compiler does not keep by itself."""
+import os
+import re
+import shutil
+import struct
+import subprocess
+
+import pytest
+
+LLVM = "/opt/rocm/llvm/bin"
+LIB = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2402_19427_amd", "librglru.so")
+OBJDUMP = shutil.which("llvm-objdump", path=LLVM)
+
+
+def code_objects(blob):
+    """gfx950 code objects of the offload bundles in a host library (magic, count, then offset, size and name of each entry)."""
+    magic, at = b"__CLANG_OFFLOAD_BUNDLE__", 0
+    while (at := blob.find(magic, at)) >= 0:
+        pos = at + len(magic)
+        (n,) = struct.unpack_from("<Q", blob, pos)
+        pos += 8
+        for _ in range(n if n < 16 else 0):
+            off, size, length = struct.unpack_from("<QQQ", blob, pos)
+            name = blob[pos + 24:pos + 24 + length]
+            pos += 24 + length
+            if b"gfx950" in name and size:
+                yield blob[at + off:at + off + size]
+        at += len(magic)
+
+
+def registers(text):
+    out = set()
+    for a, b in re.findall(r"\bv\[(\d+):(\d+)\]", text):
+        out |= set(range(int(a), int(b) + 1))
+    return out | {int(a) for a in re.findall(r"\bv(\d+)\b", text)}
+
+
+@pytest.mark.skipif(OBJDUMP is None, reason="no disassembler")
+def test_data_of_wide_stores_with_a_scalar_offset_is_left_alone(tmp_path):
+    """Behind a buffer store of 16 bytes whose offset is a scalar register, no vector instruction writes into its data registers
+    for two cycles (an s_nop counts for its operand and one more)."""
+    if not os.path.exists(LIB):
+        pytest.skip("the library is not built")
+    stores, bad = 0, []
+    for i, obj in enumerate(code_objects(open(LIB, "rb").read())):
+        path = tmp_path / ("%d.co" % i)
+        path.write_bytes(obj)
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], stdout=subprocess.PIPE, text=True, check=True).stdout
+        lines = [l.split("//")[0].strip() for l in text.split("\n") if l.startswith("\t")]
+        for k, line in enumerate(lines):
+            m = re.match(r"buffer_store_dwordx[34] (v\[\d+:\d+\]), v\d+, s\[\d+:\d+\], s\d+\b", line)
+            if not m:
+                continue
+            stores += 1
+            data, gap = registers(m.group(1)), 0
+            for nxt in lines[k + 1:k + 3]:
+                if gap >= 2:
+                    break
+                if nxt.startswith("s_nop"):
+                    gap += int(nxt.split()[1], 0)
+                elif re.match(r"v_(?!cmp)", nxt):
+                    ops = nxt.split(None, 1)[1]
+                    if registers(ops if "swap" in nxt else ops.split(",")[0]) & data:
+                        bad.append((line, nxt))
+                gap += 1
+    assert stores > 0
+    assert not bad, bad
