@@ -35,18 +35,25 @@ def registers(text):
     return out | {int(a) for a in re.findall(r"\bv(\d+)\b", text)}
 
 
-@pytest.mark.skipif(OBJDUMP is None, reason="no disassembler")
-def test_data_of_wide_stores_with_a_scalar_offset_is_left_alone(tmp_path):
-    """Behind a buffer store of 16 bytes whose offset is a scalar register, no vector instruction writes into its data registers
-    for two cycles (an s_nop counts for its operand and one more)."""
-    if not os.path.exists(LIB):
-        pytest.skip("the library is not built")
-    stores, bad = 0, []
+@pytest.fixture(scope="module")
+def listings(tmp_path_factory):
+    """Instructions of every code object, one a line."""
+    if OBJDUMP is None or not os.path.exists(LIB):
+        pytest.skip("no disassembler, or the library is not built")
+    out, where = [], tmp_path_factory.mktemp("code")
     for i, obj in enumerate(code_objects(open(LIB, "rb").read())):
-        path = tmp_path / ("%d.co" % i)
+        path = where / ("%d.co" % i)
         path.write_bytes(obj)
         text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], stdout=subprocess.PIPE, text=True, check=True).stdout
-        lines = [l.split("//")[0].strip() for l in text.split("\n") if l.startswith("\t")]
+        out.append([l.split("//")[0].strip() for l in text.split("\n") if l.startswith("\t")])
+    return out
+
+
+def test_data_of_wide_stores_with_a_scalar_offset_is_left_alone(listings):
+    """Behind a buffer store of 16 bytes whose offset is a scalar register, no vector instruction writes into its data registers
+    for two cycles (an s_nop counts for its operand and one more)."""
+    stores, bad = 0, []
+    for lines in listings:
         for k, line in enumerate(lines):
             m = re.match(r"buffer_store_dwordx[34] (v\[\d+:\d+\]), v\d+, s\[\d+:\d+\], s\d+\b", line)
             if not m:
@@ -65,3 +72,19 @@ def test_data_of_wide_stores_with_a_scalar_offset_is_left_alone(tmp_path):
                 gap += 1
     assert stores > 0
     assert not bad, bad
+
+
+def test_loads_written_out_restore_m0(listings):
+    """The direct-to-LDS loads written out by hand (the streaming ones are) put back what m0 held: the compiler does not know that
+    they write it."""
+    loads, bad = 0, []
+    for lines in listings:
+        for k, line in enumerate(lines):
+            if not re.match(r"buffer_load_dwordx4 .* offen nt lds$", line):
+                continue
+            loads += 1
+            saved = re.match(r"s_mov_b32 (s\d+), m0$", lines[k - 3])
+            if not saved or lines[k + 1] != "s_mov_b32 m0, " + saved.group(1):
+                bad.append(lines[k - 3:k + 2])
+    assert loads > 0
+    assert not bad, bad[:4]
