@@ -45,10 +45,10 @@ def algorithmic_costs(B, T, D, nb, B_dec):
         # u_t, 3 ring slots read + 1 written, h read + written, y_t, weights
         "decode_mfma_kernel": dict(bytes=(2 + 6 + 2 + 4 + 4 + 2) * B_dec * D + w_bytes + vec,
                                    flops=4 * bs * B_dec * D),
-        "apply_kernel": dict(bytes=4 * N + w_bytes + vec + 10 * B * D, flops=gemm),   # the forward in tiles
-        # the backward in tiles: u, y, dy in, du out; the gates and dx (adjoint_kernel), dW out (wgrad_pass_kernel)
-        "adjoint_kernel": dict(bytes=8 * N + w_bytes + vec + 8 * B * D, flops=2 * gemm),
-        "wgrad_pass_kernel": dict(bytes=2 * nb * bs * bs * 4, flops=gemm),
+        "fwd_tile_kernel": dict(bytes=4 * N + w_bytes + vec + 10 * B * D, flops=gemm),   # the forward in tiles
+        # the backward in tiles: u, y, dy in, du out; the gates and dx (bwd_tile_kernel), dW out (tile_wgrad_kernel)
+        "bwd_tile_kernel": dict(bytes=8 * N + w_bytes + vec + 8 * B * D, flops=2 * gemm),
+        "tile_wgrad_kernel": dict(bytes=2 * nb * bs * bs * 4, flops=gemm),
         # the backward in separate kernels (tensors off the 16-byte grid, or a small workspace):
         # u, y, dy in (gate recompute + reverse scan + pointwise adjoints)
         "bwd_gates_kernel": dict(bytes=6 * N + w_bytes + vec + 8 * B * D, flops=gemm),

@@ -337,7 +337,7 @@ hipError_t launch_backward_tile(const Problem &call, hipStream_t s) {
   a.rmask = p.reset ? masks : nullptr;
   a.nmask = (p.T + 31) / 32;
   {
-    KernelTimer kt("adjoint_kernel", s);
+    KernelTimer kt("bwd_tile_kernel", s);
     void *args[] = {&a};
     if ((e = hipLaunchKernel(in.kernel, dim3(grid8(a.total)), dim3(in.waves * 64), args, in.lds, s)) != hipSuccess) return e;
   }
@@ -347,7 +347,7 @@ hipError_t launch_backward_tile(const Problem &call, hipStream_t s) {
       if ((e = big_lds(tile_wgrad_kernel, WT_LDS)) != hipSuccess) return e;
       configured.store(true);
     }
-    KernelTimer kt("wgrad_pass_kernel", s);
+    KernelTimer kt("tile_wgrad_kernel", s);
     WgradArgs w;
     w.pqT = a.pqT; w.xT = a.xT; w.part = (float *)(ws + q.off_partW);
     w.nst = q.nst; w.per = q.per;

@@ -113,7 +113,7 @@ hipError_t launch_forward_tile(const Problem &p, size_t asked, hipStream_t s) {
   a.wg = wg;
   a.rmask = p.reset ? masks : nullptr;
   a.nmask = (p.T + 31) / 32;
-  KernelTimer kt("apply_kernel", s);
+  KernelTimer kt("fwd_tile_kernel", s);
   void *args[] = {&a};
   return hipLaunchKernel(in.kernel, dim3(grid8(a.total)), dim3(in.waves * 64), args, in.lds, s);
 }

@@ -516,9 +516,9 @@ def _long_case(rn, cg, T, D, nb, seed):
     return t, act(normal(1, T, D)), act(normal(1, T, D))
 
 
-@pytest.mark.parametrize("cg,T,D,nb", [(False, 210240, 2560, 16), (True, 131200, 4096, 16)])
+@pytest.mark.parametrize("cg,T,D,nb", [(False, 210240, 2560, 16), (False, 210240, 2560, 40), (True, 131200, 4096, 16)])
 def test_passes_on_sequences_past_32_bit_offsets(cg, T, D, nb):
-    """fp32 intermediates of more than 2^31 bytes a sequence: the passes run, and what they give at the start, around the
+    """fp32 intermediates of more than 2^31 bytes a sequence: the passes (blocks of 160 channels: the tiles) run, and what they give at the start, around the
     2^31 bytes and at the end is what a short call gives on the steps around it (a decay of 0.6 on average, so that
     512 steps more on either side leave nothing of what is missing)."""
     import paper_2402_19427_amd as R
@@ -550,7 +550,9 @@ def test_passes_on_sequences_past_32_bit_offsets(cg, T, D, nb):
         return y, du, names
 
     y, du, names = call(u, dy)
-    assert ("cg_wgrad_kernel" if cg else "wgrad_pass_kernel") in names and (not cg or "cg_apply_kernel" in names), names
+    ran = {"cg_wgrad_kernel", "cg_apply_kernel"} if cg else {"fwd_tile_kernel", "bwd_tile_kernel", "tile_wgrad_kernel"} if D // nb >= 112 \
+        else {"apply_kernel", "adjoint_kernel", "wgrad_pass_kernel"}
+    assert ran <= set(names), names
     at = (1 << 31) // (4 * D)
     for lo, hi in ((0, 300), (at - 150, at + 150), (T - 300, T)):
         a, b = max(lo - 512, 0), min(hi + 512, T)
@@ -584,10 +586,12 @@ def test_layer_forward_past_half_precision(T, bs, nb):
         assert gen.rel_err(got, want) < BF16
 
 
-@pytest.mark.parametrize("T,bs,nb,off", [(300, 160, 8, 1), (300, 160, 8, 4), (300, 352, 8, 1), (50, 352, 8, 2)])
+@pytest.mark.parametrize("T,bs,nb,off", [(300, 160, 8, 1), (300, 160, 8, 4), (300, 352, 8, 1), (50, 352, 8, 2),   # the tiles
+                                         (300, 64, 8, 1), (50, 96, 8, 2), (130, 64, 4, 4),                       # the passes
+                                         (300, 384, 4, 1), (50, 512, 4, 2)])   # the passes with the merge; 512 channels: in the forward, too
 @pytest.mark.parametrize("merge", [False, True])
 def test_layer_passes_at_any_alignment(T, bs, nb, off, merge):
-    """Tensors of the backward off the 16-byte grid, and states of the forward off the 8-byte grid: the passes, the same
+    """Tensors of the backward off the 16-byte grid, and states of the forward off the 8-byte grid: the tiles or the passes, the same
     results. (The backward's u and dy without the merge stay on the grid: nothing but the passes' own size is asked for.)"""
     import paper_2402_19427_amd as R
     import torch
@@ -600,7 +604,6 @@ def test_layer_passes_at_any_alignment(T, bs, nb, off, merge):
     ring = rn.to_device(gen.ring_from_chrono(inp["state"], 4), act)
     f32 = lambda *s: torch.empty(*s, dtype=torch.float32, device="cuda:0")
     sh = dp.shape()
-    wide = bs > 256
 
     def call(off):
         at = lambda t: _at(t, off)
@@ -634,7 +637,9 @@ def test_layer_passes_at_any_alignment(T, bs, nb, off, merge):
 
     want, _ = call(0)
     got, names = call(off)
-    assert "adjoint_kernel" in names and "wgrad_pass_kernel" in names and (not wide or "apply_kernel" in names), names
+    tiles = bs >= 112 and not (merge and bs > 352)
+    assert ({"bwd_tile_kernel", "tile_wgrad_kernel"} if tiles else {"adjoint_kernel", "wgrad_pass_kernel"}) <= set(names), names
+    assert ("fwd_tile_kernel" if 112 <= bs <= 480 else "apply_kernel") in names, names
     for k in want:
         np.testing.assert_array_equal(rn.to_host(got[k]), rn.to_host(want[k]), err_msg=k)
 
