@@ -114,8 +114,6 @@ __global__ void __launch_bounds__(256) reset_mask_kernel(const unsigned char *re
     out[(size_t)b * ntile + tile] = make_uint4((unsigned)(r >> sh), (unsigned)(l1 >> sh), (unsigned)(l2 >> sh), (unsigned)(l3 >> sh));
 }
 
-constexpr int FWD_MAX_SLICES = 16;
-
 // Contiguous time slices ("windows") of a sequence, first helper: the Conv1D ring each window
 // starts from - the caller's ring for a sequence's first window (zeros without one), the three
 // inputs in front of it for every other window, in the slots their positions select.

@@ -57,18 +57,50 @@ bool shape_ok(int B, int T, int D, int bs) {
 // bound held there is 4e-2, which the passes' y meets in the same draws (at most 3.96e-2).
 // Blocks it takes, 128 channels: everywhere (B 1 T 16 10 : 15, B 8 T 2048 82 : 146). 144 and up:
 // - not up to four tiles (160 channels, T 64: 15.7 : 14.3 and 18.4 : 14.6 with the merge; 256, T 200 with the merge
-//   23 : 20), where the workgroups' own start is most of the time and they have no second tile to hide it behind;
-// - 176 and 192 without the merge: up to 64 units. Six waves on four SIMDs leave two of these half idle; a chip full of
-//   such workgroups loses to the fused kernel's eight (176, B 16 T 512: 77 : 67; B 4 T 512: 30 : 30; 160: 62 : 67);
-// - 208 to 256: up to 32 units, where the fused kernel cuts a sequence into more than 8 slices and re-reads weights
-//   that it otherwise keeps (256, T 32768 of 10 blocks: 202 : 280, T 777: 20 : 26; but 64 units, B 4 T 1024: 53 : 49);
-//   with the merge up to 24 (32 units, B 2 T 4096: 111 : 103; 20 units: 88 : 90).
+//   23 : 20), where the workgroups' own start is most of the time and they have no second tile to hide it behind.
+// What else decides is how often a workgroup of either kernel goes round (a round is a tile of each of its slices) and what the
+// preparation costs: the tiles' converts both gates' weights of all blocks, the fused kernel's one gate's, 1 - 5 us more by the
+// number of blocks. `half`: the tiles go round at most half as often.
+// - 144 and 160: everywhere else (160, 8 - 512 units, T 129 - 2048: 0.63 - 1.02 of the fused kernel's time); with the merge
+//   and more than 24 blocks where `half` (32 blocks, 64 units: T 257 - 300 30 : 28, T 400 32 : 35).
+// - 176 and 192, six waves on four SIMDs, two of which stay half idle: a chip full of such workgroups loses to the fused
+//   kernel's eight. Without the merge up to 64 units, at 176 up to 48 (64 units: T 1024 48 : 46, T 129 18 : 20); with it up to 64
+//   and 48 and beyond where `half` (176, 128 units: T 300 47 : 43, T 2048 198 : 212) or, at 192, from 129 units on (240 : 178 at
+//   B 16 T 1024). Many blocks lose everywhere (24 blocks, 96 units: T 512 69 : 57; 32 blocks, 32 units, T 2048 58 : 48) but at 192 in
+//   a single short sequence (32 blocks, T 257 22 : 25).
+// - 208 to 256: up to 32 units, where the fused kernel cuts a sequence into more than 8 slices and re-reads weights that it otherwise
+//   keeps (256, T 32768 of 10 blocks: 202 : 280; 16 blocks, B 1 T 1024 23 : 27, B 2 T 512 22 : 26; 64 units, B 4 T 1024: 53 : 49); with
+//   the merge up to 24 (32 units, B 2 T 4096: 111 : 103). Not, with more than 12 blocks (16 at 256 channels without the merge), where the fused
+//   kernel goes round no oftener (240, 16 blocks, T 300: 25 : 22 with the merge, 20 : 19 without), nor with more than 24 (240, 32 blocks,
+//   T 2048 69 : 52). At 240 and 256 the gain is smaller: with the merge, many blocks or a long sequence take `half` (256, 24 blocks, T 2048
+//   71 : 63; B 2 of 10 blocks, T 4096 93 : 89, T 6000 123 : 124), and 29 - 32 units lose in between (256, 16 blocks: B 2 T 1400 43 : 45,
+//   T 2048 54 : 52, T 4096 90 : 85, T 8192 159 : 156, T 12000 226 : 228).
 bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
   if (!forward_mfma_block(bs) || bs <= 128) return true;
   const bool merge = var == V_MERGE || var == V_MERGE_TANH;
+  const int steps = 32 * in.mt;
   const long long units = (long long)B * nb;
-  if (T <= 4 * 32 * in.mt) return false;
-  return bs <= 160 || (bs <= 192 ? merge || units <= 64 : units <= (merge ? 24 : 32));
+  if (T <= 4 * steps) return false;
+  // (for 256 compute units on either side: the same rule where no card is visible)
+  const auto rounds = [&](int step, int workgroups, int most) {
+    const int n = (T + step - 1) / step, G = pick_slices(B * nb, n, workgroups, most);
+    return (n + G - 1) / G;
+  };
+  const int own = rounds(steps, in.per_cu * 256, FWD_TILE_SLICES), fused = rounds(32, 256, FWD_MAX_SLICES);
+  const bool half = 2 * own <= fused;
+  if (bs <= 160) return !merge || nb <= 24 || half;
+  if (bs <= 192) {
+    if (nb > 24) return bs == 192 && units <= 32 && T <= 320;
+    if (units <= 48) return true;
+    if (nb > 16) return false;
+    if (units <= 64) return bs == 192 || T <= 256;
+    return merge && (half || (bs == 192 && units > 128));
+  }
+  if (units > (merge ? 24 : 32) || nb > 24) return false;
+  if (nb > (bs == 256 && !merge ? 16 : 12) && own >= fused) return false;
+  if (bs < 240) return true;
+  if (merge) return half || units <= 16 || (nb <= 16 && T < 2048);
+  return units <= 28 || units * T < 65536 || units * T >= 300000;
 }
 size_t bytes(int B, int T, int nb, int bs, int var, size_t room) {
   const Instance in = find_instance(bs, var);

@@ -276,6 +276,7 @@ int pick_slices(int units, int ntile, int ncu, int cap);  // time slices per (se
 int ring_depth(int G);                                    // slots of a unit's record ring: 8 G rounded up to a power of two
 // room for the record rings of `units` (16 G slots each: whatever power of two ring_depth gives)
 inline size_t ring_bytes(int units, int G) { return (size_t)units * 16 * G * BS * sizeof(u64); }
+constexpr int FWD_MAX_SLICES = 16;                        // ... of the fused forward
 void set_slice_cap(int cap);                              // process-wide upper bound on that (0 = none)
 // clears zero_bytes (% 16 == 0) at `zero` with a fill kernel
 //   keep_status: the region starts with a status word, which stays if it reports an expired wait

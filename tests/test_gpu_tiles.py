@@ -268,3 +268,48 @@ def test_weights_past_half_precision(bs, nb, T):
             continue
         for at in (np.arange(D) == 4, np.arange(D) != 4):
             assert gen.rel_err(a[..., at], b[..., at]) < BF16, k
+
+
+@pytest.mark.parametrize("B,T,bs,nb,merge,tiles", [
+    (2, 1400, 256, 16, False, True), (2, 2048, 256, 16, False, False), (3, 2048, 256, 10, False, True),   # 29 - 32 units: not in between
+    (1, 512, 256, 16, False, True), (1, 512, 256, 16, True, False), (1, 640, 256, 16, True, True),        # as many rounds, half as many
+    (1, 300, 240, 16, False, False), (1, 300, 240, 10, False, True), (2, 4096, 256, 10, True, False), (2, 3000, 256, 10, True, True),
+    (1, 1024, 240, 32, False, False), (4, 1024, 176, 16, False, False), (3, 1024, 176, 16, False, True), (4, 200, 176, 16, False, True),
+    (8, 300, 176, 16, True, False), (8, 2048, 176, 16, True, True), (1, 1024, 192, 32, False, False), (1, 300, 192, 32, False, True),
+    (2, 300, 160, 32, True, False), (2, 400, 160, 32, True, True), (2, 300, 160, 32, False, True)])
+def test_forward_takes_the_faster_kernel(B, T, bs, nb, merge, tiles):
+    """Either side of the rule between the tiles and the fused kernel; y is the same but for the rounding of its last bits."""
+    import torch
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D, act = bs * nb, "bf16"
+    g = torch.Generator(device="cuda").manual_seed(T + bs)
+    rand = lambda *s, k=1.0: torch.randn(*s, generator=g, device="cuda") * k
+    bf = lambda t: t.to(torch.bfloat16)
+    weights = (bf(rand(nb, bs, bs, k=bs ** -0.5)), bf(rand(nb, bs, bs, k=bs ** -0.5)), rand(D, k=0.1), rand(D, k=0.1),
+               torch.full((D,), 4.0, device="cuda"), rand(4, D, k=0.5), rand(D, k=0.1))
+    par = R.make_params(*weights)
+    u, br, y, out, hT = bf(rand(B, T, D)), bf(rand(B, T, D)), bf(rand(B, T, D)), bf(rand(B, T, D)), rand(B, D)
+    sh = R.make_shape(B, T, D, nb, R.BF16)
+
+    def call(cap):
+        R.rglru_set_max_time_slices(cap)
+        n = R.rglru_workspace_bytes(sh, R.OP_FORWARD_MERGE if merge else R.OP_FORWARD)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        R.rglru_timing_enable(True)
+        try:
+            if merge:
+                R.rglru_forward_merge(sh, par, u, br, None, None, 0, 0, out, y, hT, None, ws, n, None)
+            else:
+                R.rglru_forward(sh, par, u, None, None, 0, y, hT, None, ws, n, None)
+            torch.cuda.synchronize()
+            return names_of(R), y.float().clone(), hT.clone()
+        finally:
+            R.rglru_timing_enable(False)
+            R.rglru_set_max_time_slices(0)
+
+    names, a, h = call(0)
+    # (a merge that neither kernel has as its epilogue there runs behind the plain forward)
+    assert ("fwd_tile_kernel" in names and "merge_fwd_kernel" not in names) == tiles, names
+    _, b, k = call(1)
+    assert ((a - b).norm() / b.norm()).item() < 2.0 ** -9 and ((h - k).norm() / k.norm()).item() < 2.0 ** -9
