@@ -1,4 +1,6 @@
-"""The built library's device code, disassembled: distances between instructions that the compiler does not keep by itself."""
+"""The built library's device code, disassembled, for a distance between instructions that the compiler does not keep by itself; and what
+inline assembly has to tell it."""
+import glob
 import os
 import re
 import shutil
@@ -8,7 +10,8 @@ import subprocess
 import pytest
 
 LLVM = "/opt/rocm/llvm/bin"
-LIB = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2402_19427_amd", "librglru.so")
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2402_19427_amd", "librglru.so")
 OBJDUMP = shutil.which("llvm-objdump", path=LLVM)
 
 
@@ -37,7 +40,7 @@ def registers(text):
 
 @pytest.fixture(scope="module")
 def listings(tmp_path_factory):
-    """(name, instructions) of every function."""
+    """The instructions of every code object, one a line."""
     if OBJDUMP is None or not os.path.exists(LIB):
         pytest.skip("no disassembler, or the library is not built")
     out, where = [], tmp_path_factory.mktemp("code")
@@ -45,9 +48,7 @@ def listings(tmp_path_factory):
         path = where / ("%d.co" % i)
         path.write_bytes(obj)
         text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], stdout=subprocess.PIPE, text=True, check=True).stdout
-        for fn in re.split(r"\n(?=[0-9a-f]{16} <)", text)[1:]:
-            name, _, body = fn.partition("\n")
-            out.append((name, [l.split("//")[0].strip() for l in body.split("\n") if l.startswith("\t")]))
+        out.append([l.split("//")[0].strip() for l in text.split("\n") if l.startswith("\t")])
     return out
 
 
@@ -55,7 +56,7 @@ def test_data_of_wide_stores_with_a_scalar_offset_is_left_alone(listings):
     """Behind a buffer store of 16 bytes whose offset is a scalar register, no vector instruction writes into its data registers
     for two cycles (an s_nop counts for its operand and one more)."""
     stores, bad = 0, []
-    for _, lines in listings:
+    for lines in listings:
         for k, line in enumerate(lines):
             m = re.match(r"buffer_store_dwordx[34] (v\[\d+:\d+\]), v\d+, s\[\d+:\d+\], s\d+\b", line)
             if not m:
@@ -76,19 +77,12 @@ def test_data_of_wide_stores_with_a_scalar_offset_is_left_alone(listings):
     assert not bad, bad
 
 
-def test_loads_written_out_restore_m0(listings):
-    """The direct-to-LDS loads written out by hand (those of the kernels in tiles) put back what m0 held: the compiler does not know
-    that they write it."""
-    loads, bad = 0, []
-    for name, lines in listings:
-        if not re.search("(bwd|fwd)_tile_kernel|tile_wgrad_kernel", name):
-            continue
-        for k, line in enumerate(lines):
-            if not re.match(r"buffer_load_dwordx4 .*\blds$", line):
-                continue
-            loads += 1
-            saved = re.match(r"s_mov_b32 (s\d+), m0$", lines[k - 3])
-            if not saved or lines[k + 1] != "s_mov_b32 m0, " + saved.group(1):
-                bad.append(lines[k - 3:k + 2])
-    assert loads > 0
-    assert not bad, bad[:4]
+def test_inline_assembly_names_m0_where_it_writes_it():
+    """The compiler sets m0 in front of loads of its own: inline assembly that writes it has to say so, or it may be moved between."""
+    found = 0
+    for path in sorted(glob.glob(os.path.join(ROOT, "paper_2402_19427_amd", "csrc", "*.h*"))):
+        for asm in re.findall(r"\basm(?: volatile)?\((.*?)\);", open(path).read(), re.S):
+            if re.search(r"\b(s_mov_b32|s_add_u32|s_movk_i32) m0\b", asm):
+                found += 1
+                assert asm.rpartition(":")[2].count('"m0"') == 1, (path, asm)
+    assert found > 0
