@@ -62,7 +62,8 @@ bool shape_ok(int B, int T, int D, int bs) {
 // preparation costs: the tiles' converts both gates' weights of all blocks, the fused kernel's one gate's, 1 - 5 us more by the
 // number of blocks. `half`: the tiles go round at most half as often.
 // - 144 and 160: everywhere else (160, 8 - 512 units, T 129 - 2048: 0.63 - 1.02 of the fused kernel's time); with the merge
-//   and more than 24 blocks where `half` (32 blocks, 64 units: T 257 - 300 30 : 28, T 400 32 : 35).
+//   and more than 24 blocks where `half` (32 blocks, 64 units: T 257 - 300 30 : 28, T 400 32 : 35), or many units and more than 8 tiles
+//   (32 blocks, 128 units: T 129 30 : 29, T 700 69 : 73).
 // - 176 and 192, six waves on four SIMDs, two of which stay half idle: a chip full of such workgroups loses to the fused
 //   kernel's eight. Without the merge up to 64 units, at 176 up to 48 (64 units: T 1024 48 : 46, T 129 18 : 20); with it up to 64
 //   and 48 and beyond where `half` (176, 128 units: T 300 47 : 43, T 2048 198 : 212) or, at 192, from 129 units on (240 : 178 at
@@ -73,8 +74,8 @@ bool shape_ok(int B, int T, int D, int bs) {
 //   the merge up to 24 (32 units, B 2 T 4096: 111 : 103). Not, with more than 12 blocks (16 at 256 channels without the merge), where the fused
 //   kernel goes round no oftener (240, 16 blocks, T 300: 25 : 22 with the merge, 20 : 19 without), nor with more than 24 (240, 32 blocks,
 //   T 2048 69 : 52). At 240 and 256 the gain is smaller: with the merge, many blocks or a long sequence take `half` (256, 24 blocks, T 2048
-//   71 : 63; B 2 of 10 blocks, T 4096 93 : 89, T 6000 123 : 124), and 29 - 32 units lose in between (256, 16 blocks: B 2 T 1400 43 : 45,
-//   T 2048 54 : 52, T 4096 90 : 85, T 8192 159 : 156, T 12000 226 : 228).
+//   71 : 63; B 2 of 10 blocks, T 4096 93 : 89, T 6000 123 : 124), and 29 - 32 units of more than 8 blocks lose in between (256, 16 blocks: B 2 T 1400
+//   43 : 45, T 2048 54 : 52, T 4096 90 : 85, T 8192 159 : 156, T 12000 226 : 228; 8 blocks, B 4 T 2048 50 : 52).
 bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
   if (!forward_mfma_block(bs) || bs <= 128) return true;
   const bool merge = var == V_MERGE || var == V_MERGE_TANH;
@@ -88,7 +89,7 @@ bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
   };
   const int own = rounds(steps, in.per_cu * 256, FWD_TILE_SLICES), fused = rounds(32, 256, FWD_MAX_SLICES);
   const bool half = 2 * own <= fused;
-  if (bs <= 160) return !merge || nb <= 24 || half;
+  if (bs <= 160) return !merge || nb <= 24 || half || (units > 64 && T > 256);
   if (bs <= 192) {
     if (nb > 24) return bs == 192 && units <= 32 && T <= 320;
     if (units <= 48) return true;
@@ -100,7 +101,7 @@ bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
   if (nb > (bs == 256 && !merge ? 16 : 12) && own >= fused) return false;
   if (bs < 240) return true;
   if (merge) return half || units <= 16 || (nb <= 16 && T < 2048);
-  return units <= 28 || units * T < 65536 || units * T >= 300000;
+  return units <= 28 || nb <= 8 || units * T < 65536 || units * T >= 300000;
 }
 size_t bytes(int B, int T, int nb, int bs, int var, size_t room) {
   const Instance in = find_instance(bs, var);
