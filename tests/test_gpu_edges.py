@@ -2,8 +2,8 @@
 gate saturated closed, where 1 - a_t^2 cancels in fp32 and 1/sqrt(1 - a_t^2) blows up in the
 backward), a_t -> 0 (Lambda far below the initialisation range), saturated input gates, large
 inputs, and upstream gradients at the scale a mean-reduced loss gives. Every kernel family is
-covered: generic fp32, the fused kernels (256-channel blocks), the padded tile (160-channel
-blocks) and the passes of the wide blocks (512 channels). All against the float64 oracle on
+covered: generic fp32, the fused forward (256-channel blocks; 160 in the padded tile), the kernels in tiles
+(a long sequence, every backward) and the forward in passes (512 channels). All against the float64 oracle on
 the same seeded inputs; the tolerances are the ones of the ordinary parity tests.
 """
 import numpy as np

@@ -57,9 +57,8 @@ def test_c2_long_sequence_forward_full_size():
 
 
 def test_long_prompt_with_sixteen_blocks_forward_in_interleaved_slices():
-    """One sequence of 16384 steps at width 4096 with 16 gate blocks: more units than the windows of
-    a single prompt take, so all 256 compute units run it as 16 interleaved time slices per unit,
-    32 rounds of them. Two of the blocks against the oracle, every output finite."""
+    """One sequence of 16384 steps at width 4096 with 16 gate blocks: all 256 compute units run it as
+    16 interleaved time slices per unit, 16 rounds of them. Two of the blocks against the oracle, every output finite."""
     import paper_2402_19427_amd.runner as rn
     B, T, D, nb, act = 1, 16384, 4096, 16, "bf16"
     inp = gen.make_inputs(B, T, D, nb, act=act, seed=41, h0=True)
@@ -267,8 +266,8 @@ def test_the_paper_s_sixteen_blocks_at_width_2560_full_size():
 
 @pytest.mark.parametrize("D", [5632, 8192])
 def test_sixteen_blocks_at_the_larger_widths_forward_full_size(D):
-    # 16 gate blocks at widths 5632 and 8192 (352 and 512 channels per block): the forward as
-    # separate passes on the matrix cores, C1's batch and length, two sampled (sequence, block) pairs
+    # 16 gate blocks at widths 5632 and 8192 (352 and 512 channels per block): the forward in
+    # tiles or as separate passes, C1's batch and length, two sampled (sequence, block) pairs
     import dataclasses
     import paper_2402_19427_amd as R
     import paper_2402_19427_amd.runner as rn
@@ -292,7 +291,7 @@ def test_sixteen_blocks_at_the_larger_widths_forward_full_size(D):
 
 
 def test_sixteen_blocks_at_width_5632_backward_full_size():
-    # 352 channels per block: the backward as passes on the matrix cores at C1's batch and length;
+    # 352 channels per block: the backward in tiles at C1's batch and length;
     # one sampled block, every sequence through the oracle for its parameter gradients
     import dataclasses
     import paper_2402_19427_amd as R

@@ -44,11 +44,11 @@ SHAPES = [
     (1, 1, 16, 1, "f32"),        # single step, single dense block
     (2, 130, 512, 2, "bf16"),    # bs = 256: the tuned block size, ragged T
     (2, 70, 320, 2, "bf16"),     # bs = 160: the paper's 16 blocks at width 2560 (MFMA path, padded tile)
-    (3, 300, 2560, 16, "bf16"),  # the same at full width: 48 units x 5 slices, ragged T
-    (1, 1100, 384, 2, "bf16"),   # bs = 192, 16 slices
+    (3, 300, 2560, 16, "bf16"),  # the same at full width, in tiles: 48 units in slices, ragged T
+    (1, 1100, 384, 2, "bf16"),   # bs = 192, tiles in slices
     (40, 40, 288, 2, "bf16"),    # bs = 144 (a multiple of 16 only), one workgroup per unit
-    (2, 100, 2816, 8, "bf16"),   # bs = 352 (16 blocks at width 5632): separate passes, 2 K chunks
-    (1, 700, 1024, 2, "bf16"),   # bs = 512 (16 blocks at width 8192), scan in time slices
+    (2, 100, 2816, 8, "bf16"),   # bs = 352 (16 blocks at width 5632): tiles
+    (1, 700, 1024, 2, "bf16"),   # bs = 512 (16 blocks at width 8192): separate passes
     (3, 70, 256, 4, "bf16"),     # bs = 64: separate passes, one partial K chunk
     (1, 130, 1536, 2, "bf16"),   # bs = 768: three K chunks
     (2, 37, 96, 2, "bf16"),      # bs = 48, width not a multiple of 256: generic kernels
@@ -57,10 +57,10 @@ SHAPES = [
     (1, 9, 24, 24, "bf16"),      # nb = D: per-channel gates
     (2, 300, 600, 2, "bf16"),    # bs = 300 > workgroup size
     (1, 1, 256, 1, "bf16"),      # MFMA path, one step
-    (1, 1500, 256, 1, "bf16"),   # MFMA path, one unit in 16 time slices
+    (1, 1500, 256, 1, "bf16"),   # tiles, one unit in as many time slices
     (33, 70, 1024, 4, "bf16"),   # MFMA path, 132 units: one workgroup per unit, no slicing
     (8, 600, 2048, 8, "bf16"),   # MFMA path, 64 units x 4 slices, record ring wraps (19 tiles > 16)
-    (1, 12400, 512, 2, "bf16"),  # MFMA path, few units and a long sequence: contiguous windows in two passes, ragged end
+    (1, 12400, 512, 2, "bf16"),  # tiles, few units and a long sequence, ragged end
     (2, 12320, 320, 2, "bf16"),  # the same with narrower blocks in the padded tile, two sequences
 ]
 
@@ -117,8 +117,8 @@ def test_forward_in_pieces_equals_one_shot_and_states_may_alias(act, D, nb):
     np.testing.assert_array_equal(gen.chrono_from_ring(rn.to_host(state), T), st_ref)
 
 
-def test_a_long_prompt_in_windows_equals_the_capped_call_and_carries_states_in_place():
-    """A single long sequence runs as contiguous windows in two passes. The same call with the
+def test_a_long_prompt_in_slices_equals_the_capped_call_and_carries_states_in_place():
+    """A single long sequence runs in as many time slices as the chip holds. The same call with the
     time slices capped at one (a single workgroup per unit walks the sequence) must agree to
     rounding; the call continues from a carried state and Conv1D ring, which may be given in place."""
     import paper_2402_19427_amd as R
@@ -275,21 +275,21 @@ BWD_SHAPES = [
     (3, 3, 40, 5, "f32"),
     (2, 1, 16, 1, "f32"),
     (2, 75, 512, 2, "bf16"),
-    (2, 33, 320, 2, "bf16"),      # bs = 160: the problem is widened to 256-channel blocks
+    (2, 33, 320, 2, "bf16"),      # bs = 160: tiles
     (3, 300, 2560, 16, "bf16"),   # the same at the paper's width, 16 blocks
-    (1, 1100, 384, 2, "bf16"),    # bs = 192, long sequence in time slices
-    (2, 100, 2816, 8, "bf16"),    # bs = 352: pointwise part in passes, contractions on the generic kernels
-    (1, 700, 1024, 2, "bf16"),    # bs = 512, adjoint scan in time slices
+    (1, 1100, 384, 2, "bf16"),    # bs = 192, long sequence in time slices (tiles)
+    (2, 100, 2816, 8, "bf16"),    # bs = 352: tiles
+    (1, 700, 1024, 2, "bf16"),    # bs = 512: tiles in time slices
     (3, 70, 256, 4, "bf16"),      # bs = 64
     (4, 1, 1024, 2, "bf16"),      # bs = 512, a single step
     (1, 24, 512, 8, "bf16"),      # bs = 64, B T a multiple of 8 but smaller than a tile
     (1, 270, 600, 2, "bf16"),
-    (1, 1, 256, 1, "bf16"),       # MFMA path, single step
-    (2, 31, 256, 1, "bf16"),      # MFMA path, one partial tile
-    (1, 700, 256, 1, "bf16"),     # MFMA path, one unit in 16 time slices
-    (1, 13000, 256, 1, "bf16"),   # ... over a long sequence: 26 rounds of the slices, the record rings wrap (forward: windows)
-    (33, 70, 1024, 4, "bf16"),    # MFMA path, 132 units, no slicing
-    (8, 300, 2048, 8, "bf16"),    # MFMA path, 64 units x 4 slices
+    (1, 1, 256, 1, "bf16"),       # tiles, single step
+    (2, 31, 256, 1, "bf16"),      # tiles, one partial tile
+    (1, 700, 256, 1, "bf16"),     # tiles, one unit in as many time slices as there are
+    (1, 13000, 256, 1, "bf16"),   # ... over a long sequence: many rounds of the slices, the record rings wrap
+    (33, 70, 1024, 4, "bf16"),    # tiles, 132 units, no slicing
+    (8, 300, 2048, 8, "bf16"),    # tiles, 64 units x 4 slices
 ]
 
 
@@ -339,10 +339,12 @@ def test_backward_optional_outputs_can_be_skipped():
     np.testing.assert_array_equal(rn.to_host(g["dW_a"]), rn.to_host(full["dW_a"]))
 
 
-@pytest.mark.parametrize("B,T,D,nb", [(2, 200, 512, 2),       # fused kernels
-                                      (2, 200, 2560, 16),     # narrower blocks: padded tile, widened copy
-                                      (2, 200, 1024, 2),      # 512-channel blocks: passes
-                                      (10, 300, 2048, 8)])    # fused kernels with time slices
+@pytest.mark.parametrize("B,T,D,nb", [(2, 200, 512, 2),       # fused forward, backward in tiles
+                                      (2, 200, 2560, 16),     # narrower blocks: tiles
+                                      (2, 200, 1024, 2),      # 512-channel blocks: forward in passes
+                                      (10, 300, 2048, 8),     # both with time slices
+                                      (1, 2100, 512, 2), (2, 700, 704, 2),   # tiles in as many time slices as the chip holds
+                                      (3, 200, 256, 4)])      # 64-channel blocks: passes
 def test_results_are_deterministic_run_to_run(B, T, D, nb):
     rn = runner()
     act = "bf16"
@@ -407,7 +409,7 @@ def test_whole_step_replays_as_a_hip_graph():
 
 
 def test_long_prompt_forward_replays_as_a_hip_graph():
-    """The windows of a single long prompt (ring pass, aggregate pass, chain, forward proper) captured
+    """The forward of a single long prompt (preparation, tiles in time slices) captured
     into a HIP graph: every replay gives the bits of the eager run, whatever the workspace held."""
     import torch
     import paper_2402_19427_amd as R
@@ -441,7 +443,7 @@ def test_long_prompt_forward_replays_as_a_hip_graph():
             assert torch.equal(v, eager[k]), (rep, k)
 
 
-@pytest.mark.parametrize("D,nb", [(2560, 16),     # 160-channel blocks: padded tile, backward on the widened copy
+@pytest.mark.parametrize("D,nb", [(2560, 16),     # 160-channel blocks: tiles
                                   (1024, 2)])      # 512-channel blocks: forward and decode as separate kernels
 def test_merge_step_replays_as_a_hip_graph(D, nb):
     """forward + merge, backward + merge and a decode step + merge captured into one HIP graph on
@@ -598,10 +600,10 @@ MERGE_SHAPES = [
     (2, 130, 512, 2, "bf16"),    # MFMA path, ragged T
     (33, 70, 1024, 4, "bf16"),   # MFMA path, one workgroup per unit
     (8, 600, 2048, 8, "bf16"),   # MFMA path, time slices
-    (1, 1500, 256, 1, "bf16"),   # MFMA path, 16 time slices: the merge runs as a kernel of its own
-    (1, 12500, 256, 1, "bf16"),  # MFMA path, contiguous windows in two passes, merge as epilogue of the second
-    (3, 300, 2560, 16, "bf16"),  # bs = 160 in the padded tile, merge as epilogue
-    (2, 100, 2816, 8, "bf16"),   # bs = 352: separate passes, then the merge kernel
+    (1, 1500, 256, 1, "bf16"),   # tiles in time slices, merge as epilogue
+    (1, 12500, 256, 1, "bf16"),  # ... over a long sequence
+    (3, 300, 2560, 16, "bf16"),  # bs = 160 in tiles, merge as epilogue
+    (2, 100, 2816, 8, "bf16"),   # bs = 352: tiles, merge as epilogue
 ]
 
 
@@ -630,8 +632,8 @@ def test_forward_merge_matches_oracle(B, T, D, nb, act, tanh_form, keep_y):
 
 @pytest.mark.parametrize("B,T,D,nb,act", [(2, 37, 96, 3, "f32"), (1, 9, 24, 24, "bf16"),
                                           (2, 130, 512, 2, "bf16"), (8, 600, 2048, 8, "bf16"),
-                                          (3, 300, 2560, 16, "bf16"),   # widened copy behind the merge adjoint
-                                          (2, 100, 2816, 8, "bf16")])   # backward in passes behind it
+                                          (3, 300, 2560, 16, "bf16"),   # tiles
+                                          (2, 100, 2816, 8, "bf16")])   # tiles
 @pytest.mark.parametrize("tanh_form", [False, True])
 def test_backward_merge_matches_oracle(B, T, D, nb, act, tanh_form):
     import paper_2402_19427_amd as R
@@ -720,8 +722,8 @@ def test_decode_steps_with_merge_match_oracle(B, D, nb, act, tanh_form):
 # ------------------------------------------------------------------ the layer without its Conv1D
 @pytest.mark.parametrize("B,T,D,nb,act", [(2, 37, 96, 3, "f32"),      # generic kernels
                                           (2, 130, 512, 2, "bf16"),   # fused kernels
-                                          (1, 1100, 256, 1, "bf16"),  # fused, 16 time slices
-                                          (1, 12300, 256, 1, "bf16"), # fused, contiguous windows in two passes
+                                          (1, 1100, 256, 1, "bf16"),  # tiles in time slices
+                                          (1, 12300, 256, 1, "bf16"), # ... over a long sequence
                                           (2, 70, 320, 2, "bf16"),    # padded tile
                                           (1, 75, 1024, 2, "bf16")])  # passes of the wide blocks
 def test_conv_width_zero_is_the_rglru_layer_alone(B, T, D, nb, act):

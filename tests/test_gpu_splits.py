@@ -271,9 +271,9 @@ def test_time_slices_that_do_not_divide_the_ring(G):
         assert gen.rel_err(rn.to_host(got[k]), ref[k]) < BF16, k
 
 
-@pytest.mark.parametrize("bs", [160, 352])
+@pytest.mark.parametrize("bs", [96, 160, 352])
 def test_layer_passes_keep_a_nan_of_a_gate(bs):
-    """A NaN in one channel's gate reaches every gradient it reaches in the oracle, and no other."""
+    """(Passes at 96 channels, tiles at the others.) A NaN in one channel's gate reaches every gradient it reaches in the oracle, and no other."""
     rn = runner()
     B, T, nb, act = 2, 130, 2, "bf16"
     inp = gen.make_inputs(B, T, bs * nb, nb, act=act, seed=bs, dy=True, bias=True)
@@ -317,11 +317,12 @@ def test_complex_gated_inputs_past_half_precision(T, hs):
         assert gen.rel_err(rn.to_host(got[k]), ref[k]) < BF16, k
 
 
-def test_layer_passes_stay_finite_past_half_precision():
-    """In the backward of 160-channel blocks x in half precision feeds products only: an x past its range
+@pytest.mark.parametrize("bs", [96, 160])
+def test_layer_passes_stay_finite_past_half_precision(bs):
+    """In the backward (passes at 96 channels, tiles at 160) x in half precision feeds products only: an x past its range
     closes or opens gates, it puts no infinity into them. (No reference: with m_t = 0 the oracle has 0 / 0.)"""
     rn = runner()
-    B, T, bs, nb, act = 1, 300, 160, 2, "bf16"
+    B, T, nb, act = 1, 300, 2, "bf16"
     inp = gen.make_inputs(B, T, bs * nb, nb, act=act, seed=7, dy=True, bias=True)
     _large(inp, 20)
     dp = rn.DeviceProblem(inp, B, T, bs * nb, nb, act)
@@ -332,9 +333,9 @@ def test_layer_passes_stay_finite_past_half_precision():
         assert np.all(np.isfinite(rn.to_host(v))), k
 
 
-@pytest.mark.parametrize("bs", [160, 352])
+@pytest.mark.parametrize("bs", [96, 160, 352])
 def test_layer_passes_round_what_they_store(bs):
-    """Sums over time: stored adjoints rounded to nearest leave errors of at most 2^-12 each that average
+    """(Passes at 96 channels, tiles at the others.) Sums over time: stored adjoints rounded to nearest leave errors of at most 2^-12 each that average
     out, truncated ones shift dx (stored twice) by 2^-11 of its size (2^-12 on average each time)."""
     rn = runner()
     B, T, nb, act = 2, 600, 2, "bf16"
