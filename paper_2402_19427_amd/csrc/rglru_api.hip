@@ -733,7 +733,7 @@ int rglru_backward_packed(const rglru_shape *shape, const rglru_params *params, 
   q.ws = workspace; q.ws_bytes = workspace_bytes;
   const bool bf = shape->act_dtype == RGLRU_BF16;
   hipError_t e;
-  if (backward_tile_supported(q, bf)) {
+  if (reset && backward_tile_supported(q, bf)) {
     e = launch_backward_tile(q, (hipStream_t)stream);
   } else if (reset && backward_mfma_supported(q, bf)) {
     e = launch_backward_mfma(q, (hipStream_t)stream);   // the fused kernels take the boundaries as bit masks

@@ -719,7 +719,11 @@ Instance pick_merge(int var) {
 template <int NCT, int MT, int WPE, int PD, int K>
 Instance pick(int var) {
   if (var == V_PLAIN) return instance<NCT, MT, V_PLAIN, WPE, PD, K>();
-  if (var == V_PACKED) return instance<NCT, MT, V_PACKED, WPE, PD, K>();
+  if constexpr (NCT == 8) {   // (packed rows: 256 channels only)
+    if (var == V_PACKED) return instance<NCT, MT, V_PACKED, WPE, PD, K>();
+  } else {
+    if (var == V_PACKED) return {nullptr, 0, 0, 0, 0};
+  }
   if constexpr (MT == 1) return pick_merge<NCT, MT, WPE, PD, K>(var);
   else return {nullptr, 0, 0, 0, 0};
 }

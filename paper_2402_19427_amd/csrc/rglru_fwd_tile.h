@@ -414,7 +414,11 @@ Instance fwd_instance() {
 template <int NCT, int MT, int WPE, int PD, int MTM, int WPEM>   // (MTM, WPEM: with the merge)
 Instance fwd_pick(int var) {
   if (var == V_PLAIN) return fwd_instance<NCT, MT, V_PLAIN, WPE, PD>();
-  if (var == V_PACKED) return fwd_instance<NCT, MT, V_PACKED, WPE, PD>();
+  if constexpr (NCT <= 8) {   // (packed rows: 128 - 256 channels)
+    if (var == V_PACKED) return fwd_instance<NCT, MT, V_PACKED, WPE, PD>();
+  } else {
+    if (var == V_PACKED) return {nullptr, 0, 0, 0, 0};
+  }
   return var == V_MERGE ? fwd_instance<NCT, MTM, V_MERGE, WPEM, PD>() : fwd_instance<NCT, MTM, V_MERGE_TANH, WPEM, PD>();
 }
 Instance find_fwd_instance_a(int nct, int var);   // 4 - 6

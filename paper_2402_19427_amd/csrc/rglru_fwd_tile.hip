@@ -44,10 +44,13 @@ Plan make_plan(int B, int T, int nb, int bs, bool packed, const Instance &in, in
 }  // namespace
 
 namespace {
-// the shapes whose kernels wait for each other anyway: their workspace brings a status word
-bool shape_ok(int B, int T, int D, int bs) {
-  return bs % 16 == 0 && T >= 1 && (size_t)D * 2 * 64 < ((size_t)1 << 31) && (long long)B * ((T + 31) / 32) < ((long long)1 << 30) &&
-         (forward_mfma_block(bs) || (D % 256 == 0 && (size_t)B * T * D * 2 < ((size_t)1 << 31)));
+// The shapes whose products run in half precision whatever kernel takes them: the fused kernel's, and without document boundaries
+// the passes'. What the general kernels serve (packed rows of the other blocks, sequences of 2^31 bytes and more, 2^32 at 256 channels) they
+// serve in plain fp32 arithmetic: hT of packed rows of 352 channels is 2e-7 off, 7e-5 in tiles.
+bool shape_ok(int B, int T, int D, int bs, bool packed) {
+  if (bs % 16 != 0 || T < 1 || (size_t)D * 2 * 64 >= ((size_t)1 << 31) || (long long)B * ((T + 31) / 32) >= ((long long)1 << 30)) return false;
+  if (forward_mfma_block(bs)) return (size_t)T * D * 2 < ((size_t)1 << (bs == 256 ? 32 : 31));
+  return !packed && D % 256 == 0 && (size_t)B * T * D * 2 < ((size_t)1 << 31);
 }
 // Where tiles are the faster forward (us, tiles : before).
 // Blocks the fused kernel does not take (through passes before): everywhere. 352 channels B 4 T 2048 165 : 274, B 1 T 16
@@ -114,14 +117,14 @@ size_t bytes(int B, int T, int nb, int bs, int var, size_t room) {
 
 size_t forward_tile_ws_bytes(int B, int T, int D, int nb, bool packed, bool merge, size_t room) {
   const int bs = D / nb;
-  if (!shape_ok(B, T, D, bs)) return 0;
+  if (!shape_ok(B, T, D, bs, packed)) return 0;
   if (packed) return bytes(B, T, nb, bs, V_PACKED, room);
   return std::max(bytes(B, T, nb, bs, V_PLAIN, room), merge ? bytes(B, T, nb, bs, V_MERGE, room) : (size_t)0);
 }
 
 // By the size the call asks for: the same kernels for a shape, whoever lays the workspace out
 bool forward_tile_supported(const Problem &p, bool bf, size_t asked) {
-  if (!bf || !p.ws || (uintptr_t)p.ws % 16 != 0 || !shape_ok(p.B, p.T, p.D, p.bs)) return false;
+  if (!bf || !p.ws || (uintptr_t)p.ws % 16 != 0 || !shape_ok(p.B, p.T, p.D, p.bs, p.reset != nullptr)) return false;
   if (((uintptr_t)p.u | (uintptr_t)p.y | (p.merge ? (uintptr_t)p.out | (uintptr_t)p.branch : 0)) % 16 != 0) return false;
   const size_t need = bytes(p.B, p.T, p.nb, p.bs, variant(p), asked);
   return need && need <= asked && p.ws_bytes >= asked;

@@ -184,3 +184,31 @@ def test_backward_in_a_workspace_the_tiles_do_not_fit(B, T, bs, nb, merge):
     ref = oracle.backward_merge(q["u"], br, *w, q["dy"], **kw) if merge else oracle.backward(q["u"], *w, q["dy"], **kw)
     for name in ref:
         assert gen.rel_err(rn.to_host(got[name]), ref[name]) < BF16, name
+
+
+@pytest.mark.parametrize("B,T,bs,nb", [(2, 2000, 128, 2), (2, 1500, 352, 1), (1, 600, 384, 2), (1, 333, 448, 4), (1, 40, 272, 16)])
+def test_packed_rows_in_fp32_arithmetic(B, T, bs, nb):
+    """Packed rows of the blocks that no fused kernel takes run in plain fp32 arithmetic: what leaves in fp32 - the state of the forward, and
+    in the backward (given the exact y, rounded once) the gradients that h_{t-1} does not enter - is that of fp32 sums over
+    the longest row: 8 sqrt(T) 2^-24 of its scale."""
+    import torch
+    rn = runner()
+    D, act = bs * nb, "bf16"
+    inp = gen.make_inputs(B, T, D, nb, act=act, seed=T + bs, h0=True, dy=True, bias=True)
+    dp, q = rn.DeviceProblem(inp, B, T, D, nb, act), f64(inp)
+    u, h0, dy = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32"), rn.to_device(inp["dy"], act)
+    reset = gen.make_resets(B, T, seed=bs, mean_len=200)
+    rs = torch.from_numpy(reset).cuda()
+    w = (q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"])
+    kw = dict(conv_b=q["conv_b"], h0=q["h0"], reset=reset)
+    y_ref, hT_ref, _ = oracle.forward(q["u"], *w, **kw)
+    ref = oracle.backward(q["u"], *w, q["dy"], **kw)
+    tol = 8 * np.sqrt(T) * 2.0 ** -24
+    n2 = lambda a, b: np.linalg.norm(np.asarray(a, np.float64) - b) / np.linalg.norm(b)
+    if bs > 256:
+        _, hT, _ = dp.forward_packed(u, rs, h0=h0)
+        assert n2(rn.to_host(hT), hT_ref) < tol
+    y = rn.to_device(gen.round_to_act(y_ref.astype(np.float32), act), act)
+    got = dp.backward_packed(u, rs, y, dy, h0=h0)
+    for k in ("dh0", "dW_x", "db_x"):
+        assert n2(rn.to_host(got[k]), ref[k]) < tol, k

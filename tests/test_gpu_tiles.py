@@ -43,8 +43,7 @@ def test_tiles(B, T, bs, nb, slices, how):
     w = (q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"])
     kw = dict(conv_b=q["conv_b"], h0=q["h0"], state_in=q["state"])
     dev = dict(h0=h0, state_in=ring, pos0=pos0)
-    # (room for the tiles at every size: what the calls ask for is what each had before there were tiles, and short
-    # packed rows then run on the general kernels)
+    # (room for the tiles at every size)
     ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0")
     dp.workspace = lambda shape, op: (ws, ws.numel())
     R.rglru_set_max_time_slices(slices)
@@ -73,7 +72,8 @@ def test_tiles(B, T, bs, nb, slices, how):
         R.rglru_timing_enable(False)
         R.rglru_set_max_time_slices(0)
     merged = how in ("merge", "tanh")
-    assert ("bwd_tile_kernel" in names and "tile_wgrad_kernel" in names) == (not merged or bs <= 352), names   # (LDS does not hold wider tiles with the merge)
+    # (LDS does not hold wider tiles with the merge; packed rows of other blocks run on the general kernels)
+    assert ("bwd_tile_kernel" in names and "tile_wgrad_kernel" in names) == (bs <= 352 if merged else bs == 256 if how == "packed" else True), names
     for k in ref:
         assert gen.rel_err(rn.to_host(got[k]), ref[k]) < BF16, k
 
@@ -90,8 +90,6 @@ def test_forward_tiles(B, T, bs, nb, slices, how):
     import paper_2402_19427_amd as R
     rn = runner()
     D, act, pos0 = bs * nb, "bf16", 5
-    if how == "packed" and (bs > 256 or bs < 128):   # (what such a call asks for is the general kernels' scratch: in a few steps less than
-        T = max(T, 333)                              # the tiles take, and the general kernels run)
     inp = gen.make_inputs(B, T, D, nb, act=act, seed=T + bs, h0=True, state=True, bias=True)
     dp, q = rn.DeviceProblem(inp, B, T, D, nb, act), f64(inp)
     u, h0 = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32")
@@ -120,7 +118,7 @@ def test_forward_tiles(B, T, bs, nb, slices, how):
         R.rglru_timing_enable(False)
         R.rglru_set_max_time_slices(0)
     if D % 256 == 0 or bs <= 256:
-        assert ("fwd_tile_kernel" in names) == (bs <= 480), names
+        assert ("fwd_tile_kernel" in names) == (bs <= 480 and (how != "packed" or 128 <= bs <= 256)), names   # (the others: general kernels)
     assert gen.rel_err(rn.to_host(y), want[0]) < BF16
     assert gen.rel_err(rn.to_host(hT), want[1]) < BF16
     np.testing.assert_array_equal(rn.to_host(st), gen.ring_from_chrono(np.asarray(want[2], np.float32), pos0 + T))
@@ -135,7 +133,8 @@ def test_states_in_place_in_slices(B, T, bs, nb, how):
     import torch
     import paper_2402_19427_amd as R
     rn = runner()
-    T = max(T, 333) if how == "packed" and bs > 256 else T
+    if how == "packed" and bs > 256:
+        pytest.skip("packed rows of such blocks run on the general kernels")
     D, act, pos0 = bs * nb, "bf16", 4
     inp = gen.make_inputs(B, T, D, nb, act=act, seed=T + bs, h0=True, state=True, bias=True)
     dp = rn.DeviceProblem(inp, B, T, D, nb, act)
@@ -168,29 +167,6 @@ def test_states_in_place_in_slices(B, T, bs, nb, how):
         h, ring = h0.clone(), ring0.clone()
         for a, b in zip(call(h, h, ring, ring), want):
             assert torch.equal(a, b)
-
-
-def test_a_mark_in_front_of_packed_wide_rows_is_reported():
-    """Packed rows of wide blocks wait for records, too: the mark (planted from the host) makes NaNs and is reported once."""
-    import torch
-    import paper_2402_19427_amd as R
-    rn = runner()
-    B, T, bs, nb, act = 1, 700, 384, 2, "bf16"
-    inp = gen.make_inputs(B, T, bs * nb, nb, act=act, seed=3)
-    dp = rn.DeviceProblem(inp, B, T, bs * nb, nb, act)
-    u, rs = rn.to_device(inp["u"], act), torch.from_numpy(gen.make_resets(B, T, seed=1, mean_len=400)).cuda()
-    ok, _, _ = dp.forward_packed(u, rs)
-    ws, _ = dp.workspace(dp.shape(), R.OP_FORWARD_PACKED)
-    R.rglru_workspace_status(dp.shape(), R.OP_FORWARD_PACKED, ws)
-    ws[:16] = torch.tensor(list(struct.pack("<4I", 0x4c474c52, 0x58452d55, 0x45524950, 0xb3d3b3ad)), dtype=torch.uint8, device="cuda:0")
-    bad, _, _ = dp.forward_packed(u, rs)
-    assert torch.isnan(bad.float()).any()
-    with pytest.raises(R.RglruError) as e:
-        R.rglru_workspace_status(dp.shape(), R.OP_FORWARD_PACKED, ws)
-    assert e.value.code == R.ERR_TIMEOUT
-    R.rglru_workspace_status(dp.shape(), R.OP_FORWARD_PACKED, ws)
-    again, _, _ = dp.forward_packed(u, rs)
-    assert torch.equal(again, ok)
 
 
 @pytest.mark.parametrize("bs", [160, 256])
@@ -228,6 +204,8 @@ def test_state_behind_infinite_last_inputs(bs, nb, T, how):
     import paper_2402_19427_amd as R
     rn = runner()
     D, act = bs * nb, "bf16"
+    if how == "packed" and bs > 256:
+        pytest.skip("packed rows of such blocks run on the general kernels")
     inp = gen.make_inputs(1, T, D, nb, act=act, seed=T + bs, h0=True, bias=True)
     inp["u"][0, T - 1, 3] = np.inf
     inp["u"][0, T - 3, bs + 5] = -np.inf
@@ -295,8 +273,8 @@ def test_backward_of_a_ragged_tile_ignores_what_lies_past_the_end(bs, nb, T, how
             R.rglru_timing_enable(False)
         return {k: v.cpu() for k, v in g.items() if v is not None}
 
-    if how == "merge" and bs > 352:
-        pytest.skip("LDS does not hold the merge of such blocks")
+    if how == "merge" and bs > 352 or how == "packed" and bs != 256:
+        pytest.skip("LDS does not hold the merge of such blocks; packed rows of others than 256 channels run on the general kernels")
     want = call(y)
     for k, v in want.items():
         v = v.float()
