@@ -247,6 +247,35 @@ bool shape_ok(int B, int T, int D, int nb, bool packed) {
   return D / nb % 16 == 0 && T >= 1 && (long long)B * ((T + 31) / 32) < ((long long)1 << 30) && (size_t)D * 2 * 64 < ((size_t)1 << 31);
 }
 
+// Where tiles are the faster backward: everywhere but for a few sequences' blocks of many steps, where 16 slices each leave most of
+// the chip idle while what runs instead (the passes; at 256 channels three kernels) is parallel over all of time. What decides is how
+// many workgroups there are (16 per unit of sequence and block) and how often each goes round. us, tiles : passes, over block sizes, units
+// and T from 300 to 32768 (4506 calls):
+// - 112 to 192 channels: up to 8 units (9 up to 128 channels), from 9 - 12 rounds on, more for more units (160, one block: T 4096
+//   97 : 120, T 16384 322 : 141; 8 units, T 4096 108 : 129, T 16384 337 : 347, with the merge 411 : 386).
+// - 208 to 240: from 8 rounds of 32 steps on, without the merge (tiles of 64 steps) up to 4 units, with it up to 8 (240, 3 blocks: T 4096
+//   106 : 126, T 8192 186 : 149).
+// - 256: with the merge, up to 3 units of 32 rounds and more (one block: T 8192 246 : 280, T 32768 879 : 762).
+// - 272 to 384: up to 7 units (8 with the merge, or above 320 channels from 16 rounds on), from 5 - 6 rounds on (352, one block: T 2048 104 : 123, T 4096 174 : 127; 384, 7
+//   blocks, T 4096 211 : 228, T 8192 388 : 382).
+// - 400 to 512, whose tiles spill: up to 10 units from 4 rounds on, 3 above 448 channels (512, 4 blocks: T 1024 115 : 141, T 2048
+//   179 : 155, T 4096 318 : 183; 10 blocks, T 6144 620 : 581); 11 from 8 on.
+// Calls past these lines gave up to five times their time away to the tiles (512, one block, T 16384).
+bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
+  const bool merge = var == V_MERGE || var == V_MERGE_TANH;
+  if (T <= 256) return true;   // (even a single slice's 8 rounds take no longer than the launches of the passes)
+  // (for 256 compute units: the same rule where no card is visible)
+  const int ntile = (T + 32 * in.mt - 1) / (32 * in.mt), G = pick_slices(B * nb, ntile, in.per_cu * 256, 16);
+  const long long w = (long long)B * nb * G, rounds = (long long)((ntile + G - 1) / G) * in.mt;   // workgroups; rounds of 32 steps
+  const auto units = [&](int n) { return w <= 16 * n; };
+  if (bs <= 192) return !units(bs <= 128 ? 9 : 8) || 32 * rounds <= 256 + w;
+  if (bs < BS) return !units(merge ? 8 : 4) || rounds <= (merge ? 7 : 7 + w / 16);
+  if (bs == BS) return !merge || !units(3) || rounds < 32;
+  if (bs <= 384) return !units(merge || (bs > 320 && rounds >= 16) ? 8 : 7) || 64 * rounds <= (bs <= 320 ? 320 : 256) + w;
+  if (units(10)) return rounds <= (bs <= 448 ? 3 : 2);
+  return !units(11) || rounds <= 7;
+}
+
 }  // namespace
 
 // these kernels ask for more than the default LDS limit; told once per instance
@@ -283,6 +312,7 @@ bool backward_tile_supported(const Problem &p, bool bf) {
   if (!bf || p.dy_lo || !shape_ok(p.B, p.T, p.D, p.nb, p.reset != nullptr) || (uintptr_t)p.ws % 16 != 0) return false;
   const Instance in = find_instance(p.bs, variant(p));
   if (!in.kernel || (p.bs == BS && !on_grid(p))) return false;
+  if (!worth(p.B, p.T, p.nb, p.bs, variant(p), in) && (p.bs == BS ? backward_mfma_supported(p, true) : backward_pass_supported(p, true))) return false;
   const size_t r = room(p.B, p.T, p.D, p.bs, p.merge != 0), have = p.ws_bytes > r ? p.ws_bytes - r : 0;
   return have >= make_plan(p.B, p.T, p.D, p.nb, p.reset != nullptr, in, have, compute_units()).total;
 }

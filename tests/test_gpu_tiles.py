@@ -358,3 +358,40 @@ def test_forward_takes_the_faster_kernel(B, T, bs, nb, merge, tiles):
     assert ("fwd_tile_kernel" in names and "merge_fwd_kernel" not in names) == tiles, names
     _, b, k = call(1)
     assert ((a - b).norm() / b.norm()).item() < 2.0 ** -9 and ((h - k).norm() / k.norm()).item() < 2.0 ** -9
+
+
+@pytest.mark.parametrize("T,bs,nb,merge,tiles,cap", [
+    (4096, 112, 1, False, True, 0), (4097, 112, 1, False, False, 0), (6000, 112, 10, False, True, 0), (4096, 192, 1, True, True, 0),
+    (4609, 192, 1, True, False, 0), (4096, 224, 1, False, True, 0), (4200, 224, 1, False, False, 0), (3584, 240, 1, True, True, 0),
+    (3600, 240, 1, True, False, 0), (15872, 256, 1, True, True, 0), (16000, 256, 1, True, False, 0), (16000, 256, 1, False, True, 0),
+    (2560, 320, 1, False, True, 0), (2592, 320, 1, True, False, 0), (2048, 352, 1, True, True, 0), (2100, 352, 1, False, False, 0),
+    (4096, 352, 7, False, False, 0), (4096, 352, 8, False, True, 0), (1536, 448, 1, False, True, 0), (1540, 448, 1, False, False, 0),
+    (1024, 512, 1, False, True, 0), (1030, 512, 1, False, False, 0), (3584, 512, 11, False, True, 0), (3600, 512, 11, False, False, 0),
+    (3600, 512, 12, False, True, 0), (600, 128, 4, False, False, 1)])
+def test_backward_takes_the_faster_kernel(T, bs, nb, merge, tiles, cap):
+    """Either side of the rule between the tiles and what is parallel over all of time; against the oracle where one block is quick."""
+    import torch
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D, act = bs * nb, "bf16"
+    inp = gen.make_inputs(1, T, D, nb, act=act, seed=T + bs, h0=True, dy=True, bias=True)
+    dp, q = rn.DeviceProblem(inp, 1, T, D, nb, act), f64(inp)
+    u, h0, dy = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32"), rn.to_device(inp["dy"], act)
+    br = gen.make_branch(1, T, D, act=act, seed=T)
+    R.rglru_set_max_time_slices(cap)
+    try:
+        y, _, _ = dp.forward(u, h0=h0)
+        R.rglru_timing_enable(True)
+        got = dp.backward_merge(u, rn.to_device(br, act), y, dy, h0=h0) if merge else dp.backward(u, y, dy, h0=h0)
+        torch.cuda.synchronize()
+        names = names_of(R)
+    finally:
+        R.rglru_timing_enable(False)
+        R.rglru_set_max_time_slices(0)
+    assert ("bwd_tile_kernel" in names) == tiles, names
+    if nb * T * bs * bs > 600e6:
+        return
+    w, kw = (q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"]), dict(conv_b=q["conv_b"], h0=q["h0"])
+    ref = oracle.backward_merge(q["u"], br, *w, q["dy"], **kw) if merge else oracle.backward(q["u"], *w, q["dy"], **kw)
+    for k in ref:
+        assert gen.rel_err(rn.to_host(got[k]), ref[k]) < BF16, k
