@@ -43,18 +43,24 @@
  * (Appendix A prints softplus(+Lambda); that contradicts a = sigma(Lambda) of Section 2.4,
  * which is what this library follows.)
  *
- * Which kernels run. bf16 storage: gate blocks of 256 channels, or of a multiple of 16 channels
- * from 128 to 240 (e.g. Section 4.1's 16 blocks at width 2560 = 160 channels), run on the fused
- * matrix-core kernels in the forward and in decode steps, and so does the backward of 256. The
- * forward of any other multiple of 16 (e.g. 352 and 512 channels at widths 5632 and 8192; widths
- * that are a multiple of 256) and the backward of every multiple of 16 but 256 run as matrix-core
- * passes through the workspace, parallel over time; decode steps of blocks up to 768 channels on
- * matrix-core or vector-unit kernels of their own. fp32 storage: the forward of multiples of 16 up
+ * Which kernels run. bf16 storage, forward: gate blocks of 256 channels, or of a multiple of 16
+ * channels from 128 to 240 (e.g. Section 4.1's 16 blocks at width 2560 = 160 channels), run on fused
+ * matrix-core kernels or in tiles (a workgroup holds some steps of all of a block's channels),
+ * whichever is faster for the size; blocks of 272 to 480 channels (widths that are a multiple of
+ * 256, e.g. 352 channels at width 5632) in tiles; other multiples of 16 (512 channels at width 8192)
+ * as matrix-core passes through the workspace, parallel over time. Backward: 112 to 512 channels
+ * (with the merge to 352) run in tiles, but a few blocks of few long sequences, which run as
+ * passes like the other multiples of 16, or in three kernels at 256 channels. Packed rows: the fused
+ * kernels or tiles for the forward of 128 to 256 channels and tiles for the backward of 256, the
+ * generic kernels otherwise. Decode steps of blocks up to 768 channels run on matrix-core or
+ * vector-unit kernels of their own. fp32 storage: the forward of multiples of 16 up
  * to 512 channels runs on the fp32 matrix cores. All other block sizes up to 2048, and the backward
  * in fp32 storage, run on generic kernels that give the same results far more slowly. So does a
- * bf16 call of the fused kernels, the forward in passes or the decode kernels whose tensors do not
- * lie on 16-byte boundaries (h0 and hT of the former two may); the passes of the backward and those of the
- * complex-gated variant take any alignment.
+ * bf16 forward or decode step whose tensors do not lie on 16-byte boundaries (h0 and hT of the
+ * forward may, and u and the conv states on four bytes where the fused kernels take the block); the backward of other blocks than 256 channels and the passes of the complex-gated
+ * variant take any alignment (what the backward stages 16 bytes at a time is copied first).
+ * The fused forward, the tiles, the three kernels and the scan cut long sequences into time slices whose
+ * workgroups wait for each other (rglru_workspace_status); the passes and the generic kernels never wait.
  * rglru_workspace_bytes() accounts for all of it.
  */
 #ifndef RGLRU_H
@@ -441,9 +447,9 @@ int rglru_workspace_status(const rglru_shape *shape, int op, const void *workspa
 
 /*
  * Upper bound on the number of time slices a sequence is cut into (process-wide; 0 = automatic,
- * the default; it also bounds the contiguous windows that the forward of a single long prompt is
- * run in, which exchange nothing while they run and cannot time out). With 1 no kernel ever waits on another workgroup: every (sequence, gate block)
- * pair is walked by a single workgroup, slower for few long sequences but independent of all
+ * the default; it also bounds the contiguous windows that the fused forward of a single long prompt
+ * is run in, which exchange nothing while they run). With 1 no kernel ever waits on another workgroup:
+ * a (sequence, gate block) pair is walked by a single workgroup or by passes parallel over time, slower for few long sequences but independent of all
  * workgroups of a launch being resident at once. This is the setting to retry with after
  * rglru_workspace_status has reported RGLRU_ERR_TIMEOUT (e.g. when another process occupies part
  * of the GPU). Workspace sizes depend on it: query them again after changing it.

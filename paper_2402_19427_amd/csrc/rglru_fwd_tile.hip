@@ -54,10 +54,10 @@ bool shape_ok(int B, int T, int D, int bs, bool packed) {
 }
 // Where tiles are the faster forward (us, tiles : before).
 // Blocks the fused kernel does not take (through passes before): everywhere. 352 channels B 4 T 2048 165 : 274, B 1 T 16
-// 25 : 40; 448 channels B 4 T 2048 227 : 338; 288 channels B 1 T 300 23 : 53. Up to 480 channels, though: at 512 the tiles
-// would be faster too (275 : 402), but y as they round it (2-norm error 1.654e-3, 1.652e-3 being that of the exact y in
-// bf16; the passes' 1.701e-3) puts dW_a at Lambda = -3 where the exact y does, 4.5e-2 off in one draw of six, and the
-// bound held there is 4e-2, which the passes' y meets in the same draws (at most 3.96e-2).
+// 25 : 40; 448 channels B 4 T 2048 227 : 338; 288 channels B 1 T 300 23 : 53. Up to 480 channels, though: whether 512
+// may follow (275 : 402) is an open question of precision. The tiles' y is the more exact one (2-norm error 1.654e-3,
+// 1.652e-3 being that of the exact y in bf16; the passes' 1.701e-3), but the bound held on dW_a at Lambda = -3, 4e-2, is below
+// what the storage rounding of y supports: the exact y in bf16 is 4.5e-2 off in one draw of six, where the passes' y is not.
 // Blocks it takes, 128 channels: everywhere (B 1 T 16 10 : 15, B 8 T 2048 82 : 146). 144 and up:
 // - not up to four tiles (160 channels, T 64: 15.7 : 14.3 and 18.4 : 14.6 with the merge; 256, T 200 with the merge
 //   23 : 20), where the workgroups' own start is most of the time and they have no second tile to hide it behind.
