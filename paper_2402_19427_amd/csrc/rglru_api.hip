@@ -215,11 +215,14 @@ size_t forward_bytes(const rglru_shape *s, bool packed) {
 }
 size_t workspace_need(const rglru_shape *s, int op) {
   switch (op) {
-    case RGLRU_OP_BACKWARD:   // (the tiles take more than the passes where rows are few)
-      return !backward_pass_shape(s) ? least_backward_bytes(s)
-                                     : std::max({least_backward_bytes(s), narrow_backward_bytes(s),
-                                                 backward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks),
-                                                 backward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, false, false)});
+    case RGLRU_OP_BACKWARD: {   // (the tiles take more than the passes where rows are few, and more than the three kernels for
+                                // the partial sums of their weight gradients)
+      const size_t least = least_backward_bytes(s),
+                   tile = s->act_dtype == RGLRU_BF16 ? backward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, false, false) : 0;
+      return !backward_pass_shape(s) ? std::max(least, tile)
+                                     : std::max({least, tile, narrow_backward_bytes(s),
+                                                 backward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks)});
+    }
     case RGLRU_OP_SCAN:
       if (s->act_dtype == RGLRU_BF16 && s->D % 256 == 0 && s->T >= 1)
         return scan_tiled_ws_bytes(s->B, s->T, s->D);

@@ -41,7 +41,7 @@ struct FusedArgs {
   u64 *rec;
   int *err;
   const u32x4 *wg, *wd;       // weights in fragment order, [nb][wave][K-step][gate][lane]: as they are, transposed
-  unsigned short *xT, *pqT;   // half precision [B][MT ntile][D][32] x, [B][MT ntile][nb][2][bs][32] S dp | S dq
+  unsigned short *xT, *pqT;   // half precision x, S dp | S dq in stages of 32 steps (rglru_wgrad.h)
   const float *sc;            // sc[1] = S, sc[2] = 1 / S
   float *partA, *partC;       // [B G][3][D] sums for db_a, db_x, dLambda; [B G][5][D] for dconv_w, dconv_b
   float *edge;                // [B][ntile][6][D]: S dx of a tile's first and last three rows (sliced in time), or null
@@ -225,19 +225,15 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
     const u32x2 lo = lds_tr(t + f_rd[0] + rb * 2048), hi = lds_tr(t + f_rd[1] + rb * 2048);
     return __builtin_bit_cast(f16x8, (u32x4){lo[0], lo[1], hi[0], hi[1]});
   };
-  // [channel][step] tiles as they lie, to global memory: `per` bytes of all waves' channels per tile
-  auto copy_out = [&](const unsigned char *t, const unsigned short *out, size_t per) __attribute__((always_inline)) {
-    const int l = lane_again();   // 16 channels per kilobyte
-    const unsigned l_rd = (unsigned)(l >> 2) * 64 + (unsigned)((l & 3) ^ key(l >> 2)) * 16;
-#pragma unroll
-    for (int rb = 0; rb < MT; ++rb) {
-      const __amdgpu_buffer_rsrc_t rs = buf((const char *)out + rb * per, (size_t)bs * 64);
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-        store16<RGLRU_NT>(*(const u32x4 *)(t + l_rd + rb * 2048 + m * 1024), rs, (unsigned)l * 16, (unsigned)wv * 2048 + m * 1024);
-    }
+  // a lane's 16 steps, for the weight gradients (rglru_wgrad.h); `per` bytes of all blocks per 32 steps
+  auto run_out = [&](const unsigned (&v)[8], int rb, const unsigned short *out, size_t per) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rs = buf((const char *)out + rb * per, (size_t)bs * 64);   // (channels past the block: past its range)
+    const int l = lane_again();
+    const unsigned vo = (unsigned)wv * 2048 + (unsigned)((l >> 4) & 1) * 1024 + (unsigned)(l >> 5) * 512 + (unsigned)(l & 15) * 16;
+    store16<RGLRU_NT>(u32x4{v[0], v[1], v[2], v[3]}, rs, vo, 0);
+    store16<RGLRU_NT>(u32x4{v[4], v[5], v[6], v[7]}, rs, vo + 256, 0);
   };
-  // ... and as rows of a [B][T][D] tensor
+  // [channel][step] tiles as rows of a [B][T][D] tensor
   auto rows_out = [&](const unsigned char *t, void *out, int t0, unsigned nrow) __attribute__((always_inline)) {
     const __amdgpu_buffer_rsrc_t rs = buf((unsigned short *)out + (seq + t0) * D, (size_t)nrow * row2);
     // lane -> row 16 m + 4 (lane / 16) + (lane & 3), channels 8 ((lane & 15) / 4) .. + 7 in two reads
@@ -346,6 +342,7 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
         }
       }
       put16(my + L::X, rb, pk);
+      run_out(pk, rb, a.xT + (((size_t)b * a.ntile + tile) * MT * D + g * bs) * 32, (size_t)D * 64);
     }
     // ---- the upstream gradient (with the merge: dy = dout GeLU(branch) in fp32, dbranch = dout y GeLU'(branch))
     float dym[MERGE ? MT : 1][16];
@@ -382,7 +379,6 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
     }
     lds_barrier();   // x is there
     if constexpr (MERGE) rows_out(my + L::B, p.dbranch, t0, nrow);
-    copy_out(my + L::X, a.xT + (((size_t)b * a.ntile + tile) * MT * D + g * bs) * 32, (size_t)D * 64);
 
     // ---- gate pre-activations
     f32x16 accp[MT], accq[MT];
@@ -573,15 +569,13 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(W
       }
       put16(my + L::P, rb, pk);
       put16(my + L::Q, rb, qk);
+      const unsigned short *o = a.pqT + (((size_t)b * a.ntile + tile) * MT * D + g * bs) * 64;
+      run_out(pk, rb, o, (size_t)D * 128);
+      run_out(qk, rb, o + (size_t)bs * 32, (size_t)D * 128);
     }
 #pragma unroll
     for (int ks = 0; ks < PD; ++ks) load_w(wd_rs, ks);
     lds_barrier();   // dp, dq are there
-    {
-      const unsigned short *o = a.pqT + (((size_t)b * a.ntile + tile) * MT * D + g * bs) * 64;
-      copy_out(my + L::P, o, (size_t)D * 128);
-      copy_out(my + L::Q, o + (size_t)bs * 32, (size_t)D * 128);
-    }
     // ---- dx: the products with the transposed weights on top of the direct part
     {
       f16x8 fa[2][2][MT];

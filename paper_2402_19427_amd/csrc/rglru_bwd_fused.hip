@@ -1,5 +1,6 @@
 // The backward in tiles (see rglru_bwd_fused.h): preparation, weight gradients, dispatch.
 #include "rglru_fwd_tile.h"
+#include "rglru_wgrad.h"
 
 #include <algorithm>
 #include <atomic>
@@ -89,96 +90,6 @@ __global__ void __launch_bounds__(256) absmax_merge_kernel(const u32x4 *dout, co
   if (threadIdx.x == 0) parts[blockIdx.x] = __float_as_uint(fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3])));
 }
 
-// ------------------------------------------------------------------------ weight gradients
-// part[slice][g][gate bs + j][k] = sum over the slice's steps of S dp|dq[j][t] x[k][t]: 256 x 128 outputs per
-// workgroup of four waves, 64 x 128 each. Both operands lie time fastest, so that a fragment is one 16-byte
-// read; stages of 32 steps (256 + 128 rows of 64 bytes, pieces permuted by the row) by direct-to-LDS loads,
-// three buffers, two stages in flight (a counted wait: each wave loads six pieces of 16 rows per stage).
-// Bound by the operands' way into LDS: 24 KB per stage for 32 products of a wave. B 16 T 4096, 16 blocks of 256
-// channels: 346 us (0.79 PFLOP/s; 490 as it was, with x formed again from u); twice that with the loads marked streaming:
-// neighbouring workgroups share rows and want them in L2. Blocks that do not fill 256 x 128 pay for the rest: 160
-// channels use 39 % of their products.
-constexpr int WT_A = 256 * 64, WT_B = 128 * 64, WT_STAGE = WT_A + WT_B, WT_LDS = 3 * WT_STAGE;
-static_assert(WT_LDS <= 80 * 1024, "two workgroups per CU");
-struct WgradArgs {
-  const unsigned short *pqT, *xT;
-  float *part;
-  int nst, per;                 // stages in all, per slice
-  int D, nb, bs, njt, nkt;
-  unsigned total;
-};
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) tile_wgrad_kernel(WgradArgs a) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const unsigned id = xcd_id();
-  if (id >= a.total) return;
-  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, j = lane & 31;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // the tiles of one (slice, block) are neighbours: they share rows
-  const int kt = (int)(id % a.nkt), jt = (int)(id / a.nkt % a.njt), g = (int)(id / a.nkt / a.njt % a.nb),
-            sl = (int)(id / a.nkt / a.njt / a.nb);
-  const int D = a.D, bs = a.bs, j0 = jt * 256, k0 = kt * 128;
-  const int s_lo = sl * a.per, s_hi = s_lo + a.per < a.nst ? s_lo + a.per : a.nst;
-  const unsigned vo = (unsigned)(lane >> 2) * 64 + (unsigned)((lane & 3) ^ ((lane >> 3) & 3)) * 16;   // key: (row >> 1) & 3
-  auto load_stage = [&](int s) __attribute__((always_inline)) {
-    const size_t at = ((size_t)s * D + (size_t)g * bs) * 32;
-    const u32x4 q_rs = buf_words(a.pqT + 2 * at, (size_t)2 * bs * 64), x_rs = buf_words(a.xT + at, (size_t)bs * 64);
-    const unsigned st = lds_offset(smem) + (unsigned)(s - s_lo) % 3u * WT_STAGE;
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const int i = wv + 4 * m;
-      lds16<false>(q_rs, st + i * 1024, vo, (unsigned)(j0 + 16 * i) * 64);
-    }
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const int i = wv + 4 * m;
-      lds16<false>(x_rs, st + WT_A + i * 1024, vo, (unsigned)(k0 + 16 * i) * 64);
-    }
-  };
-  f32x16 acc[2][4];
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int n = 0; n < 4; ++n)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
-  const unsigned a_rd = (unsigned)(wv * 64 + j) * 64 + (unsigned)(hf ^ key_b(j)) * 16, b_rd = WT_A + (unsigned)j * 64 + (unsigned)(hf ^ key_b(j)) * 16;
-  const int njb = (2 * bs - j0 - wv * 64 + 31) / 32, nkb = (bs - k0 + 31) / 32;   // 32-blocks that exist
-  if (s_lo < s_hi) load_stage(s_lo);
-  if (s_lo + 1 < s_hi) load_stage(s_lo + 1);
-  for (int s = s_lo; s < s_hi; ++s) {
-    if (s + 1 < s_hi) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");   // this stage is there, the next may be under way
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    lds_barrier();
-    if (s + 2 < s_hi) load_stage(s + 2);   // (into the buffer everyone has just left)
-    if (njb <= 0) continue;
-    const unsigned char *st = smem + (unsigned)(s - s_lo) % 3u * WT_STAGE;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      f16x8 fa[2], fb[4];
-#pragma unroll
-      for (int m = 0; m < 2; ++m) fa[m] = *(const f16x8 *)(st + ((a_rd + m * 2048) ^ (ks * 32)));
-#pragma unroll
-      for (int n = 0; n < 4; ++n) fb[n] = *(const f16x8 *)(st + ((b_rd + n * 2048) ^ (ks * 32)));
-#pragma unroll
-      for (int n = 0; n < 4; ++n)
-        if (n < nkb)
-#pragma unroll
-          for (int m = 0; m < 2; ++m)
-            acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[m], fb[n], acc[m][n], 0, 0, 0);
-    }
-  }
-  float *out = a.part + ((size_t)sl * a.nb + g) * 2 * bs * bs;
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int n = 0; n < 4; ++n)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = j0 + wv * 64 + m * 32 + 8 * (r >> 2) + 4 * hf + (r & 3), col = k0 + n * 32 + j;
-        if (row < 2 * bs && col < bs) out[(size_t)row * bs + col] = acc[m][n][r];
-      }
-}
-
 // ------------------------------------------------------------------------ host side
 Instance find_instance(int bs, int var) {
   const int nct = (bs + 31) / 32;
@@ -187,7 +98,7 @@ Instance find_instance(int bs, int var) {
 int variant(const Problem &p) { return p.reset ? V_PACKED : p.merge == 2 ? V_MERGE_TANH : p.merge ? V_MERGE : V_PLAIN; }
 
 struct Plan {
-  int nct, TM, ntile, G, R, S, per, nst, njt, nkt;
+  int nct, TM, ntile, G, R, S, per, nst;
   size_t off_sc, off_partA, off_partC, off_edge, off_masks, off_rec, off_x, off_pq, off_w, off_partW, wbytes, total;
 };
 // have: bytes there are (the weight gradients take as many slices as fit); ncu: compute units
@@ -200,8 +111,6 @@ Plan make_plan(int B, int T, int D, int nb, bool packed, const Instance &in, siz
   q.G = pick_slices(units, q.ntile, in.per_cu * ncu, 16);   // (slices wait for each other: all run at once)
   q.R = ring_depth(q.G);
   q.nst = B * q.ntile * in.mt;
-  q.njt = (2 * bs + 255) / 256;
-  q.nkt = (bs + 127) / 128;
   const size_t n2 = (size_t)B * q.ntile * q.TM * D * 2;
   size_t off = 256;   // the status word
   q.off_sc = off; off += al256(SCALE_CELL_BYTES);
@@ -217,14 +126,8 @@ Plan make_plan(int B, int T, int D, int nb, bool packed, const Instance &in, siz
   q.off_rec = off + 2 * q.wbytes;
   const size_t first = 2 * q.wbytes + (q.G > 1 ? (size_t)units * q.R * q.nct * 32 * sizeof(u64) : 0);
   const size_t one = (size_t)nb * 2 * bs * bs * 4;
-  // slices of the weight gradients: two workgroups per CU, none shorter than 8 stages, as many as there is room for
-  const long long tiles = (long long)nb * q.njt * q.nkt;
-  long long S = (2 * 256 + tiles - 1) / tiles;
-  if (S > q.nst / 8) S = q.nst / 8;
-  const long long fit = have > off ? (long long)((have - off) / one) : 0;
-  if (S > fit) S = fit;
-  if (S < 1) S = 1;
-  q.per = (int)((q.nst + S - 1) / S);
+  const int S = tile_wgrad_slices(q.nst, nb, 2 * bs, bs, have > off ? (long long)((have - off) / one) : 1);
+  q.per = (q.nst + S - 1) / S;
   q.S = (q.nst + q.per - 1) / q.per;
   q.total = off + std::max(first, q.S * one);
   return q;
@@ -316,11 +219,11 @@ bool backward_tile_supported(const Problem &p, bool bf) {
   const size_t r = room(p.B, p.T, p.D, p.bs, p.merge != 0), have = p.ws_bytes > r ? p.ws_bytes - r : 0;
   return have >= make_plan(p.B, p.T, p.D, p.nb, p.reset != nullptr, in, have, compute_units()).total;
 }
-// the least it runs in, for 256 compute units; 0: not for this shape
+// what it runs best in, for 256 compute units (less makes the slices of the weight gradients fewer); 0: not for this shape
 size_t backward_tile_ws_bytes(int B, int T, int D, int nb, bool packed, bool merge) {
   if (!shape_ok(B, T, D, nb, packed)) return 0;
   const Instance in = find_instance(D / nb, packed ? V_PACKED : merge ? V_MERGE : V_PLAIN);
-  return in.kernel ? al256(make_plan(B, T, D, nb, packed, in, 0, 256).total + room(B, T, D, D / nb, merge)) : 0;
+  return in.kernel ? al256(make_plan(B, T, D, nb, packed, in, ~(size_t)0, 256).total + room(B, T, D, D / nb, merge)) : 0;
 }
 
 hipError_t launch_backward_tile(const Problem &call, hipStream_t s) {
@@ -374,21 +277,12 @@ hipError_t launch_backward_tile(const Problem &call, hipStream_t s) {
     void *args[] = {&a};
     if ((e = hipLaunchKernel(in.kernel, dim3(grid8(a.total)), dim3(in.waves * 64), args, in.lds, s)) != hipSuccess) return e;
   }
-  {
-    static std::atomic<bool> configured{false};
-    if (!configured.load()) {
-      if ((e = big_lds(tile_wgrad_kernel, WT_LDS)) != hipSuccess) return e;
-      configured.store(true);
-    }
-    KernelTimer kt("tile_wgrad_kernel", s);
-    WgradArgs w;
-    w.pqT = a.pqT; w.xT = a.xT; w.part = (float *)(ws + q.off_partW);
-    w.nst = q.nst; w.per = q.per;
-    w.D = p.D; w.nb = p.nb; w.bs = p.bs; w.njt = q.njt; w.nkt = q.nkt;
-    w.total = (unsigned)q.S * p.nb * q.njt * q.nkt;
-    hipLaunchKernelGGL(tile_wgrad_kernel, dim3(grid8(w.total)), dim3(256), WT_LDS, s, w);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
+  TileWgrad w;
+  w.A[0] = a.pqT; w.B[0] = a.xT; w.A[1] = w.B[1] = nullptr;
+  w.part = (float *)(ws + q.off_partW);
+  w.nst = q.nst; w.S = q.S; w.per = q.per;
+  w.nb = p.nb; w.ra = 2 * p.bs; w.cb = p.bs;
+  if ((e = launch_tile_wgrad(w, 1, s)) != hipSuccess) return e;
   FinishArgs f;
   f.partW = (const float *)(ws + q.off_partW);
   f.partA = a.partA; f.partC = a.partC; f.sc = sc;

@@ -78,6 +78,36 @@ def test_tiles(B, T, bs, nb, slices, how):
         assert gen.rel_err(rn.to_host(got[k]), ref[k]) < BF16, k
 
 
+@pytest.mark.parametrize("B,T,bs,nb", [(1, 16384, 256, 1), (1, 16448, 256, 1), (2, 8300, 240, 1), (3, 1000, 352, 1), (1, 2080, 512, 1),
+                                       (1, 900, 160, 3), (1, 700, 112, 1)])
+def test_weight_gradients_in_slices(B, T, bs, nb):
+    """Tiles of half and of all columns of a block (512 stages of 32 steps and more), in as many slices of the stages as the reported
+    workspace holds and as a large one does. Half-precision adjoints and inputs (11 bits): 2^-6 as above."""
+    import paper_2402_19427_amd as R
+    import torch
+    rn = runner()
+    D, act = bs * nb, "bf16"
+    inp = gen.make_inputs(B, T, D, nb, act=act, seed=T + bs, dy=True, bias=True)
+    dp, q = rn.DeviceProblem(inp, B, T, D, nb, act), f64(inp)
+    u, dy = rn.to_device(inp["u"], act), rn.to_device(inp["dy"], act)
+    y, _, _ = dp.forward(u)
+    ref = oracle.backward(q["u"], q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"], q["dy"], conv_b=q["conv_b"])
+    for room in (0, 512 << 20):
+        if room:
+            ws = torch.empty(room, dtype=torch.uint8, device="cuda:0")
+            dp.workspace = lambda shape, op: (ws, ws.numel())
+        R.rglru_timing_enable(True)
+        try:
+            got = dp.backward(u, y, dy)
+            torch.cuda.synchronize()
+            names = names_of(R)
+        finally:
+            R.rglru_timing_enable(False)
+        assert "tile_wgrad_kernel" in names
+        for k in ref:
+            assert gen.rel_err(rn.to_host(got[k]), ref[k]) < BF16, k
+
+
 @pytest.mark.parametrize("B,T,bs,nb,slices", [
     (1, 1, 128, 1, 0), (2, 33, 128, 2, 0), (1, 129, 144, 2, 0), (1, 700, 160, 2, 3), (2, 160, 176, 1, 0), (1, 191, 192, 1, 1),
     (1, 257, 208, 1, 0), (1, 3000, 256, 2, 0), (3, 319, 256, 1, 4), (1, 320, 240, 1, 0), (1, 2, 320, 4, 0), (2, 31, 384, 2, 0),
