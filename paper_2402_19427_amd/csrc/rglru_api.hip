@@ -241,11 +241,15 @@ size_t workspace_need(const rglru_shape *s, int op) {
       return gen;
     }
     case RGLRU_OP_CG_BACKWARD:
-      return std::max(cg_backward_ws_bytes(s->B, s->T, s->D, s->num_blocks),
-                      s->act_dtype == RGLRU_BF16 ? cg_backward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks) : 0);
-    case RGLRU_OP_CG_FORWARD:   // optional: the passes, or the two-pass forward of the general kernels
-      return std::max(forward_generic_ws_bytes(s->B, s->T, s->D),
-                      s->act_dtype == RGLRU_BF16 ? cg_forward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks) : 0);
+      return s->act_dtype != RGLRU_BF16 ? cg_backward_ws_bytes(s->B, s->T, s->D, s->num_blocks)
+                                        : std::max({cg_backward_ws_bytes(s->B, s->T, s->D, s->num_blocks),
+                                                    cg_backward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks),
+                                                    cg_backward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks)});
+    case RGLRU_OP_CG_FORWARD:   // optional: the tiles, the passes, or the two-pass forward of the general kernels
+      return s->act_dtype != RGLRU_BF16 ? forward_generic_ws_bytes(s->B, s->T, s->D)
+                                        : std::max({forward_generic_ws_bytes(s->B, s->T, s->D),
+                                                    cg_forward_pass_ws_bytes(s->B, s->T, s->D, s->num_blocks),
+                                                    cg_forward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks)});
     case RGLRU_OP_BACKWARD_MERGE:   // dy (+ dy_lo) between the merge adjoint and the backward, then the backward's own
       return merge_dy_bytes(s) + workspace_need(s, RGLRU_OP_BACKWARD);
     case RGLRU_OP_FORWARD_MERGE:

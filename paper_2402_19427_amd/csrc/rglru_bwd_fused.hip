@@ -126,7 +126,7 @@ Plan make_plan(int B, int T, int D, int nb, bool packed, const Instance &in, siz
   q.off_rec = off + 2 * q.wbytes;
   const size_t first = 2 * q.wbytes + (q.G > 1 ? (size_t)units * q.R * q.nct * 32 * sizeof(u64) : 0);
   const size_t one = (size_t)nb * 2 * bs * bs * 4;
-  const int S = tile_wgrad_slices(q.nst, nb, 2 * bs, bs, have > off ? (long long)((have - off) / one) : 1);
+  const int S = tile_wgrad_slices(q.nst, nb, 2 * bs, bs, 1, have > off ? (long long)((have - off) / one) : 1);
   q.per = (q.nst + S - 1) / S;
   q.S = (q.nst + q.per - 1) / q.per;
   q.total = off + std::max(first, q.S * one);

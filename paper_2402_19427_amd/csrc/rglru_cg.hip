@@ -779,6 +779,7 @@ size_t cg_backward_ws_bytes(int B, int T, int D, int nb) {   // ... + the recomp
 }
 
 hipError_t launch_cg_forward(const Problem &p, bool bf, hipStream_t s) {
+  if (bf && cg_forward_tile_supported(p)) return launch_cg_forward_tile(p, s);
   const bool fused = bf && cg_fused_ok(p);
   if (bf && !(fused && cg_fused_fills(p)) && cg_forward_pass_supported(p)) return launch_cg_forward_pass(p, s);
   if (fused) return launch_cg_fused(p, s);
@@ -820,6 +821,7 @@ hipError_t launch_cg_decode(const Problem &p, bool bf, hipStream_t s) {
 }
 
 hipError_t launch_cg_backward(const Problem &p, bool bf, hipStream_t s) {
+  if (bf && cg_backward_tile_supported(p)) return launch_cg_backward_tile(p, s);
   if (bf && cg_backward_pass_supported(p)) return launch_cg_backward_pass(p, s);
   return bf ? cg_backward_t<bf16>(p, s) : cg_backward_t<float>(p, s);
 }

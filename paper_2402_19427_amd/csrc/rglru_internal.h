@@ -135,6 +135,13 @@ hipError_t launch_cg_forward_pass(const Problem &p, hipStream_t s);
 size_t cg_backward_pass_ws_bytes(int B, int T, int D, int nb);
 bool cg_backward_pass_supported(const Problem &p);
 hipError_t launch_cg_backward_pass(const Problem &p, hipStream_t s);
+// ... and of 80 to 128 of them, tensors on the 16-byte grid: in tiles (rglru_cg_tile.hip)
+size_t cg_forward_tile_ws_bytes(int B, int T, int D, int nb);
+bool cg_forward_tile_supported(const Problem &p);
+hipError_t launch_cg_forward_tile(const Problem &p, hipStream_t s);
+size_t cg_backward_tile_ws_bytes(int B, int T, int D, int nb);
+bool cg_backward_tile_supported(const Problem &p);
+hipError_t launch_cg_backward_tile(const Problem &p, hipStream_t s);
 
 // Forward for fp32 storage and blocks of a multiple of 16 channels, parallel over time (rglru_f32.hip): y
 // or the merge, hT, the ring; needs scratch

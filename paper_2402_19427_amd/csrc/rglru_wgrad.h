@@ -14,7 +14,7 @@ struct TileWgrad {
   int nb, ra, cb;                      // blocks; channels of a block on either side (multiples of 16)
 };
 // the number of slices the chip is filled best with, at most `fit`
-int tile_wgrad_slices(int nst, int nb, int ra, int cb, long long fit);
+int tile_wgrad_slices(int nst, int nb, int ra, int cb, int parts, long long fit);
 // parts 1: half precision, one product; 2: bf16 high and low parts, three products
 hipError_t launch_tile_wgrad(const TileWgrad &w, int parts, hipStream_t s);
 

@@ -142,9 +142,9 @@ struct Shape {
 // Tiles of all columns up to 256, but of half of 224 or 256 where there are few stages: their workgroups start and end in 9 us
 // instead of 12, and half as many slices keep the chip as busy. us, halves : whole, with the final sums: 10 blocks of 256, 2 stages 14.5 :
 // 17, 64 24 : 28, 512 78 : 83, 1024 125 : 127, 2048 217 : 209; 16 of 512 32 stages 45 : 52, 128 104 : 102, 256 188 : 171.
-Shape shape(int nst, int ra, int cb) {
+Shape shape(int nst, int ra, int cb, int parts) {
   const int blocks = (cb + 31) / 32, whole = (blocks + 7) / 8;
-  const bool half = (blocks + whole - 1) / whole >= 7 && nst <= (whole == 1 ? 512 : 64);
+  const bool half = (blocks + whole - 1) / whole >= 7 && (parts == 2 || nst <= (whole == 1 ? 512 : 64));
   Shape q;
   q.njt = (ra + 255) / 256;
   q.nkt = half ? 2 * whole : whole;
@@ -162,6 +162,16 @@ hipError_t launch(const WgradArgs &a, hipStream_t s) {
   hipLaunchKernelGGL((tile_wgrad_kernel<PARTS, N>), dim3(grid8(a.total)), dim3(256), (Wg<PARTS, N>::LDS), s, a);
   return hipGetLastError();
 }
+template <int PARTS>
+hipError_t launch_n(int n, const WgradArgs &a, hipStream_t s) {
+  switch (n) {
+    case 4: return launch<PARTS, 4>(a, s);
+    case 5: return launch<PARTS, 5>(a, s);
+    case 6: return launch<PARTS, 6>(a, s);
+  }
+  if constexpr (PARTS == 1) return n == 7 ? launch<1, 7>(a, s) : launch<1, 8>(a, s);
+  return hipErrorInvalidValue;   // (never: halves, above)
+}
 
 }  // namespace
 
@@ -170,8 +180,8 @@ hipError_t launch(const WgradArgs &a, hipStream_t s) {
 // partial sums 0.5 us more in the final sums: as many
 // slices as make the time of all rounds least. us at 4, 8, 12 slices: B 8 T 2048, 10 blocks of 256 120, 76, 70; 16 of 160 92, 72, 82 (12:
 // a second round of workgroups).
-int tile_wgrad_slices(int nst, int nb, int ra, int cb, long long fit) {
-  const Shape q = shape(nst, ra, cb);
+int tile_wgrad_slices(int nst, int nb, int ra, int cb, int parts, long long fit) {
+  const Shape q = shape(nst, ra, cb, parts);
   const long long tiles = (long long)nb * q.njt * q.nkt, sums = ((long long)nb * ra * cb * 4) >> 10;
   long long best = 1, cost = -1;
   for (long long S = 1; S <= 64 && S <= fit && S <= nst; ++S) {
@@ -182,19 +192,13 @@ int tile_wgrad_slices(int nst, int nb, int ra, int cb, long long fit) {
 }
 
 hipError_t launch_tile_wgrad(const TileWgrad &w, int parts, hipStream_t s) {
-  const Shape q = shape(w.nst, w.ra, w.cb);
+  const Shape q = shape(w.nst, w.ra, w.cb, parts);
   WgradArgs a;
   a.w = w;
   a.njt = q.njt; a.nkt = q.nkt;
   a.total = (unsigned)w.S * w.nb * q.njt * q.nkt;
   KernelTimer kt("tile_wgrad_kernel", s);
-  switch (q.n) {
-    case 4: return launch<1, 4>(a, s);
-    case 5: return launch<1, 5>(a, s);
-    case 6: return launch<1, 6>(a, s);
-    case 7: return launch<1, 7>(a, s);
-    default: return launch<1, 8>(a, s);
-  }
+  return parts == 1 ? launch_n<1>(q.n, a, s) : launch_n<2>(q.n, a, s);
 }
 
 }  // namespace rglru

@@ -135,6 +135,44 @@ def test_cg_at_the_paper_s_block_shape_full_width():
         assert errs[k] < TOL[act], (k, errs)
 
 
+@pytest.mark.parametrize("B,T,hs,nb", [
+    (1, 1, 128, 1), (1, 31, 80, 2), (2, 33, 128, 1),    # (the backward only: a sequence of up to 64 steps has the fused forward)
+    (1, 65, 128, 2), (3, 96, 96, 2), (1, 257, 80, 4),   # a window per tile; a last tile of one step
+    (5, 300, 128, 20), (9, 165, 112, 20),               # windows of two and three tiles, the last one short
+    (130, 70, 96, 4)])                                  # one window: nothing in front of it
+@pytest.mark.parametrize("conv", [True, False])
+def test_cg_tiles(B, T, hs, nb, conv):
+    """The kernels in tiles: tile and window edges, blocks that leave part of a wave without channels, the last state in the place of
+    the first one, the reverse state likewise. 2^-6 as for the other bf16 kernels (8-bit results; 16 bits and more in between)."""
+    import paper_2402_19427_amd as R
+    import torch
+    rn = runner()
+    D, act, pos0 = 2 * hs * nb, "bf16", 5
+    inp = gen.make_cg_inputs(B, T, D, nb, act=act, seed=T + hs, h0=True, state=True, bias=True, dy=True)
+    dp = rn.CgDeviceProblem(inp, B, T, D, nb, act, conv=conv)
+    u, dy, state = rn.to_device(inp["u"], act), rn.to_device(inp["dy"], act), rn.to_device(inp["h0"], "f32")
+    ring = rn.to_device(gen.ring_from_chrono(inp["state"], pos0), act) if conv else None
+    q = f64(inp)
+    kw = dict(conv_w=q["conv_w"], conv_b=q["conv_b"], state_in=q["state"]) if conv else {}
+    want = oracle.cg_forward(q["u"], *params(q), h0=q["h0"], **kw)
+    ref = oracle.cg_backward(q["u"], *params(q), q["dy"], h0=q["h0"], dhT=q["dhT"], **kw)
+    n = max(R.rglru_workspace_bytes(dp.shape(), op) for op in (R.OP_CG_FORWARD, R.OP_CG_BACKWARD))
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+    y, names = torch.empty_like(u), []
+    R.rglru_timing_enable(True)
+    try:
+        g = dp.backward(u, dy, h0=state, state_in=ring, pos0=pos0, dhT=rn.to_device(inp["dhT"], "f32"))
+        R.rglru_cg_forward(dp.shape(), dp.params, u, state, ring, pos0, y, state, None, ws, n, None)
+        torch.cuda.synchronize()
+        names = [R.rglru_timing_get(i)[0] for i in range(R.rglru_timing_count())]
+    finally:
+        R.rglru_timing_enable(False)
+    assert "cg_bwd_tile_kernel" in names and names.count("cg_tile_prep_kernel") == (2 if T > 64 else 1), names
+    assert gen.rel_err(rn.to_host(y), want[0]) < 2.0 ** -6 and gen.rel_err(rn.to_host(state), want[1]) < 2.0 ** -6
+    for k in ref:
+        assert gen.rel_err(rn.to_host(g[k]), ref[k]) < 2.0 ** -6, k
+
+
 @pytest.mark.parametrize("hs,nb,T", [(48, 2, 40), (128, 2, 70)])
 def test_weights_past_half_precision(hs, nb, T):
     """Finite weights stop at 65504 in the products: where they meet inputs of zero, nothing comes of them (an infinity would be a
