@@ -21,34 +21,50 @@ struct CgPrepArgs {
 __global__ void __launch_bounds__(256) cg_tile_prep_kernel(CgPrepArgs a) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   const int nks = 4 * a.nct, hs = a.hs;
-  const size_t per = (size_t)a.nb * a.nct * nks * 2 * 64;
-  if (i >= (a.wd ? 2 * per : per)) return;
-  const bool tr = i >= per;
+  const size_t per = (size_t)a.nb * a.nct * nks * 2 * 64, wn = (size_t)hs * 2 * hs;
+  const bool tr = i >= per;   // (then a thread forms four lanes, from eight rows)
+  if (i >= (a.wd ? per + per / 4 : per)) return;
   size_t f = tr ? i - per : i;
-  const int lane = (int)(f & 63);
-  f >>= 6;
+  const int q = (int)(tr ? f & 15 : f & 63);
+  f >>= tr ? 4 : 6;
   const int two = (int)(f & 1), ks = (int)((f >> 1) % nks), wv = (int)((f >> 1) / nks % a.nct), g = (int)((f >> 1) / nks / a.nct);
-  const int c = wv * 32 + (lane & 31), k = (ks >> 2) * 32 + (ks & 1) * 16 + (lane >> 5) * 8, mid = (ks >> 1) & 1;
-  u32x4 o = {0u, 0u, 0u, 0u};
-  if (c < hs && k < hs) {
-    const size_t wn = (size_t)hs * 2 * hs;
-    unsigned short v[8];
+  const int mid = (ks >> 1) & 1, k0 = (ks >> 2) * 32 + (ks & 1) * 16;
+  if (!tr) {
+    const int c = wv * 32 + (q & 31), k = k0 + (q >> 5) * 8;
+    u32x4 o = {0u, 0u, 0u, 0u};
+    if (c < hs && k < hs) {
+      const u32x4 v = *(const u32x4_at2 *)(a.W[two] + g * wn + (size_t)c * 2 * hs + mid * hs + k);
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      v[e] = tr ? a.W[mid][g * wn + (size_t)(k + e) * 2 * hs + two * hs + c] : a.W[two][g * wn + (size_t)c * 2 * hs + mid * hs + k + e];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      o[e] = tr ? (unsigned)v[2 * e] | (unsigned)v[2 * e + 1] << 16
-                : pack_sat(__uint_as_float((unsigned)v[2 * e] << 16), __uint_as_float((unsigned)v[2 * e + 1] << 16));
+      for (int e = 0; e < 4; ++e) o[e] = pack_sat(bf_lo(v[e]), bf_hi(v[e]));
+    }
+    a.wg[i] = o;
+    return;
   }
-  (tr ? a.wd : a.wg)[tr ? i - per : i] = o;
+  const int c = wv * 32 + (q & 7) * 4, k = k0 + (q >> 3) * 8;
+  u32x2 v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = u32x2{0u, 0u};
+  if (c < hs && k < hs)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = *(const u32x2_at2 *)(a.W[mid] + g * wn + (size_t)(k + e) * 2 * hs + two * hs + c);
+  u32x4 *to = a.wd + f * 64 + (q >> 3) * 32 + (q & 7) * 4;
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    u32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const unsigned x = v[2 * e][n >> 1], y = v[2 * e + 1][n >> 1];
+      o[e] = n & 1 ? x >> 16 | (y & 0xffff0000u) : (x & 0xffffu) | y << 16;
+    }
+    to[n] = o;
+  }
 }
 hipError_t launch_prep(const Problem &p, int nct, u32x4 *wg, u32x4 *wd, hipStream_t s) {
   KernelTimer kt("cg_tile_prep_kernel", s);
   CgPrepArgs a;
   a.W[0] = (const unsigned short *)p.W_a; a.W[1] = (const unsigned short *)p.W_x;
   a.wg = wg; a.wd = wd; a.nb = p.nb; a.hs = p.bs; a.nct = nct;
-  const size_t n = (size_t)p.nb * nct * nct * 8 * 64 * (wd ? 2 : 1);
+  const size_t frags = (size_t)p.nb * nct * nct * 8 * 64, n = wd ? frags + frags / 4 : frags;
   hipLaunchKernelGGL(cg_tile_prep_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
