@@ -203,14 +203,14 @@ size_t least_backward_bytes(const rglru_shape *s) {
   return backward_generic_ws_bytes(s->B, s->T, s->D, s->num_blocks);
 }
 
-// What the fused forward of a shape takes: the least a call has to bring. For gate blocks of 128 - 240 channels the
-// tiles may take more (all weights in half precision, not those of one gate), which the size query asks for.
+// What the fused forward of a shape takes: the least a call has to bring. For gate blocks of 128 - 240 channels, and 256 in short
+// sequences, the tiles may take more (all weights in half precision, not those of one gate), which the size query asks for.
 size_t fused_forward_bytes(const rglru_shape *s, bool packed) {
   return forward_mfma_ws_bytes(s->B, s->T, s->D, s->num_blocks) + (packed ? forward_mfma_mask_bytes(s->B, s->T) : 0);
 }
 size_t forward_bytes(const rglru_shape *s, bool packed) {
   const size_t n = fused_forward_bytes(s, packed);
-  if (s->D / s->num_blocks == 256) return n;
+  if (s->D / s->num_blocks == 256 && (s->T <= 8 || s->T > 256)) return n;   // (a quarter of a tile: not worth a second gate's weights)
   return std::max(n, forward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, packed, !packed, n));
 }
 size_t workspace_need(const rglru_shape *s, int op) {

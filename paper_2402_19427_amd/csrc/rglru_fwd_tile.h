@@ -423,6 +423,7 @@ Instance fwd_pick(int var) {
 }
 Instance find_fwd_instance_a(int nct, int var);   // 4 - 6
 Instance find_fwd_instance_b(int nct, int var);   // 7, 8
+Instance find_fwd_short_instance(int nct, int var);   // 7, 8: tiles of 32 steps
 Instance find_fwd_instance_c(int nct, int var);   // 9 - 12
 Instance find_fwd_instance_d(int nct, int var);   // 13 - 15
 

@@ -59,8 +59,8 @@ bool shape_ok(int B, int T, int D, int bs, bool packed) {
 // 1.652e-3 being that of the exact y in bf16; the passes' 1.701e-3), but the bound held on dW_a at Lambda = -3, 4e-2, is below
 // what the storage rounding of y supports: the exact y in bf16 is 4.5e-2 off in one draw of six, where the passes' y is not.
 // Blocks it takes, 128 channels: everywhere (B 1 T 16 10 : 15, B 8 T 2048 82 : 146). 144 and up:
-// - not up to four tiles (160 channels, T 64: 15.7 : 14.3 and 18.4 : 14.6 with the merge; 256, T 200 with the merge
-//   23 : 20), where the workgroups' own start is most of the time and they have no second tile to hide it behind.
+// - up to four tiles (of 32 steps, up to 192 channels): up to 256 units (160, 16 blocks: B 1 T 20 11.2 : 16.3, T 128 12.8 : 16.9, with the
+//   merge 14.8 : 16.8, B 16 T 128 25 : 30; 192, 10 blocks, B 16 T 128 25 : 32). Tiles of 64 steps (from 208 channels on): see choose.
 // What else decides is how often a workgroup of either kernel goes round (a round is a tile of each of its slices) and what the
 // preparation costs: the tiles' converts both gates' weights of all blocks, the fused kernel's one gate's, 1 - 5 us more by the
 // number of blocks. `half`: the tiles go round at most half as often.
@@ -84,7 +84,7 @@ bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
   const bool merge = var == V_MERGE || var == V_MERGE_TANH;
   const int steps = 32 * in.mt;
   const long long units = (long long)B * nb;
-  if (T <= 4 * steps) return false;
+  if (T <= 4 * steps) return in.mt == 1 && units <= 256;
   // (for 256 compute units on either side: the same rule where no card is visible)
   const auto rounds = [&](int step, int workgroups, int most) {
     const int n = (T + step - 1) / step, G = pick_slices(B * nb, n, workgroups, most);
@@ -106,9 +106,33 @@ bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
   if (merge) return half || units <= 16 || (nb <= 16 && T < 2048);
   return units <= 28 || nb <= 8 || units * T < 65536 || units * T >= 300000;
 }
+// The instance a call runs on; kernel null: not in tiles. Blocks of 208 - 256 channels have tiles of 64 steps, whose weights take half the way
+// from L2 per step, and of 32, of which there are twice as many to fill the chip. What decides is how often a workgroup goes round. us, tiles of
+// 32 : before (fused up to T 256, where the tiles' start is most of the time and those of 64 are no gain):
+// - up to T 256, one round: B 1, 10 blocks of 256 T 20 13.3 : 19.7, T 128 14.7 : 20.7, T 256 15.1 : 21.8, with the merge 17.4 : 22.4; B 11 T 128
+//   24 : 29; 16 blocks B 16 T 64 24.7 : 25.9; 10 of 208 B 1 T 256 15.6 : 18.9.
+// - two rounds with the merge, or of three slices and more: B 5 T 256 16 blocks 30 : 33, with the merge 35 : 36, B 16 T 100 10 blocks 29 : 31;
+//   two slices 33 : 31 (B 11 T 100, 16 blocks), 35 : 33 with B 16. Not from three rounds on (10 blocks, B 16 T 256 44 : 43).
+// - past T 256, where tiles are the faster forward at all: in one round of a workgroup per compute unit (B 1, 10 blocks, T 777 with the merge
+//   20.8 : 24.9 in tiles of 64; T 500 17.2 : 17.9), or in one round where those of 64 take two (B 2 T 777 25.5 : 29.7; but B 2 T 500, one round of
+//   either, 23 : 20).
+Instance choose(int B, int T, int nb, int bs, int var) {
+  const Instance none = {nullptr, 0, 0, 0, 0}, in = find_instance(bs, var);
+  if (!in.kernel) return none;
+  if (in.mt == 1 || bs < 208 || bs > 256) return worth(B, T, nb, bs, var, in) ? in : none;
+  const Instance one = find_fwd_short_instance(in.waves, var);
+  const int n1 = (T + 31) / 32, n2 = (T + 63) / 64, G1 = pick_slices(B * nb, n1, one.per_cu * 256, FWD_TILE_SLICES),
+            G2 = pick_slices(B * nb, n2, in.per_cu * 256, FWD_TILE_SLICES), r1 = (n1 + G1 - 1) / G1, r2 = (n2 + G2 - 1) / G2;
+  if (T <= 256) return (long long)B * nb <= 256 && (r1 == 1 || (r1 == 2 && (var == V_MERGE || var == V_MERGE_TANH || G1 >= 3))) ? one : none;
+  if (!worth(B, T, nb, bs, var, in)) return none;
+  return r1 == 1 && ((long long)B * nb * n1 <= 256 || r2 > 1) ? one : in;
+}
+// Of short calls the whole plan is asked for: a few KB of records and the second gate's weights.
+constexpr int SHORT = 256;
 size_t bytes(int B, int T, int nb, int bs, int var, size_t room) {
-  const Instance in = find_instance(bs, var);
-  if (!in.kernel || !worth(B, T, nb, bs, var, in)) return 0;
+  const Instance in = choose(B, T, nb, bs, var);
+  if (!in.kernel) return 0;
+  if (T <= SHORT) room = ~(size_t)0;
   // (a size asked for where no card is visible must do on one: the whole chip's slices are the most there can be)
   return std::max(make_plan(B, T, nb, bs, var == V_PACKED, in, 256, room).total,
                   make_plan(B, T, nb, bs, var == V_PACKED, in, compute_units(), room).total);
@@ -131,8 +155,8 @@ bool forward_tile_supported(const Problem &p, bool bf, size_t asked) {
 }
 
 hipError_t launch_forward_tile(const Problem &p, size_t asked, hipStream_t s) {
-  const Instance in = find_instance(p.bs, variant(p));
-  const Plan q = make_plan(p.B, p.T, p.nb, p.bs, p.reset, in, compute_units(), asked);
+  const Instance in = choose(p.B, p.T, p.nb, p.bs, variant(p));
+  const Plan q = make_plan(p.B, p.T, p.nb, p.bs, p.reset, in, compute_units(), p.T <= SHORT ? ~(size_t)0 : asked);
   char *ws = (char *)p.ws;
   hipError_t e;
   if ((e = configure(in)) != hipSuccess) return e;

@@ -345,6 +345,49 @@ def test_weights_past_half_precision(bs, nb, T):
             assert gen.rel_err(a[..., at], b[..., at]) < BF16, k
 
 
+@pytest.mark.parametrize("B,T,bs,nb,how", [
+    (1, 9, 256, 2, "plain"), (2, 20, 256, 1, "plain"), (3, 32, 160, 2, "merge"), (1, 33, 256, 1, "packed"), (2, 64, 224, 1, "tanh"),
+    (1, 100, 192, 2, "packed"), (3, 128, 144, 1, "plain"), (1, 255, 208, 2, "merge"), (2, 256, 256, 2, "packed"), (1, 257, 256, 2, "plain"),
+    (130, 40, 256, 1, "merge"), (1, 800, 240, 2, "merge")])
+def test_short_forward(B, T, bs, nb, how):
+    """Short sequences run in tiles of 32 steps in the workspace that is asked for, and on the fused kernel in the least it takes (no
+    records where a sequence is one tile: the status word and one gate's weights)."""
+    import torch
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D, act, pos0 = bs * nb, "bf16", 9
+    inp = gen.make_inputs(B, T, D, nb, act=act, seed=T + bs, h0=True, state=True, bias=True)
+    dp, q = rn.DeviceProblem(inp, B, T, D, nb, act), f64(inp)
+    u, h0 = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32")
+    ring = rn.to_device(gen.ring_from_chrono(inp["state"], pos0), act)
+    br = gen.make_branch(B, T, D, act=act, seed=T)
+    reset = gen.make_resets(B, T, seed=bs, mean_len=20) if how == "packed" else None
+    kw = dict(conv_b=q["conv_b"], h0=q["h0"], state_in=q["state"])
+    want = oracle.forward(q["u"], q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"], reset=reset, **kw)
+    dev = dict(h0=h0, state_in=ring, pos0=pos0)
+    for least in (False, True) if how == "plain" and T <= 32 else (False,):
+        if least:
+            ws = torch.empty(256 + nb * 256 * 256 * 2, dtype=torch.uint8, device="cuda:0")
+            dp.workspace = lambda shape, op: (ws, ws.numel())
+        R.rglru_timing_enable(True)
+        try:
+            if how == "packed":
+                y, hT, st = dp.forward_packed(u, torch.from_numpy(reset).cuda(), **dev)
+            elif how == "plain":
+                y, hT, st = dp.forward(u, **dev)
+            else:
+                out, y, hT, st = dp.forward_merge(u, rn.to_device(br, act), flags=R.MERGE_GELU_TANH if how == "tanh" else 0, **dev)
+                ref = oracle.merge(want[0], br, approx=how == "tanh")
+                assert gen.rel_err(rn.to_host(out), ref) < BF16
+            torch.cuda.synchronize()
+            names = names_of(R)
+        finally:
+            R.rglru_timing_enable(False)
+        assert ("fwd_tile_kernel" in names) == (not least), names
+        assert gen.rel_err(rn.to_host(y), want[0]) < BF16 and gen.rel_err(rn.to_host(hT), want[1]) < BF16
+        np.testing.assert_array_equal(gen.chrono_from_ring(rn.to_host(st), pos0 + T), want[2])
+
+
 @pytest.mark.parametrize("B,T,bs,nb,merge,tiles", [
     (2, 1400, 256, 16, False, True), (2, 2048, 256, 16, False, False), (3, 2048, 256, 10, False, True),   # 29 - 32 units: not in between
     (1, 512, 256, 16, False, True), (1, 512, 256, 16, True, False), (1, 640, 256, 16, True, True),        # as many rounds, half as many
