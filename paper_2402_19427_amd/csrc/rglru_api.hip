@@ -254,8 +254,10 @@ size_t workspace_need(const rglru_shape *s, int op) {
       return merge_dy_bytes(s) + workspace_need(s, RGLRU_OP_BACKWARD);
     case RGLRU_OP_FORWARD_MERGE:
     case RGLRU_OP_FORWARD:
-      if (s->act_dtype == RGLRU_BF16 && forward_mfma_block(s->D / s->num_blocks) && s->T >= 1)
-        return forward_bytes(s, false);
+      if (s->act_dtype == RGLRU_BF16 && forward_mfma_block(s->D / s->num_blocks) && s->T >= 1) {
+        const size_t n = forward_bytes(s, false);   // (256 channels, one workgroup per sequence and block: the merge in tiles takes both gates' weights)
+        return op == RGLRU_OP_FORWARD ? n : std::max(n, forward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, false, true, n));
+      }
       if (s->act_dtype == RGLRU_BF16 && forward_wide_block(s->D / s->num_blocks) && s->T >= 1 &&
           s->D % 256 == 0 && (size_t)s->B * s->T * s->D * 2 < ((size_t)1 << 31))
         return forward_wide_ws_bytes(s->B, s->T, s->D, s->num_blocks);

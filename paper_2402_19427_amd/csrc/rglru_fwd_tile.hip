@@ -100,6 +100,16 @@ bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
     if (units <= 64) return bs == 192 || T <= 256;
     return merge && (half || (bs == 192 && units > 128));
   }
+  // More units of 256 channels, up to 16 blocks (call times, tiles : fused): where the fused kernel goes in more than 4 slices, too (40 units T 300
+  // 20 : 27, T 1024 38 : 43, T 4096 107 : 112; 50 units T 2048 72 : 77), with the merge only up to 640 steps (T 300 25 : 29, T 600 38 : 40, T 1024
+  // 61 : 56); without it also in two slices that leave a fifth of the chip idle (100 units T 600 52 : 56, T 2048 139 : 142) and in short
+  // sequences (80 units T 300 30 : 35, T 600 45 : 46, T 1024 63 : 61; 128 units T 300 37 : 39, T 2048 159 : 149). With the merge and one workgroup per
+  // unit up to 216 of them, where the fused kernel's epilogue costs it most (130 units T 1024 163 : 184, 208 units T 2048 333 : 354; 256 units
+  // 368 : 368).
+  if (bs == 256 && units > 32 && nb <= 16) {
+    if (merge) return (units <= 51 && T <= 640) || (units > 128 && units <= 216);
+    return units <= 51 || (units > 85 && units <= 100) || (units <= 128 && T <= 640);
+  }
   if (units > (merge ? 24 : 32) || nb > 24) return false;
   if (nb > (bs == 256 && !merge ? 16 : 12) && own >= fused) return false;
   if (bs < 240) return true;

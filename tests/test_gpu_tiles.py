@@ -388,6 +388,37 @@ def test_short_forward(B, T, bs, nb, how):
         np.testing.assert_array_equal(gen.chrono_from_ring(rn.to_host(st), pos0 + T), want[2])
 
 
+@pytest.mark.parametrize("B,T,nb,merge,tiles", [
+    (5, 300, 10, False, True), (6, 2000, 10, False, False), (10, 700, 10, False, True), (8, 640, 16, False, True), (8, 700, 16, False, False),
+    (4, 640, 10, True, True), (4, 700, 10, True, False), (13, 300, 10, True, True), (14, 300, 16, True, False)])
+def test_forward_of_many_units_takes_the_faster_kernel(B, T, nb, merge, tiles):
+    """Either side of the rule for 33 units of 256 channels and more."""
+    import torch
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D, act = 256 * nb, "bf16"
+    inp = gen.make_inputs(1, T, D, nb, act=act, seed=T + nb, bias=True)
+    dp, q = rn.DeviceProblem(inp, B, T, D, nb, act), f64(inp)
+    u = rn.to_device(inp["u"], act).expand(B, T, D).contiguous()
+    R.rglru_timing_enable(True)
+    try:
+        if merge:
+            br = gen.make_branch(1, T, D, act=act, seed=T)
+            out, y, _, _ = dp.forward_merge(u, rn.to_device(br, act).expand(B, T, D).contiguous())
+        else:
+            y, _, _ = dp.forward(u)
+        torch.cuda.synchronize()
+        names = names_of(R)
+    finally:
+        R.rglru_timing_enable(False)
+    assert ("fwd_tile_kernel" in names) == tiles, names
+    want = oracle.forward(q["u"], q["W_a"], q["W_x"], q["b_a"], q["b_x"], q["Lambda"], q["conv_w"], conv_b=q["conv_b"])[0]
+    assert torch.equal(y, y[:1].expand(B, T, D))
+    assert gen.rel_err(rn.to_host(y[:1]), want) < BF16
+    if merge:
+        assert gen.rel_err(rn.to_host(out[-1:]), oracle.merge(want, br)) < BF16
+
+
 @pytest.mark.parametrize("B,T,bs,nb,merge,tiles", [
     (2, 1400, 256, 16, False, True), (2, 2048, 256, 16, False, False), (3, 2048, 256, 10, False, True),   # 29 - 32 units: not in between
     (1, 512, 256, 16, False, True), (1, 512, 256, 16, True, False), (1, 640, 256, 16, True, True),        # as many rounds, half as many
