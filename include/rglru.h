@@ -337,8 +337,8 @@ typedef struct rglru_cg_param_grads {
  * the appendix's equations with real and imaginary parts as independent variables; it also
  * returns dtheta; it takes no y: the gradient of the decay multiplies the state's adjoint by
  * conj(h~_{t-1}), which needs more than the 8 bits of a bf16 y, so the backward recomputes the
- * states in fp32 into its workspace). They run on shape-generic kernels (fp32 arithmetic for either storage
- * type); no kernel waits on another. The forward's workspace is optional (NULL, or
+ * states in fp32 into its workspace). They run on shape-generic kernels in fp32 arithmetic, in bf16 storage also
+ * on the matrix cores (blocks of a multiple of 16); no kernel waits on another. The forward's workspace is optional (NULL, or
  * rglru_workspace_bytes(shape, RGLRU_OP_CG_FORWARD) bytes: with it the forward runs in two passes
  * parallel over time, without it in one pass, a workgroup per (sequence, gate block)); the decode
  * step needs none; the backward needs rglru_workspace_bytes(shape, RGLRU_OP_CG_BACKWARD) bytes.

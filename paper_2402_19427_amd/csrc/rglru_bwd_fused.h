@@ -12,7 +12,7 @@
 //   S dx = S dxd + [S dp | S dq] [W_a | W_x]      matrix cores
 //   du and the tap sums, the Conv1D's adjoint
 // so that logits, dxd and dx never leave the registers; what the weight gradients need (x, S dp, S dq)
-// leaves as it lies in LDS, time fastest, which is what they contract over.
+// leaves from registers in the order of their matrix fragments (rglru_wgrad.h).
 // B 16 T 4096, 16 blocks of 256 channels: 1.2 ms for what took two kernels 1.65 ms (gates and adjoints 1.12, products
 // and Conv1D 0.54), 1.68 GB read and 2.15 GB written, which is what goes in and out, 3.9 and 2.3 GB before. Bound by the
 // vector unit (busy 60 % of the time: some 60 instructions per element, 10 of them transcendental) and what two waves
