@@ -207,8 +207,10 @@ int rglru_forward(const rglru_shape *shape, const rglru_params *params, const vo
  *   Arguments, results and error codes: as rglru_forward (same kernels, same results bit for bit).
  *   RGLRU_ERR_WORKSPACE if rglru_workspace_bytes(shape, RGLRU_OP_FORWARD) exceeds
  *   RGLRU_STATIC_SCRATCH_BYTES (the five workloads this library is tuned for need 2 - 9 MB);
- *   nothing is launched then. In fp32 storage sizes up to a tenth above that run too, in two pieces
- *   of the time axis (sums in another order).
+ *   nothing is launched then. Two kinds of shape run up to some way above that, with results that may differ from
+ *   rglru_forward's in the last bits: fp32 storage up to a tenth above, in two pieces of the time axis (sums in
+ *   another order), and bf16 storage in 110 gate blocks and more of 128 to 240 channels where the fused kernel's scratch fits
+ *   and that of the tiles, which rglru_forward takes, does not.
  * All calls on one GPU share that GPU's array: two calls that overlap in time on the same GPU
  * (different streams or threads) race on it - serialise them, or give the overlapping ones a
  * workspace of their own through rglru_forward. The array keeps the last call's contents; the

@@ -210,8 +210,16 @@ size_t fused_forward_bytes(const rglru_shape *s, bool packed) {
 }
 size_t forward_bytes(const rglru_shape *s, bool packed) {
   const size_t n = fused_forward_bytes(s, packed);
-  if (s->D / s->num_blocks == 256 && (s->T <= 8 || s->T > 256)) return n;   // (a quarter of a tile: not worth a second gate's weights)
-  return std::max(n, forward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, packed, !packed, n));
+  const int bs = s->D / s->num_blocks;
+  if (bs == 256 && (s->T <= 8 || s->T > 256)) return n;   // (a quarter of a tile: not worth a second gate's weights)
+  size_t tile = forward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, packed, !packed, n);
+  // Short sequences: rglru_forward_static promises the bits of rglru_forward, so tiles that its array does not hold are not asked
+  // for where it holds what the fused kernel takes (256 channels: from 64 blocks on).
+  if (!packed && tile > RGLRU_STATIC_SCRATCH_BYTES && n <= RGLRU_STATIC_SCRATCH_BYTES && s->T <= (bs >= 208 ? 256 : bs > 128 ? 128 : 0)) {
+    tile = forward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, false, false, n);
+    if (tile > RGLRU_STATIC_SCRATCH_BYTES) tile = 0;
+  }
+  return std::max(n, tile);
 }
 size_t workspace_need(const rglru_shape *s, int op) {
   switch (op) {
@@ -255,7 +263,7 @@ size_t workspace_need(const rglru_shape *s, int op) {
     case RGLRU_OP_FORWARD_MERGE:
     case RGLRU_OP_FORWARD:
       if (s->act_dtype == RGLRU_BF16 && forward_mfma_block(s->D / s->num_blocks) && s->T >= 1) {
-        const size_t n = forward_bytes(s, false);   // (256 channels, one workgroup per sequence and block: the merge in tiles takes both gates' weights)
+        const size_t n = forward_bytes(s, false);   // (the merge has no static call; 256 channels, one workgroup per sequence and block: its tiles take both gates' weights)
         return op == RGLRU_OP_FORWARD ? n : std::max(n, forward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, false, true, n));
       }
       if (s->act_dtype == RGLRU_BF16 && forward_wide_block(s->D / s->num_blocks) && s->T >= 1 &&

@@ -49,7 +49,8 @@ extern "C" int rglru_forward_static(const rglru_shape *shape, const rglru_params
   // fp32 storage: the forward parallel over time takes as many steps at a time as its scratch holds, so
   // the limit is what the general kernels ask for
   if (need > 0 && shape->act_dtype == RGLRU_F32) need = rglru::forward_generic_ws_bytes(shape->B, shape->T, shape->D);
-  // (and gate blocks of 128 - 240 channels go back to the kernels that take less, where the array cannot hold the tiles')
+  // (and gate blocks of 128 - 192 channels in more than 128 steps, 128 in any number, go back to the fused kernel where the array cannot hold
+  // the tiles', 110 blocks and more: results may differ from rglru_forward's in the last bits)
   if (need > SCRATCH_BYTES) need = rglru::forward_least_bytes(shape);
   if (need > SCRATCH_BYTES) {
     rglru::set_last_error("rglru_forward_static: this shape needs %zu bytes of scratch, the static array holds %zu "

@@ -39,6 +39,12 @@ def test_static_scratch_forward_equals_the_workspace_call_twice_in_a_row():
     assert np.isfinite(y1).all() and np.isfinite(y2).all()
 
 
+@pytest.mark.parametrize("B,T,bs,nb", [(1, 20, 256, 64), (1, 96, 256, 64), (2, 9, 256, 80), (1, 64, 240, 64), (1, 33, 144, 176)])
+def test_static_scratch_forward_of_short_sequences_in_many_blocks(B, T, bs, nb):
+    """The weights of both gates do not fit the array, those of one do: the same kernels all the same."""
+    assert np.isfinite(run_both(B, T, bs * nb, nb, seed=T + nb)).all()
+
+
 def test_static_scratch_forward_refuses_shapes_beyond_its_array():
     import paper_2402_19427_amd as R
     # 64 blocks of 256 channels in 4 time slices: 8 MiB of records + 8 MiB of weights + the status word
