@@ -59,8 +59,7 @@ bool shape_ok(int B, int T, int D, int bs, bool packed) {
 // 1.652e-3 being that of the exact y in bf16; the passes' 1.701e-3), but the bound held on dW_a at Lambda = -3, 4e-2, is below
 // what the storage rounding of y supports: the exact y in bf16 is 4.5e-2 off in one draw of six, where the passes' y is not.
 // Blocks it takes, 128 channels: everywhere (B 1 T 16 10 : 15, B 8 T 2048 82 : 146). 144 and up:
-// - up to four tiles (of 32 steps, up to 192 channels): up to 256 units (160, 16 blocks: B 1 T 20 11.2 : 16.3, T 128 12.8 : 16.9, with the
-//   merge 14.8 : 16.8, B 16 T 128 25 : 30; 192, 10 blocks, B 16 T 128 25 : 32). Tiles of 64 steps (from 208 channels on): see choose.
+// - up to four tiles (of 32 steps, up to 192 channels): see worth_short. Tiles of 64 steps (from 208 channels on): see choose.
 // What else decides is how often a workgroup of either kernel goes round (a round is a tile of each of its slices) and what the
 // preparation costs: the tiles' converts both gates' weights of all blocks, the fused kernel's one gate's, 1 - 5 us more by the
 // number of blocks. `half`: the tiles go round at most half as often.
@@ -79,12 +78,40 @@ bool shape_ok(int B, int T, int D, int bs, bool packed) {
 //   T 2048 69 : 52). At 240 and 256 the gain is smaller: with the merge, many blocks or a long sequence take `half` (256, 24 blocks, T 2048
 //   71 : 63; B 2 of 10 blocks, T 4096 93 : 89, T 6000 123 : 124), and 29 - 32 units of more than 8 blocks lose in between (256, 16 blocks: B 2 T 1400
 //   43 : 45, T 2048 54 : 52, T 4096 90 : 85, T 8192 159 : 156, T 12000 226 : 228; 8 blocks, B 4 T 2048 50 : 52).
+// Short sequences, up to 128 steps of 144 - 192 channels and 256 of 208 - 256 (160, 16 blocks: B 1 T 20 11.2 : 16.3, T 128 12.8 : 16.9, with the
+// merge 14.8 : 16.8, B 16 T 128 25 : 30; 192, 10 blocks, B 16 T 128 25 : 32): up to 256 units. What the tiles give away there is the preparation
+// of both gates' weights, in proportion to the blocks, so the line is the size of those weights (7200 calls, 1 - 128 blocks):
+// - 192 and 256 channels, where the fused kernel itself takes longest: 20 and 16 MB (256: 64 blocks B 2 T 32 20.2 : 19.8, 96 blocks B 1 T 32
+//   23.1 : 20.9).
+// - one tile: 6.5 MB (176, 64 blocks T 9 15.8 : 15.1; 208, 40 blocks 15.5 : 15.1; 240, 32 blocks 16.0 : 15.5, 48 blocks 18.1 : 16.5); with the merge
+//   or boundaries, which cost the fused kernel more, 10 (208, 64 blocks with the merge 19.3 : 18.6).
+// - more tiles of one sequence: 6.5 MB (208, 48 blocks T 64 17.3 : 16.2), with boundaries 10, with the merge 5 (176, 40 blocks T 33 16.5 : 15.6; 240,
+//   24 blocks T 64 17.6 : 16.1; 208, 32 blocks T 128 18.2 : 16.5); from five tiles on 10 and, with boundaries, 16 MB (208, 64 blocks T 256: with the
+//   merge 28.6 : 26.0, with boundaries 27.7 : 28.6).
+// - of several sequences: 16 MB (240, 64 blocks B 2 T 64 21.5 : 23.6), with the merge of more than 160 channels 10 (240, 96 blocks B 2 T 64 32.1 : 30.7).
+// Past 128 units the second tile loses where a unit's workgroups share a compute unit and the fused kernel has one each: more than 16 blocks
+// from 208 channels on (24 blocks, B 8 T 64, 208: 20.0 : 18.9), at 240 any (16 blocks, B 16 T 64 21.1 : 19.5), at 256 more than 24 (40 blocks, B 4
+// T 64 23.9 : 22.7), at 176, past 160 units, more than 24 (48 blocks, B 4 T 128 27.7 : 26.2); five tiles from 113 units on (240, 16 blocks,
+// B 8 T 160 29.9 : 28.6). Not with the merge, whose epilogue the fused kernel pays more for.
+bool worth_short(int B, int T, int nb, int bs, int var) {
+  const bool merge = var == V_MERGE || var == V_MERGE_TANH, plain = var == V_PLAIN;
+  const int nct = (bs + 31) / 32, n = (T + 31) / 32;
+  const long long units = (long long)B * nb, KB = (long long)nb * nct * nct * 4;
+  if (units > 256) return false;
+  const long long most = bs == 192 ? 20000 : bs == 256 ? 16384 : n == 1 ? (plain ? 6450 : 10000) : B > 1 ? (merge && bs > 160 ? 10000 : 16384)
+                         : n <= 4 ? (plain ? 6450 : merge ? 5000 : 10000) : (plain || merge ? 10000 : 16384);
+  if (KB > most) return false;
+  if (merge || n == 1) return true;
+  if (bs >= 208 && units > 112 && units <= 128 && n == 5) return false;
+  if (bs >= 208 && units > 128) return nb <= (bs == 256 ? 24 : bs >= 240 ? 0 : 16);
+  return bs != 176 || units <= 160 || nb <= 24;
+}
 bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
   if (!forward_mfma_block(bs) || bs <= 128) return true;
   const bool merge = var == V_MERGE || var == V_MERGE_TANH;
   const int steps = 32 * in.mt;
   const long long units = (long long)B * nb;
-  if (T <= 4 * steps) return in.mt == 1 && units <= 256;
+  if (T <= 4 * steps) return in.mt == 1 && worth_short(B, T, nb, bs, var);
   // (for 256 compute units on either side: the same rule where no card is visible)
   const auto rounds = [&](int step, int workgroups, int most) {
     const int n = (T + step - 1) / step, G = pick_slices(B * nb, n, workgroups, most);
@@ -133,7 +160,7 @@ Instance choose(int B, int T, int nb, int bs, int var) {
   const Instance one = find_fwd_short_instance(in.waves, var);
   const int n1 = (T + 31) / 32, n2 = (T + 63) / 64, G1 = pick_slices(B * nb, n1, one.per_cu * 256, FWD_TILE_SLICES),
             G2 = pick_slices(B * nb, n2, in.per_cu * 256, FWD_TILE_SLICES), r1 = (n1 + G1 - 1) / G1, r2 = (n2 + G2 - 1) / G2;
-  if (T <= 256) return (long long)B * nb <= 256 && (r1 == 1 || (r1 == 2 && (var == V_MERGE || var == V_MERGE_TANH || G1 >= 3))) ? one : none;
+  if (T <= 256) return worth_short(B, T, nb, bs, var) && (r1 == 1 || (r1 == 2 && (var == V_MERGE || var == V_MERGE_TANH || G1 >= 3))) ? one : none;
   if (!worth(B, T, nb, bs, var, in)) return none;
   return r1 == 1 && ((long long)B * nb * n1 <= 256 || r2 > 1) ? one : in;
 }

@@ -464,6 +464,54 @@ def test_forward_takes_the_faster_kernel(B, T, bs, nb, merge, tiles):
     assert ((a - b).norm() / b.norm()).item() < 2.0 ** -9 and ((h - k).norm() / k.norm()).item() < 2.0 ** -9
 
 
+@pytest.mark.parametrize("B,T,bs,nb,how,tiles", [
+    (1, 9, 176, 44, "plain", True), (1, 9, 176, 45, "plain", False), (1, 9, 176, 45, "packed", True), (1, 32, 208, 33, "plain", False),
+    (1, 20, 208, 51, "merge", True), (1, 20, 208, 52, "merge", False), (1, 64, 240, 25, "plain", True), (1, 64, 240, 26, "plain", False),
+    (1, 64, 240, 19, "merge", True), (1, 64, 240, 20, "merge", False), (1, 200, 208, 51, "plain", True), (1, 200, 208, 52, "plain", False),
+    (1, 64, 240, 39, "packed", True), (1, 64, 240, 40, "packed", False), (2, 64, 240, 50, "plain", True), (2, 64, 240, 39, "merge", True),
+    (2, 64, 240, 40, "merge", False), (2, 33, 160, 100, "merge", True), (1, 32, 192, 128, "merge", True), (1, 32, 192, 139, "packed", False),
+    (8, 64, 208, 24, "plain", False), (8, 32, 208, 24, "plain", True), (8, 64, 208, 24, "merge", True), (8, 160, 240, 16, "plain", False),
+    (8, 128, 240, 16, "plain", True), (16, 64, 240, 16, "packed", False), (4, 128, 176, 48, "plain", False), (4, 128, 176, 40, "plain", True),
+    (8, 64, 256, 32, "plain", False), (8, 64, 256, 24, "packed", True)])
+def test_short_forward_takes_the_faster_kernel(B, T, bs, nb, how, tiles):
+    """Either side of the rule by the size of the weights that the tiles prepare; the two kernels' results differ by the rounding of their
+    last bits (2^-9 in the 2-norm), seen against the least workspace's fused kernel."""
+    import torch
+    import paper_2402_19427_amd as R
+    D = bs * nb
+    g = torch.Generator(device="cuda").manual_seed(T + bs)
+    rand = lambda *s, k=1.0: torch.randn(*s, generator=g, device="cuda") * k
+    bf = lambda t: t.to(torch.bfloat16)
+    weights = (bf(rand(nb, bs, bs, k=bs ** -0.5)), bf(rand(nb, bs, bs, k=bs ** -0.5)), rand(D, k=0.1), rand(D, k=0.1),
+               torch.full((D,), 4.0, device="cuda"), rand(4, D, k=0.5), rand(D, k=0.1))
+    par, sh = R.make_params(*weights), R.make_shape(B, T, D, nb, R.BF16)
+    u, br, y, out, hT = bf(rand(B, T, D)), bf(rand(B, T, D)), bf(rand(B, T, D)), bf(rand(B, T, D)), rand(B, D)
+    reset = (torch.rand(B, T, generator=g, device="cuda") < 0.05).to(torch.uint8)
+    need = R.rglru_workspace_bytes(sh, {"plain": R.OP_FORWARD, "merge": R.OP_FORWARD_MERGE, "packed": R.OP_FORWARD_PACKED}[how])
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+
+    def call(n):
+        R.rglru_timing_enable(True)
+        try:
+            if how == "merge":
+                R.rglru_forward_merge(sh, par, u, br, None, None, 0, 0, out, y, hT, None, ws, n, None)
+            elif how == "packed":
+                R.rglru_forward_packed(sh, par, u, reset, None, None, 0, y, hT, None, ws, n, None)
+            else:
+                R.rglru_forward(sh, par, u, None, None, 0, y, hT, None, ws, n, None)
+            torch.cuda.synchronize()
+            return names_of(R), y.float().clone(), hT.clone()
+        finally:
+            R.rglru_timing_enable(False)
+
+    names, a, h = call(need)
+    assert ("fwd_tile_kernel" in names and "merge_fwd_kernel" not in names) == tiles, names
+    if tiles:
+        names, b, k = call(need - 256)   # (one cell less than the tiles ask for)
+        assert "fwd_tile_kernel" not in names, names
+        assert ((a - b).norm() / b.norm()).item() < 2.0 ** -9 and ((h - k).norm() / k.norm()).item() < 2.0 ** -9
+
+
 @pytest.mark.parametrize("T,bs,nb,merge,tiles,cap", [
     (4096, 112, 1, False, True, 0), (4097, 112, 1, False, False, 0), (6000, 112, 10, False, True, 0), (4096, 192, 1, True, True, 0),
     (4609, 192, 1, True, False, 0), (4096, 224, 1, False, True, 0), (4200, 224, 1, False, False, 0), (3584, 240, 1, True, True, 0),
