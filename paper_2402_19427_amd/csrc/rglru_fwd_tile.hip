@@ -152,7 +152,8 @@ bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
 //   two slices 33 : 31 (B 11 T 100, 16 blocks), 35 : 33 with B 16. Not from three rounds on (10 blocks, B 16 T 256 44 : 43).
 // - past T 256, where tiles are the faster forward at all: in one round of a workgroup per compute unit (B 1, 10 blocks, T 777 with the merge
 //   20.8 : 24.9 in tiles of 64; T 500 17.2 : 17.9), or in one round where those of 64 take two (B 2 T 777 25.5 : 29.7; but B 2 T 500, one round of
-//   either, 23 : 20).
+//   either, 23 : 20). Up to 25 slices: more records than that take a fourth round trip in every workgroup (8 blocks of 256, T 800 15.2 : 17.3 in
+//   tiles of 64, T 900 19.9 : 17.4, T 1024 19.5 : 17.7, T 900 with the merge 21.8 : 20.7; 208, one block, T 900 17.9 : 15.4).
 Instance choose(int B, int T, int nb, int bs, int var) {
   const Instance none = {nullptr, 0, 0, 0, 0}, in = find_instance(bs, var);
   if (!in.kernel) return none;
@@ -162,7 +163,7 @@ Instance choose(int B, int T, int nb, int bs, int var) {
             G2 = pick_slices(B * nb, n2, in.per_cu * 256, FWD_TILE_SLICES), r1 = (n1 + G1 - 1) / G1, r2 = (n2 + G2 - 1) / G2;
   if (T <= 256) return worth_short(B, T, nb, bs, var) && (r1 == 1 || (r1 == 2 && (var == V_MERGE || var == V_MERGE_TANH || G1 >= 3))) ? one : none;
   if (!worth(B, T, nb, bs, var, in)) return none;
-  return r1 == 1 && ((long long)B * nb * n1 <= 256 || r2 > 1) ? one : in;
+  return r1 == 1 && G1 <= 25 && ((long long)B * nb * n1 <= 256 || r2 > 1) ? one : in;
 }
 // Of short calls the whole plan is asked for: a few KB of records and the second gate's weights.
 constexpr int SHORT = 256;

@@ -512,6 +512,38 @@ def test_short_forward_takes_the_faster_kernel(B, T, bs, nb, how, tiles):
         assert ((a - b).norm() / b.norm()).item() < 2.0 ** -9 and ((h - k).norm() / k.norm()).item() < 2.0 ** -9
 
 
+@pytest.mark.parametrize("T,bs,nb", [(832, 256, 8), (1024, 208, 1), (900, 240, 4)])
+@pytest.mark.parametrize("merge", [False, True])
+def test_tiles_of_32_steps_up_to_25_slices(T, bs, nb, merge):
+    """Past 25 slices a sequence goes in tiles of 64 steps: the bits of a call whose slices are capped at the number of those, which the
+    smaller tiles could only walk in two rounds (the state is rounded where it enters a tile)."""
+    import torch
+    import paper_2402_19427_amd as R
+    rn = runner()
+    D, act = bs * nb, "bf16"
+    inp = gen.make_inputs(1, T, D, nb, act=act, seed=T + bs, h0=True, bias=True)
+    dp = rn.DeviceProblem(inp, 1, T, D, nb, act)
+    u, h0 = rn.to_device(inp["u"], act), rn.to_device(inp["h0"], "f32")
+    br = rn.to_device(gen.make_branch(1, T, D, act=act, seed=T), act)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0")
+    dp.workspace = lambda shape, op: (ws, ws.numel())
+
+    def call(cap):
+        R.rglru_set_max_time_slices(cap)
+        R.rglru_timing_enable(True)
+        try:
+            out = dp.forward_merge(u, br, h0=h0)[1:3] if merge else dp.forward(u, h0=h0)[:2]
+            torch.cuda.synchronize()
+            assert "fwd_tile_kernel" in names_of(R)
+            return out
+        finally:
+            R.rglru_timing_enable(False)
+            R.rglru_set_max_time_slices(0)
+
+    for a, b in zip(call(0), call((T + 63) // 64)):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("T,bs,nb,merge,tiles,cap", [
     (4096, 112, 1, False, True, 0), (4097, 112, 1, False, False, 0), (6000, 112, 10, False, True, 0), (4096, 192, 1, True, True, 0),
     (4609, 192, 1, True, False, 0), (4096, 224, 1, False, True, 0), (4200, 224, 1, False, False, 0), (3584, 240, 1, True, True, 0),
