@@ -356,6 +356,15 @@ static bool cg_fused_fills(const Problem &p) {
   const long long pairs = (long long)p.nb * p.B, ncu = mfma::num_cu();
   return pairs * p.bs > 64 * ncu * ((pairs + ncu - 1) / ncu);
 }
+// Whether it beats the tiles, too: one round of nearly all compute units and three of its tiles, where many blocks' weights are as much
+// work to prepare as a tile. Us, 128 channels, fused / tiles: 16 blocks, B 16, T 65 32.0 / 34.4, T 96 33.0 / 34.7, T 97 39.9 / 36.0, B 12
+// T 65 31.6 / 32.2; 20 blocks, B 10, T 65 31.6 / 33.0; 10 blocks, B 20, T 65 31.6 / 31.6, B 24 31.9 / 32.6, T 96 33.1 / 34.3; 8 blocks, B 30
+// 32.0 / 32.0.
+// Past one round 2 / 1 (10 blocks, B 26), and 96 channels 31 / 30.
+static bool cg_fused_beats_tiles(const Problem &p) {
+  const long long pairs = (long long)p.nb * p.B, ncu = mfma::num_cu();
+  return cg_fused_ok(p) && p.bs == 128 && p.T <= 96 && pairs <= ncu && (p.nb >= 16 ? 4 * pairs >= 3 * ncu : p.nb >= 10 && 16 * pairs >= 15 * ncu);
+}
 static hipError_t launch_cg_fused(const Problem &p, hipStream_t s) {
   const size_t lds = (size_t)MT * 2 * p.bs * 4 + (size_t)2 * MT * (2 * p.bs + 8) * 2;
   if (lds > 48 * 1024) {
@@ -779,7 +788,7 @@ size_t cg_backward_ws_bytes(int B, int T, int D, int nb) {   // ... + the recomp
 }
 
 hipError_t launch_cg_forward(const Problem &p, bool bf, hipStream_t s) {
-  if (bf && cg_forward_tile_supported(p)) return launch_cg_forward_tile(p, s);
+  if (bf && !cg_fused_beats_tiles(p) && cg_forward_tile_supported(p)) return launch_cg_forward_tile(p, s);
   const bool fused = bf && cg_fused_ok(p);
   if (bf && !(fused && cg_fused_fills(p)) && cg_forward_pass_supported(p)) return launch_cg_forward_pass(p, s);
   if (fused) return launch_cg_fused(p, s);

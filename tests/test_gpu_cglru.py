@@ -197,3 +197,28 @@ def test_weights_past_half_precision(hs, nb, T):
         if k in ("du", "dh0", "dconv_w", "dconv_b"):   # (the channel such a weight leads to on a scale of its own)
             a, b = a[..., np.arange(D) != 4], b[..., np.arange(D) != 4]
         assert gen.rel_err(a, b) < tol, k
+
+
+@pytest.mark.parametrize("B,T,hs,nb,tiles", [(16, 65, 128, 16, False), (12, 96, 128, 16, False), (16, 97, 128, 16, True), (17, 65, 128, 16, True),
+                                             (11, 65, 128, 16, True), (24, 96, 128, 10, False), (23, 65, 128, 10, True), (16, 65, 96, 16, True)])
+def test_cg_forward_takes_the_faster_kernel(B, T, hs, nb, tiles):
+    """Either side of the rule between the tiles and the fused kernel, rows of equal inputs against the oracle's one."""
+    import paper_2402_19427_amd as R
+    import torch
+    rn = runner()
+    D, act = 2 * hs * nb, "bf16"
+    inp = gen.make_cg_inputs(1, T, D, nb, act=act, seed=T + hs, h0=True, bias=True)
+    dp = rn.CgDeviceProblem(inp, 1, T, D, nb, act)
+    u, h0 = rn.to_device(inp["u"], act).expand(B, T, D).contiguous(), rn.to_device(inp["h0"], "f32").expand(B, D).contiguous()
+    R.rglru_timing_enable(True)
+    try:
+        y, hT, _ = dp.forward(u, h0=h0)
+        torch.cuda.synchronize()
+        names = [R.rglru_timing_get(i)[0] for i in range(R.rglru_timing_count())]
+    finally:
+        R.rglru_timing_enable(False)
+    assert ("cg_tile_kernel" in names) == tiles, names
+    q = f64(inp)
+    want = oracle.cg_forward(q["u"], *params(q), h0=q["h0"], conv_w=q["conv_w"], conv_b=q["conv_b"])
+    assert torch.equal(y, y[:1].expand(B, T, D)) and torch.equal(hT, hT[:1].expand(B, D))
+    assert gen.rel_err(rn.to_host(y[:1]), want[0]) < TOL[act] and gen.rel_err(rn.to_host(hT[:1]), want[1]) < TOL[act]
