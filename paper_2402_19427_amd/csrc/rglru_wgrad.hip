@@ -9,10 +9,11 @@ using namespace pass;
 
 namespace {
 
-// 256 rows x 32 N columns per workgroup of four waves, one wave per SIMD: 128 x 16 N outputs each, or 64 x 32 N where N is odd. All of
-// a block's columns up to 256 in one workgroup: rows are read once (in tiles of 256 x 128 twice: as much again as memory delivers
-// beside the products), and a pair of fragments from LDS serves 2 N products instead of 8 for 6 of 128 columns, for which LDS
-// was as busy as the matrix units.
+// 256 rows x 32 N columns per workgroup of four waves, one wave per SIMD: 128 x 16 N outputs each, or 64 x 32 N where N is odd. Where
+// stages are many, all of a block's columns up to 256 are in one workgroup: rows are read once (in tiles of 256 x 128 twice: as much again
+// as memory delivers beside the products), and a pair of fragments from LDS serves 2 N products instead of 8 for 6 of 128 columns,
+// for which LDS was as busy as the matrix units. Where they are few, its start and end are what it takes, and half of the columns start and
+// end faster (see cost).
 // What goes round is a unit of two planes of 16 steps: both halves of a stage, or the two parts of one half. Rows and columns
 // come to LDS by direct-to-LDS loads, P units ahead (a counted wait and one barrier per unit); the fragments of a plane
 // arrive while the other's products run. Bound by memory where the chip is full: B 16 T 4096, 16 blocks of 256 channels 303 us, 1.6 GB
@@ -139,17 +140,26 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 struct Shape {
   int njt, nkt, n;   // row and column tiles of a block; 32-column blocks of a tile
 };
-// Tiles of all columns up to 256, but of half of 224 or 256 where there are few stages: their workgroups start and end in 9 us
-// instead of 12, and half as many slices keep the chip as busy. us, halves : whole, with the final sums: 10 blocks of 256, 2 stages 14.5 :
-// 17, 64 24 : 28, 512 78 : 83, 1024 125 : 127, 2048 217 : 209; 16 of 512 32 stages 45 : 52, 128 104 : 102, 256 188 : 171.
-Shape shape(int nst, int ra, int cb, int parts) {
+// all columns of a block up to 256 in one tile, or half of them
+Shape shape(int ra, int cb, int parts, bool half) {
   const int blocks = (cb + 31) / 32, whole = (blocks + 7) / 8;
-  const bool half = (blocks + whole - 1) / whole >= 7 && (parts == 2 || nst <= (whole == 1 ? 512 : 64));
   Shape q;
   q.njt = (ra + 255) / 256;
   q.nkt = half ? 2 * whole : whole;
-  q.n = std::max(4, (blocks + q.nkt - 1) / q.nkt);
+  q.n = std::max(parts == 1 ? 2 : 4, (blocks + q.nkt - 1) / q.nkt);
   return q;
+}
+// ns of S slices of `per` stages, nst in all. A compute unit runs one workgroup at a time: a round of them starts, ends and writes its sums in
+// 0.9 us + 0.8 per 32 columns and takes 0.23 us + 0.025 per 32 columns for a stage, or all together as long as the operands need,
+// 0.08 us for a MB of them and 0.02 for a MB that comes to a workgroup; the final sums read 1 MB in 0.16 us (least squares over 7000 calls: 112 - 512
+// channels, 1 - 16 blocks, 1 - 1024 stages, 1 - 64 slices, tiles of all and of half the columns; what it takes is on average 0.6 %,
+// at most 8 %, slower than the best of them). us of the backward, so : with as many slices as a fixed start of 12 us per workgroup pays for and halves
+// from 224 channels on only : with tiles of 256 x 128 and slices of 8 stages and more: one block of 208, B 18 T 273 51 : 62 : 50; one of
+// 192, T 4096 97 : 119 : 103; two of 160, B 16 T 59 31 : 41 : 34; 16 of 128, T 512 33 : 38 : 35; 10 of 192, T 156 33 : 40 : 35.
+long long cost(const Shape &q, int nst, int nb, int ra, int cb, int S, int per) {
+  const long long tiles = (long long)nb * q.njt * q.nkt, rounds = (tiles * S + 255) / 256, KB = ((long long)nb * ra * cb * S) >> 8;
+  const long long all = ((long long)nb * (ra + cb) * nst) >> 4, moved = (tiles * (256 + 32 * q.n) * nst) >> 4;   // KB
+  return rounds * (880 + 760 * q.n) + std::max(rounds * per * (234 + 25 * q.n), (78 * all + 18 * moved) >> 10) + (168 * KB >> 10);
 }
 template <int PARTS, int N>
 hipError_t launch(const WgradArgs &a, hipStream_t s) {
@@ -164,6 +174,8 @@ hipError_t launch(const WgradArgs &a, hipStream_t s) {
 }
 template <int PARTS>
 hipError_t launch_n(int n, const WgradArgs &a, hipStream_t s) {
+  if constexpr (PARTS == 1)
+    if (n < 4) return n == 2 ? launch<1, 2>(a, s) : launch<1, 3>(a, s);
   switch (n) {
     case 4: return launch<PARTS, 4>(a, s);
     case 5: return launch<PARTS, 5>(a, s);
@@ -175,24 +187,25 @@ hipError_t launch_n(int n, const WgradArgs &a, hipStream_t s) {
 
 }  // namespace
 
-// A compute unit runs one workgroup. A stage takes 0.7 us (256 columns; 0.5 of it products), a workgroup's start, first loads and
-// partial sums 12 us (measured at 2 - 64 stages, 20 workgroups), 5 MB of
-// partial sums 0.5 us more in the final sums: as many
-// slices as make the time of all rounds least. us at 4, 8, 12 slices: B 8 T 2048, 10 blocks of 256 120, 76, 70; 16 of 160 92, 72, 82 (12:
-// a second round of workgroups).
+// As many slices as make the time least. Two parts: tiles of half the columns of 112 and 128 channels (a wave has no room for the sums of all), a
+// stage takes 0.7 us, a workgroup's start, first loads and partial sums 12 us, 5 MB of partial sums 0.5 us more in the final sums.
 int tile_wgrad_slices(int nst, int nb, int ra, int cb, int parts, long long fit) {
-  const Shape q = shape(nst, ra, cb, parts);
+  const Shape one = shape(ra, cb, parts, false), two = shape(ra, cb, parts, true), &q = parts == 2 && one.n >= 7 ? two : one;
   const long long tiles = (long long)nb * q.njt * q.nkt, sums = ((long long)nb * ra * cb * 4) >> 10;
-  long long best = 1, cost = -1;
+  long long best = 1, least = -1;
   for (long long S = 1; S <= 64 && S <= fit && S <= nst; ++S) {
-    const long long c = ((tiles * S + 255) / 256) * ((nst + S - 1) / S + 16) * 7000 + S * sums;   // (a stage: 7 MB of sums)
-    if (cost < 0 || c < cost) best = S, cost = c;
+    const int per = (int)((nst + S - 1) / S);
+    const long long c = parts == 2 ? ((tiles * S + 255) / 256) * (per + 16) * 7000 + S * sums   // (a stage: 7 MB of sums)
+                                   : std::min(cost(one, nst, nb, ra, cb, (int)S, per), cost(two, nst, nb, ra, cb, (int)S, per));
+    if (least < 0 || c < least) best = S, least = c;
   }
   return (int)best;
 }
 
 hipError_t launch_tile_wgrad(const TileWgrad &w, int parts, hipStream_t s) {
-  const Shape q = shape(w.nst, w.ra, w.cb, parts);
+  const Shape one = shape(w.ra, w.cb, parts, false), two = shape(w.ra, w.cb, parts, true);
+  const bool half = parts == 2 ? one.n >= 7 : cost(two, w.nst, w.nb, w.ra, w.cb, w.S, w.per) < cost(one, w.nst, w.nb, w.ra, w.cb, w.S, w.per);
+  const Shape &q = half ? two : one;
   WgradArgs a;
   a.w = w;
   a.njt = q.njt; a.nkt = q.nkt;

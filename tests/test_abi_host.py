@@ -354,3 +354,10 @@ def test_workspace_sizes_for_narrower_gate_blocks():
 def test_backward_workspace_stays_what_it_was_for_few_rows(shape, op, was):
     """A few rows of a wide block: the partial sums of the weight gradients take the room of what they no longer need."""
     assert R.rglru_workspace_bytes(R.make_shape(*shape, R.BF16), getattr(R, op)) <= was
+
+
+@pytest.mark.parametrize("shape,was", [((16, 59, 320, 2), 13259264), ((3, 758, 224, 1), 15736320), ((1, 156, 1920, 10), 17289728), ((1, 4096, 192, 1), 26530304)])
+def test_backward_asks_for_no_more_slices_than_pay(shape, was):
+    """Each slice of the weight gradients costs the final sums another pass over them: short calls had become up to 40 % slower by slices of one or
+    two stages, and asked for the room of all their sums."""
+    assert R.rglru_workspace_bytes(R.make_shape(*shape, R.BF16), R.OP_BACKWARD) <= was
