@@ -57,8 +57,8 @@
  * to 512 channels runs on the fp32 matrix cores. All other block sizes up to 2048, and the backward
  * in fp32 storage, run on generic kernels that give the same results far more slowly. So does a
  * bf16 forward or decode step whose tensors do not lie on 16-byte boundaries (h0 and hT of the
- * forward may, and u and the conv states on four bytes where the fused kernels take the block); the backward of other blocks than 256 channels and the passes of the complex-gated
- * variant take any alignment (what the backward stages 16 bytes at a time is copied first).
+ * forward may, and u and the conv states on four bytes where the fused kernels take the block); the backward of other blocks than 256 channels and the matrix-core kernels of the
+ * complex-gated variant take tensors of any alignment, with the same results (what the backward stages 16 bytes at a time is copied first).
  * The fused forward, the tiles, the three kernels and the scan cut long sequences into time slices whose
  * workgroups wait for each other (rglru_workspace_status); the passes and the generic kernels never wait.
  * rglru_workspace_bytes() accounts for all of it.

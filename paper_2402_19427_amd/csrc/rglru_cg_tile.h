@@ -45,7 +45,11 @@ struct CgTileArgs {
   float *edge;                  // [B][W][6][D] dx of a window's first and last three rows, or null (one window)
 };
 
-template <int NCT>
+// ANY: u, dy, y and du need not lie on the 16-byte grid. Their rows then go through registers instead of straight to LDS and in 16-byte
+// accesses of any alignment: the same values in the same places, so that results do not depend on where the tensors lie. What is not in
+// flight while the tile in front is worked on costs 15 - 25 % (10 blocks of 128, B 8 T 2048: forward 146 us on the grid, 166 eight bytes off it,
+// 186 two bytes off it, backward 394, 437 and 463; in passes 307 - 316 and 790).
+template <int NCT, bool ANY>
 struct Wave {
   static constexpr int NKS = 4 * NCT;
   const CgTileArgs &a;
@@ -104,8 +108,26 @@ struct Wave {
   __device__ __forceinline__ f32x4 gate_consts() const { return con4(0); }
   __device__ __forceinline__ f32x4 taps(int part) const { return con4(4 + 4 * part); }
 
+  // sixteen rows from step t on of one part, zero where there are none, to 1 KB of LDS
+  __device__ __forceinline__ void rows_in(const void *from, unsigned char *to, int t, int part) const {
+    const int l = lane_again(), step = t + (l >> 2), c0 = wv * 32 + (l & 3) * 8;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (step >= 0 && step < T && c0 < hs) v = *(const u32x4_at2 *)((const unsigned short *)from + (seq + step) * D + part * H + g * hs + c0);
+    *(u32x4 *)(to + l * 16) = v;
+  }
   // six loads: u of steps -4 .. 31 of a tile
   __device__ __forceinline__ void load_u(int tile) const {
+    if constexpr (ANY) {
+#pragma unroll
+      for (int part = 0; part < 2; ++part) {
+        unsigned char *to = my + U + part * U_PART;
+        rows_in(p.u, to, tile * 32 - 4, part);
+        rows_in(p.u, to + 1024, tile * 32 + 12, part);
+        if (lane_again() < 16) rows_in(p.u, to + 2048, tile * 32 + 28, part);
+      }
+      wave_lds_fence();
+      return;
+    }
     const int t0 = tile * 32, back = t0 > 0 ? 4 : 0;
     const int l = lane_again(), lrow = l >> 2, c0 = wv * 32 + (l & 3) * 8;
     const bool pc_ok = c0 < hs;
@@ -122,6 +144,14 @@ struct Wave {
   }
   // four loads: dy of a tile's steps
   __device__ __forceinline__ void load_dy(int tile) const {
+    if constexpr (ANY) {
+#pragma unroll
+      for (int part = 0; part < 2; ++part)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) rows_in(p.dy, my + S + part * 2048 + m * 1024, tile * 32 + 16 * m, part);
+      wave_lds_fence();
+      return;
+    }
     const int l = lane_again(), lrow = l >> 2, c0 = wv * 32 + (l & 3) * 8;
     const unsigned vo = c0 < hs ? (unsigned)lrow * row2 + (unsigned)(g * hs + c0) * 2 : OOB;
     const u32x4 rs = buf_words((const unsigned short *)p.dy + (seq + tile * 32) * D, (size_t)rows(tile) * row2);
@@ -171,7 +201,13 @@ struct Wave {
 #pragma unroll
       for (int n = 0; n < 2; ++n)
         q[n] = lds_tr(t + (unsigned)(8 * c4 + 4 * n + r4) * 64 + (unsigned)(((2 * m + (l >> 5)) ^ key(4 * n + r4)) * 16) + (unsigned)((l >> 4) & 1) * 8);
-      store16<0>((u32x4){q[0][0], q[0][1], q[1][0], q[1][1]}, rs, vo, (unsigned)(16 * m) * row2);
+      const u32x4 v = {q[0][0], q[0][1], q[1][0], q[1][1]};
+      if constexpr (ANY) {
+        const int step = tile * 32 + 16 * m + 4 * (l >> 4) + c4;
+        if (step < T && c0 < hs) *(u32x4_at2 *)((unsigned short *)out + (seq + step) * D + part * H + g * hs + c0) = v;
+      } else {
+        store16<0>(v, rs, vo, (unsigned)(16 * m) * row2);
+      }
     }
   }
   // a lane's 16 steps of one part (or gate), as rglru_wgrad.h has them
@@ -242,8 +278,8 @@ struct CgInstance {
   const void *agg, *bagg, *y, *bwd;
   int nct;
 };
-CgInstance cg_instance_fwd(int nct);   // agg, y
-CgInstance cg_instance_bwd(int nct);   // bagg, bwd
+CgInstance cg_instance_fwd(int nct, bool any);   // agg, y
+CgInstance cg_instance_bwd(int nct, bool any);   // bagg, bwd
 
 }  // namespace cgt
 }  // namespace rglru

@@ -4,11 +4,14 @@
 namespace rglru {
 namespace cgt {
 
-template <int NCT>
+template <int NCT, bool ANY>
 static CgInstance instance() {
-  return {(const void *)cg_tile_kernel<NCT, M_AGG>, (const void *)cg_tile_kernel<NCT, M_BAGG>, (const void *)cg_tile_kernel<NCT, M_Y>, nullptr, NCT};
+  return {(const void *)cg_tile_kernel<NCT, M_AGG, ANY>, (const void *)cg_tile_kernel<NCT, M_BAGG, ANY>, (const void *)cg_tile_kernel<NCT, M_Y, ANY>,
+          nullptr, NCT};
 }
-CgInstance cg_instance_fwd(int nct) { return nct == 3 ? instance<3>() : instance<4>(); }
+CgInstance cg_instance_fwd(int nct, bool any) {
+  return nct == 3 ? any ? instance<3, true>() : instance<3, false>() : any ? instance<4, true>() : instance<4, false>();
+}
 
 }  // namespace cgt
 }  // namespace rglru

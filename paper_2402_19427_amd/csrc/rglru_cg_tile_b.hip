@@ -4,9 +4,13 @@
 namespace rglru {
 namespace cgt {
 
-CgInstance cg_instance_bwd(int nct) {
-  CgInstance in = cg_instance_fwd(nct);
-  in.bwd = nct == 3 ? (const void *)cg_bwd_tile_kernel<3, 4> : (const void *)cg_bwd_tile_kernel<4, 4>;
+template <int NCT>
+static const void *kernel(bool any) {
+  return any ? (const void *)cg_bwd_tile_kernel<NCT, 4, true> : (const void *)cg_bwd_tile_kernel<NCT, 4, false>;
+}
+CgInstance cg_instance_bwd(int nct, bool any) {
+  CgInstance in = cg_instance_fwd(nct, any);
+  in.bwd = nct == 3 ? kernel<3>(any) : kernel<4>(any);
   return in;
 }
 

@@ -10,10 +10,10 @@ namespace cgt {
 
 constexpr int M_AGG = 0, M_BAGG = 1, M_Y = 2;
 
-template <int NCT, int MODE>
+template <int NCT, int MODE, bool ANY>
 __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) cg_tile_kernel(CgTileArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  typedef Wave<NCT> Wv;
+  typedef Wave<NCT, ANY> Wv;
   constexpr int NKS = Wv::NKS;
   const unsigned id = xcd_id();
   if (id >= a.total) return;

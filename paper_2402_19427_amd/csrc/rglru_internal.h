@@ -135,7 +135,7 @@ hipError_t launch_cg_forward_pass(const Problem &p, hipStream_t s);
 size_t cg_backward_pass_ws_bytes(int B, int T, int D, int nb);
 bool cg_backward_pass_supported(const Problem &p);
 hipError_t launch_cg_backward_pass(const Problem &p, hipStream_t s);
-// ... and of 80 to 128 of them, tensors on the 16-byte grid: in tiles (rglru_cg_tile.hip)
+// ... and of 80 to 128 of them: in tiles (rglru_cg_tile.hip)
 size_t cg_forward_tile_ws_bytes(int B, int T, int D, int nb);
 bool cg_forward_tile_supported(const Problem &p);
 hipError_t launch_cg_forward_tile(const Problem &p, hipStream_t s);

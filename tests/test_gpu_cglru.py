@@ -222,3 +222,51 @@ def test_cg_forward_takes_the_faster_kernel(B, T, hs, nb, tiles):
     want = oracle.cg_forward(q["u"], *params(q), h0=q["h0"], conv_w=q["conv_w"], conv_b=q["conv_b"])
     assert torch.equal(y, y[:1].expand(B, T, D)) and torch.equal(hT, hT[:1].expand(B, D))
     assert gen.rel_err(rn.to_host(y[:1]), want[0]) < TOL[act] and gen.rel_err(rn.to_host(hT[:1]), want[1]) < TOL[act]
+
+
+@pytest.mark.parametrize("B,T,hs,nb", [(1, 65, 80, 2), (2, 300, 96, 2), (9, 165, 112, 20), (3, 129, 128, 3), (130, 70, 96, 4)])
+@pytest.mark.parametrize("off", [1, 2, 4])
+def test_cg_tiles_at_any_alignment(B, T, hs, nb, off):
+    """Tensors and parameters off the 16-byte grid, all of them or the outputs only: the tiles, the same bits."""
+    import paper_2402_19427_amd as R
+    import torch
+    rn = runner()
+    D, H, act = 2 * hs * nb, hs * nb, "bf16"
+    inp = gen.make_cg_inputs(B, T, D, nb, act=act, seed=off + hs, h0=True, state=True, bias=True, dy=True)
+    cg = rn.CgDeviceProblem(inp, B, T, D, nb, act)
+    sh = cg.shape()
+    u, dy, h0 = rn.to_device(inp["u"], act), rn.to_device(inp["dy"], act), rn.to_device(inp["h0"], "f32")
+    ring = rn.to_device(gen.ring_from_chrono(inp["state"], 4), act)
+    f32 = lambda *s: torch.empty(*s, dtype=torch.float32, device="cuda:0")
+    n = max(R.rglru_workspace_bytes(sh, R.OP_CG_FORWARD), R.rglru_workspace_bytes(sh, R.OP_CG_BACKWARD))
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+
+    def at(t, off):
+        room = torch.empty(t.numel() + 64, dtype=t.dtype, device=t.device)
+        out = room[off:off + t.numel()].view(t.shape)
+        out.copy_(t)
+        return out
+
+    def call(off_in, off_out):
+        held = [at(cg.t[k], off_in) for k in ("W_a", "W_x", "b_a", "b_x", "Lambda", "theta", "conv_w", "conv_b")]
+        par = R.make_cg_params(*held)
+        g = dict(dW_a=f32(nb, hs, 2 * hs), dW_x=f32(nb, hs, 2 * hs), db_a=f32(H), db_x=f32(H), dLambda=f32(H), dtheta=f32(H),
+                 dconv_w=f32(4, D), dconv_b=f32(D))
+        out = dict(y=at(torch.zeros_like(u), off_out), hT=f32(B, D), ring=at(torch.zeros_like(ring), off_out), du=at(torch.zeros_like(u), off_out),
+                   dh0=f32(B, D))
+        uu, dd, rr = at(u, off_in), at(dy, off_in), at(ring, off_in)
+        R.rglru_timing_enable(True)
+        try:
+            R.rglru_cg_forward(sh, par, uu, h0, rr, 4, out["y"], out["hT"], out["ring"], ws, n, None)
+            R.rglru_cg_backward(sh, par, uu, h0, rr, 4, dd, None, out["du"], out["dh0"], R.make_cg_param_grads(*g.values()), ws, n, None)
+            torch.cuda.synchronize()
+            names = [R.rglru_timing_get(i)[0] for i in range(R.rglru_timing_count())]
+        finally:
+            R.rglru_timing_enable(False)
+        assert names.count("cg_tile_prep_kernel") == 2 and "cg_bwd_tile_kernel" in names, names
+        return dict(g, **out)
+
+    want = call(0, 0)
+    for got in (call(off, off), call(0, off)):
+        for k in want:
+            assert torch.equal(got[k], want[k]), k
