@@ -267,7 +267,9 @@ __device__ __forceinline__ float2 madd(float2 a, float2 s, float2 e) {   // a s 
   return make_float2(fmaf(a.x, s.x, fmaf(-a.y, s.y, e.x)), fmaf(a.x, s.y, fmaf(a.y, s.x, e.y)));
 }
 
-// The factor of a run's map: the product of a~_t over steps whose r_t sum to rsum, as |a~_t| and its phase are exponentials of r_t
+// The factor of a run's map: the product of a~_t over steps whose r_t sum to rsum, as |a~_t| and its phase are exponentials of r_t.
+// (Up to 64 revolutions and more: the state is as far off as with the product of 16 factors, 6e-6 : 8e-6 at theta up to 0.314, 5.0e-5 : 5.3e-5
+// up to pi, 4.2e-3 : 4.2e-3 up to 30, T 1000 - 2048 - each step's own phase, rounded alike in both, is what counts.)
 __device__ __forceinline__ float2 run_decay(const Decay &k, float rsum) {
   float l2, mod;
   return cdecay(k, rsum, l2, mod);
