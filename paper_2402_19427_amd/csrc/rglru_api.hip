@@ -243,8 +243,8 @@ size_t workspace_need(const rglru_shape *s, int op) {
                                        // fallback for loosely aligned pointers), the general kernels otherwise
       const size_t gen = backward_generic_ws_bytes(s->B, s->T, s->D, s->num_blocks);
       if (s->act_dtype == RGLRU_BF16 && s->D / s->num_blocks == 256 && (size_t)s->T * s->D * 4 < ((size_t)1 << 32)) {
-        return std::max({gen, backward_mfma_packed_ws_bytes(s->B, s->T, s->D, s->num_blocks),
-                         backward_tile_ws_bytes(s->B, s->T, s->D, s->num_blocks, true, false)});
+        const size_t fused = backward_mfma_packed_ws_bytes(s->B, s->T, s->D, s->num_blocks);
+        return fused > gen ? fused : gen;
       }
       return gen;
     }

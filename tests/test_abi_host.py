@@ -361,10 +361,3 @@ def test_backward_asks_for_no_more_slices_than_pay(shape, was):
     """Each slice of the weight gradients costs the final sums another pass over them: short calls had become up to 40 % slower by slices of one or
     two stages, and asked for the room of all their sums."""
     assert R.rglru_workspace_bytes(R.make_shape(*shape, R.BF16), R.OP_BACKWARD) <= was
-
-
-@pytest.mark.parametrize("shape", [(2, 300, 4096, 16), (1, 128, 2560, 10), (3, 77, 512, 2), (8, 2048, 2560, 10)])
-def test_backward_of_packed_rows_asks_for_all_slices(shape):
-    """The same kernels as without boundaries, and the boundaries' masks (16 bytes per 32 steps)."""
-    sh = R.make_shape(*shape, R.BF16)
-    assert R.rglru_workspace_bytes(sh, R.OP_BACKWARD_PACKED) >= R.rglru_workspace_bytes(sh, R.OP_BACKWARD) + 16 * shape[0] * (shape[1] // 32)
