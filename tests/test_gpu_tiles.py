@@ -126,6 +126,7 @@ def test_weight_gradients_in_slices(B, T, bs, nb, packed):
     least = least_room(runs, 256, asked)
     sizes = sorted({asked, least, min(least + one, asked), min(least + 3 * one, asked)})
     print("workspace:", sizes, "a slice:", one)
+    assert len(sizes) > 1 or packed or T > 16000   # (there the general kernels' room is the least that is accepted)
     for n in sizes:
         assert runs(n), n
         for k in ref:
