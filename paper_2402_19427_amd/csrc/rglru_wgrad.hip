@@ -151,15 +151,17 @@ Shape shape(int ra, int cb, int parts, bool half) {
 }
 // ns of S slices of `per` stages, nst in all. A compute unit runs one workgroup at a time: a round of them starts, ends and writes its sums in
 // 0.9 us + 0.8 per 32 columns and takes 0.23 us + 0.025 per 32 columns for a stage, or all together as long as the operands need,
-// 0.08 us for a MB of them and 0.02 for a MB that comes to a workgroup; the final sums read 1 MB in 0.16 us (least squares over 7000 calls: 112 - 512
-// channels, 1 - 16 blocks, 1 - 1024 stages, 1 - 64 slices, tiles of all and of half the columns; what it takes is on average 0.6 %,
-// at most 8 %, slower than the best of them). us of the backward, so : with as many slices as a fixed start of 12 us per workgroup pays for and halves
+// 0.08 us for a MB of them and 0.02 for a MB that comes to a workgroup, more where workgroups are fewer than compute units; the final sums
+// read 1 MB in 0.16 us (least squares over 7000 calls: 112 - 512 channels, 1 - 16 blocks, 1 - 2048 stages, 1 - 64 slices, tiles of all and of half the
+// columns; what it takes is on average 0.6 %,
+// at most 5 %, slower than the best of them). us of the backward, so : with as many slices as a fixed start of 12 us per workgroup pays for and halves
 // from 224 channels on only : with tiles of 256 x 128 and slices of 8 stages and more: one block of 208, B 18 T 273 51 : 62 : 50; one of
 // 192, T 4096 97 : 119 : 103; two of 160, B 16 T 59 31 : 41 : 34; 16 of 128, T 512 33 : 38 : 35; 10 of 192, T 156 33 : 40 : 35.
 long long cost(const Shape &q, int nst, int nb, int ra, int cb, int S, int per) {
   const long long tiles = (long long)nb * q.njt * q.nkt, rounds = (tiles * S + 255) / 256, KB = ((long long)nb * ra * cb * S) >> 8;
   const long long all = ((long long)nb * (ra + cb) * nst) >> 4, moved = (tiles * (256 + 32 * q.n) * nst) >> 4;   // KB
-  return rounds * (880 + 760 * q.n) + std::max(rounds * per * (234 + 25 * q.n), (78 * all + 18 * moved) >> 10) + (168 * KB >> 10);
+  const long long memory = 51 * all + (31 * all + 20 * moved) * 256 * rounds / (tiles * S);
+  return rounds * (880 + 760 * q.n) + std::max(rounds * per * (234 + 25 * q.n), memory >> 10) + (168 * KB >> 10);
 }
 template <int PARTS, int N>
 hipError_t launch(const WgradArgs &a, hipStream_t s) {
