@@ -282,6 +282,8 @@ struct CgInstance {
 };
 CgInstance cg_instance_fwd(int nct, bool any);   // agg, y
 CgInstance cg_instance_bwd(int nct, bool any);   // bagg, bwd
+CgInstance cg_instance_fwd_any(int nct);
+const void *cg_instance_bwd_any(int nct);
 
 }  // namespace cgt
 }  // namespace rglru

@@ -4,13 +4,8 @@
 namespace rglru {
 namespace cgt {
 
-template <int NCT, bool ANY>
-static CgInstance instance() {
-  return {(const void *)cg_tile_kernel<NCT, M_AGG, ANY>, (const void *)cg_tile_kernel<NCT, M_BAGG, ANY>, (const void *)cg_tile_kernel<NCT, M_Y, ANY>,
-          nullptr, NCT};
-}
 CgInstance cg_instance_fwd(int nct, bool any) {
-  return nct == 3 ? any ? instance<3, true>() : instance<3, false>() : any ? instance<4, true>() : instance<4, false>();
+  return any ? cg_instance_fwd_any(nct) : nct == 3 ? fwd_instance<3, false>() : fwd_instance<4, false>();
 }
 
 }  // namespace cgt

@@ -4,13 +4,9 @@
 namespace rglru {
 namespace cgt {
 
-template <int NCT>
-static const void *kernel(bool any) {
-  return any ? (const void *)cg_bwd_tile_kernel<NCT, 4, true> : (const void *)cg_bwd_tile_kernel<NCT, 4, false>;
-}
 CgInstance cg_instance_bwd(int nct, bool any) {
   CgInstance in = cg_instance_fwd(nct, any);
-  in.bwd = nct == 3 ? kernel<3>(any) : kernel<4>(any);
+  in.bwd = any ? cg_instance_bwd_any(nct) : nct == 3 ? (const void *)cg_bwd_tile_kernel<3, 4, false> : (const void *)cg_bwd_tile_kernel<4, 4, false>;
   return in;
 }
 

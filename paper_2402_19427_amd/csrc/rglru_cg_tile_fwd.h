@@ -199,5 +199,11 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(2
   if (MODE == M_BAGG) a.wrev[o] = Rw;
 }
 
+template <int NCT, bool ANY>
+CgInstance fwd_instance() {
+  return {(const void *)cg_tile_kernel<NCT, M_AGG, ANY>, (const void *)cg_tile_kernel<NCT, M_BAGG, ANY>, (const void *)cg_tile_kernel<NCT, M_Y, ANY>,
+          nullptr, NCT};
+}
+
 }  // namespace cgt
 }  // namespace rglru
