@@ -12,11 +12,11 @@
 // steps, the map from the window's start, so that its second kernel, which walks backwards, has the state entering each run.
 // The gates are formed twice for that; an exchange of records between running workgroups would form them once, but the entry
 // points promise that no kernel waits on another.
-// Forward + backward, us, in passes : in tiles: B 8 T 2048, 10 blocks of 128 channels 1054 : 577 (first walk 77, y 93; first walk 90,
-// backward 240, weight gradients 85); 16 blocks B 16 T 4096 5370 : 2830 (the forward in one kernel with the state carried), B 1 T 12000
-// 1200 : 660, B 8 T 130 219 : 146; B 1 T 64, 10 blocks 126 : 77; 10 blocks of 80, B 16 T 2048 1530 : 810.
-// What bounds them: the vector unit (50 % busy, 165 instructions per complex step in the backward, 8 of them transcendental), the
-// matrix units next to it (20 - 25 %), and what two waves per SIMD cannot hide.
+// Forward + backward, us, in passes : in tiles: B 8 T 2048, 10 blocks of 128 channels 1058 : 580 (under the tracer, 4 % slower in all: first walk 76, y 93;
+// first walk 92, backward 239, weight gradients 86); 16 blocks B 16 T 4096 5320 : 2830 (256 units: two windows of each sequence); 10 blocks
+// B 1 T 12000 794 : 433, B 8 T 130 193 : 98, the backward of B 1 T 64 91 : 42; 10 blocks of 80, B 16 T 2048 1526 : 788.
+// What bounds them: the vector unit (two waves per SIMD keep it busy 76 % of the forward walks' time and 63 % of the backward's, 165 instructions
+// per complex step there, 8 of them transcendental), the matrix units next to it (24 and 18 %), and what two waves per SIMD cannot hide.
 #pragma once
 #include "rglru_bwd_fused.h"
 #include "rglru_cg_math.h"

@@ -78,7 +78,8 @@ bool shape_ok(int B, int T, int D, int hs) {
 }
 size_t weight_bytes(int nb, int nct) { return (size_t)nb * nct * nct * 8 * 1024; }
 
-// As many windows as fill the chip, of whole tiles; none is empty
+// As many windows as fill the chip, of whole tiles; none is empty. (From 257 units on one, whose second round of workgroups is nearly empty up to
+// 511: 260 units of 128 channels, T 2048 398 us, 256 in two windows 291; in the fused kernel, which rounds the same way, 1075 and 520.)
 struct Windows {
   int ntile, W, per;
 };

@@ -131,8 +131,9 @@ bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
   // 20 : 27, T 1024 38 : 43, T 4096 107 : 112; 50 units T 2048 72 : 77), with the merge only up to 640 steps (T 300 25 : 29, T 600 38 : 40, T 1024
   // 61 : 56); without it also in two slices that leave a fifth of the chip idle (100 units T 600 52 : 56, T 2048 139 : 142) and in short
   // sequences (80 units T 300 30 : 35, T 600 45 : 46, T 1024 63 : 61; 128 units T 300 37 : 39, T 2048 159 : 149). With the merge and one workgroup per
-  // unit up to 216 of them, where the fused kernel's epilogue costs it most (130 units T 1024 163 : 184, 208 units T 2048 333 : 354; 256 units
-  // 368 : 368).
+  // unit up to 216 of them, where the fused kernel's epilogue costs it most (130 units T 257 57 : 60, T 300 59 : 65, T 1024 163 : 184; 208 units T 300 61 : 66,
+  // T 2048 333 : 354; 256 units 368 : 368). Boundaries cost the fused kernel more than the tiles: as without them (40 units T 257 20 : 28, T 2048
+  // 67 : 71; 80 units T 640 48 : 51; 100 units T 2048 and 4096 0.95 - 0.97 of its time; 128 units T 300 40 : 43, T 640 62 : 64).
   if (bs == 256 && units > 32 && nb <= 16) {
     if (merge) return (units <= 51 && T <= 640) || (units > 128 && units <= 216);
     return units <= 51 || (units > 85 && units <= 100) || (units <= 128 && T <= 640);
@@ -165,7 +166,8 @@ Instance choose(int B, int T, int nb, int bs, int var) {
   if (!worth(B, T, nb, bs, var, in)) return none;
   return r1 == 1 && G1 <= 25 && ((long long)B * nb * n1 <= 256 || r2 > 1) ? one : in;
 }
-// Of short calls the whole plan is asked for: a few KB of records and the second gate's weights.
+// Of short calls the whole plan is asked for: the second gate's weights and up to some MB of records (10 blocks of 256, B 1 T 256 2.6 MB of weights
+// and 1.3 of records; 16 blocks, B 16 T 64 8.4 and 4.2).
 constexpr int SHORT = 256;
 size_t bytes(int B, int T, int nb, int bs, int var, size_t room) {
   const Instance in = choose(B, T, nb, bs, var);

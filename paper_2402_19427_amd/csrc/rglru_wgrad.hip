@@ -17,7 +17,8 @@ namespace {
 // What goes round is a unit of two planes of 16 steps: both halves of a stage, or the two parts of one half. Rows and columns
 // come to LDS by direct-to-LDS loads, P units ahead (a counted wait and one barrier per unit); the fragments of a plane
 // arrive while the other's products run. Bound by memory where the chip is full: B 16 T 4096, 16 blocks of 256 channels 303 us, 1.6 GB
-// (346 in tiles of 256 x 128); B 8 T 2048, 10 blocks of 256 70 (90), 16 of 160 72 (77), B 4 16 of 352 99 (117).
+// (346 in tiles of 256 x 128); B 8 T 2048, 10 blocks of 256 66 (90), 16 of 160 72 (77), B 4 16 of 352 in two slices 105 (117; in five 99, but
+// 6 us more in the final sums).
 template <int PARTS, int N>
 struct Wg {
   static constexpr int WC = N % 2 ? 1 : 2, WR = 4 / WC, M = 8 / WR, NW = N / WC;   // waves along columns, rows; 32-blocks of a wave
