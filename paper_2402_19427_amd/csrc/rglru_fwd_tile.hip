@@ -153,9 +153,10 @@ bool worth(int B, int T, int nb, int bs, int var, const Instance &in) {
 //   two slices 33 : 31 (B 11 T 100, 16 blocks), 35 : 33 with B 16. Not from three rounds on (10 blocks, B 16 T 256 44 : 43).
 // - past T 256, where tiles are the faster forward at all: in one round of a workgroup per compute unit (B 1, 10 blocks, T 777 with the merge
 //   20.8 : 24.9 in tiles of 64; T 500 17.2 : 17.9), or in one round where those of 64 take two (B 2 T 777 25.5 : 29.7; but B 2 T 500, one round of
-//   either, 23 : 20). Up to 25 slices: more records than that take a fourth round trip in every workgroup (8 blocks of 256, T 800 15.2 : 17.3 in
-//   tiles of 64, T 900 19.9 : 17.4, T 1024 19.5 : 17.7, T 900 with the merge 21.8 : 20.7; 208, one block, T 900 17.9 : 15.4).
-Instance choose(int B, int T, int nb, int bs, int var) {
+//   either, 23 : 20). Not where the plan gives up slices for its room, from 26 tiles on, and the round is none (8 blocks of 256, T 800
+//   15.2 : 17.3 in tiles of 64, T 900 in 25 slices 19.9 : 17.4, T 1024 19.5 : 17.7, T 900 with the merge 21.8 : 20.7; one block of 208, which
+//   leaves the room to two sequences, T 928 B 1 17.9 : 15.4, B 2 13.8 : 15.5).
+Instance choose(int B, int T, int nb, int bs, int var, size_t room) {
   const Instance none = {nullptr, 0, 0, 0, 0}, in = find_instance(bs, var);
   if (!in.kernel) return none;
   if (in.mt == 1 || bs < 208 || bs > 256) return worth(B, T, nb, bs, var, in) ? in : none;
@@ -164,13 +165,14 @@ Instance choose(int B, int T, int nb, int bs, int var) {
             G2 = pick_slices(B * nb, n2, in.per_cu * 256, FWD_TILE_SLICES), r1 = (n1 + G1 - 1) / G1, r2 = (n2 + G2 - 1) / G2;
   if (T <= 256) return worth_short(B, T, nb, bs, var) && (r1 == 1 || (r1 == 2 && (var == V_MERGE || var == V_MERGE_TANH || G1 >= 3))) ? one : none;
   if (!worth(B, T, nb, bs, var, in)) return none;
-  return r1 == 1 && G1 <= 25 && ((long long)B * nb * n1 <= 256 || r2 > 1) ? one : in;
+  if (r1 > 1 || ((long long)B * nb * n1 > 256 && r2 == 1)) return in;
+  return make_plan(B, T, nb, bs, var == V_PACKED, one, 256, room).G == G1 ? one : in;
 }
 // Of short calls the whole plan is asked for: the second gate's weights and up to some MB of records (10 blocks of 256, B 1 T 256 2.6 MB of weights
 // and 1.3 of records; 16 blocks, B 16 T 64 8.4 and 4.2).
 constexpr int SHORT = 256;
 size_t bytes(int B, int T, int nb, int bs, int var, size_t room) {
-  const Instance in = choose(B, T, nb, bs, var);
+  const Instance in = choose(B, T, nb, bs, var, room);
   if (!in.kernel) return 0;
   if (T <= SHORT) room = ~(size_t)0;
   // (a size asked for where no card is visible must do on one: the whole chip's slices are the most there can be)
@@ -195,7 +197,7 @@ bool forward_tile_supported(const Problem &p, bool bf, size_t asked) {
 }
 
 hipError_t launch_forward_tile(const Problem &p, size_t asked, hipStream_t s) {
-  const Instance in = choose(p.B, p.T, p.nb, p.bs, variant(p));
+  const Instance in = choose(p.B, p.T, p.nb, p.bs, variant(p), asked);
   const Plan q = make_plan(p.B, p.T, p.nb, p.bs, p.reset, in, compute_units(), p.T <= SHORT ? ~(size_t)0 : asked);
   char *ws = (char *)p.ws;
   hipError_t e;

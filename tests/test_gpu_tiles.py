@@ -542,9 +542,10 @@ def test_short_forward_takes_the_faster_kernel(B, T, bs, nb, how, tiles):
 
 @pytest.mark.parametrize("T,bs,nb", [(832, 256, 8), (1024, 208, 1), (900, 240, 4)])
 @pytest.mark.parametrize("merge", [False, True])
-def test_tiles_of_32_steps_up_to_25_slices(T, bs, nb, merge):
-    """Past 25 slices a sequence goes in tiles of 64 steps: the bits of a call whose slices are capped at the number of those, which the
-    smaller tiles could only walk in two rounds (the state is rounded where it enters a tile)."""
+def test_tiles_of_32_steps_in_one_round(T, bs, nb, merge):
+    """Where the room makes the plan give up slices, and one round of tiles of 32 steps becomes two, a sequence goes in tiles of 64: the bits
+    of a call whose slices are capped at the number of those, which the smaller tiles could only walk in two rounds, too (the state is
+    rounded where it enters a tile)."""
     import torch
     import paper_2402_19427_amd as R
     rn = runner()
