@@ -70,9 +70,9 @@ hipError_t launch_prep(const Problem &p, int nct, u32x4 *wg, u32x4 *wd, hipStrea
 }
 
 int tiles_of(int hs) { return (hs + 31) / 32; }
-// Blocks of 80 to 128 channels, for which there are instances, at any alignment. Sequences of 2^31 bytes in fp32 and more stay with the
-// passes, which nothing else of these widths runs at such lengths. Not for their speed: 16 blocks of 128, T 131072, forward 1.62 ms in tiles and
-// 3.45 in passes, backward 4.26 and 8.46.
+// Blocks of 80 to 128 channels, for which there are instances, at any alignment. Sequences of 2^31 bytes in fp32 and more run in passes as they did
+// before there were tiles, though nothing here stands against them: 16 blocks of 128, T 131072, forward 1.62 ms in tiles and 3.45 in passes,
+// backward 4.26 and 8.46.
 bool shape_ok(int B, int T, int D, int hs) {
   return (size_t)T * D * 4 < ((size_t)1 << 31) && hs % 16 == 0 && hs > 64 && hs <= 128 && T >= 1 && (size_t)D * 2 * 64 < ((size_t)1 << 31) && (long long)B * ((T + 31) / 32) < ((long long)1 << 28);
 }

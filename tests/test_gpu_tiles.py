@@ -87,9 +87,10 @@ def least_room(runs, least, most):
     return hi * 256
 
 
-@pytest.mark.parametrize("B,T,bs,nb", [(1, 16384, 256, 1), (1, 16448, 256, 1), (8, 2100, 240, 1), (3, 1000, 352, 1), (12, 300, 512, 1),
-                                       (1, 900, 160, 3), (1, 700, 112, 1), (4, 300, 128, 8), (2, 500, 192, 4), (3, 200, 320, 2), (3, 800, 288, 1), (2, 300, 256, 2)])
-@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("B,T,bs,nb,packed", [
+    (1, 16384, 256, 1, False), (1, 16448, 256, 1, False), (8, 2100, 240, 1, False), (3, 1000, 352, 1, False), (12, 300, 512, 1, False),
+    (1, 900, 160, 3, False), (1, 700, 112, 1, False), (4, 300, 128, 8, False), (2, 500, 192, 4, False), (3, 200, 320, 2, False),
+    (3, 800, 288, 1, False), (2, 300, 256, 2, False), (1, 16384, 256, 1, True), (2, 300, 256, 2, True)])
 def test_weight_gradients_in_slices(B, T, bs, nb, packed):
     """Tiles of half and of all columns of a block, in as many slices of the stages as pay (the reported workspace) and in fewer, down to
     those of the smallest workspace in which the tiles run. Half-precision adjoints and inputs (11 bits): 2^-6 as above; sums in another
@@ -97,8 +98,6 @@ def test_weight_gradients_in_slices(B, T, bs, nb, packed):
     import paper_2402_19427_amd as R
     import torch
     rn = runner()
-    if packed and bs != 256:
-        pytest.skip("packed rows of other blocks run on the general kernels")
     D, act = bs * nb, "bf16"
     inp = gen.make_inputs(B, T, D, nb, act=act, seed=T + bs, dy=True, bias=True)
     dp, q = rn.DeviceProblem(inp, B, T, D, nb, act), f64(inp)
