@@ -49,6 +49,10 @@ struct CgTileArgs {
 // accesses of any alignment: the same values in the same places, so that results do not depend on where the tensors lie. What is not in
 // flight while the tile in front is worked on costs 15 - 25 % (10 blocks of 128, B 8 T 2048: forward 146 us on the grid, 166 eight bytes off it,
 // 186 two bytes off it, backward 394, 437 and 463; in passes 307 - 316 and 790).
+// The kernels take it as AT_ANY in their second argument, so that the aligned ones' names stay as short as they are: a third argument's
+// letters move their code by 256 bytes in its object, and the same instructions then take up to 1.4 % longer (forward and backward,
+// 10 blocks of 128, B 8 T 2048: 581 us, 574 where they are; on one of three cards 541 either way).
+constexpr int AT_ANY = 16;
 template <int NCT, bool ANY>
 struct Wave {
   static constexpr int NKS = 4 * NCT;

@@ -6,7 +6,7 @@ namespace cgt {
 
 CgInstance cg_instance_bwd(int nct, bool any) {
   CgInstance in = cg_instance_fwd(nct, any);
-  in.bwd = any ? cg_instance_bwd_any(nct) : nct == 3 ? (const void *)cg_bwd_tile_kernel<3, 4, false> : (const void *)cg_bwd_tile_kernel<4, 4, false>;
+  in.bwd = any ? cg_instance_bwd_any(nct) : nct == 3 ? (const void *)cg_bwd_tile_kernel<3, 4> : (const void *)cg_bwd_tile_kernel<4, 4>;
   return in;
 }
 

@@ -11,10 +11,11 @@
 namespace rglru {
 namespace cgt {
 
-template <int NCT, int PD, bool ANY>
+template <int NCT, int HOW>
 __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) cg_bwd_tile_kernel(CgTileArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  typedef Wave<NCT, ANY> Wv;
+  constexpr int PD = HOW % AT_ANY;
+  typedef Wave<NCT, (HOW >= AT_ANY)> Wv;
   constexpr int NKS = Wv::NKS;
   const unsigned id = xcd_id();
   if (id >= a.total) return;

@@ -10,10 +10,11 @@ namespace cgt {
 
 constexpr int M_AGG = 0, M_BAGG = 1, M_Y = 2;
 
-template <int NCT, int MODE, bool ANY>
+template <int NCT, int HOW>
 __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) cg_tile_kernel(CgTileArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  typedef Wave<NCT, ANY> Wv;
+  constexpr int MODE = HOW % AT_ANY;
+  typedef Wave<NCT, (HOW >= AT_ANY)> Wv;
   constexpr int NKS = Wv::NKS;
   const unsigned id = xcd_id();
   if (id >= a.total) return;
@@ -201,7 +202,8 @@ __global__ void __launch_bounds__(NCT * 64) __attribute__((amdgpu_waves_per_eu(2
 
 template <int NCT, bool ANY>
 CgInstance fwd_instance() {
-  return {(const void *)cg_tile_kernel<NCT, M_AGG, ANY>, (const void *)cg_tile_kernel<NCT, M_BAGG, ANY>, (const void *)cg_tile_kernel<NCT, M_Y, ANY>,
+  constexpr int at = ANY ? AT_ANY : 0;
+  return {(const void *)cg_tile_kernel<NCT, M_AGG + at>, (const void *)cg_tile_kernel<NCT, M_BAGG + at>, (const void *)cg_tile_kernel<NCT, M_Y + at>,
           nullptr, NCT};
 }
 

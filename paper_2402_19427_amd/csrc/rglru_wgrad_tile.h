@@ -148,8 +148,9 @@ hipError_t launch(const WgradArgs &a, hipStream_t s) {
   hipLaunchKernelGGL((tile_wgrad_kernel<PARTS, N>), dim3(grid8(a.total)), dim3(256), (Wg<PARTS, N>::LDS), s, a);
   return hipGetLastError();
 }
-// tiles of 2 and 3 column blocks, in an object of their own (rglru_wgrad_b.hip): in one with the others, all kernels of the complex-gated forward and
-// backward, code for code the same, ran 1 - 2 % slower (16 blocks of 128, T 2771 208 -> 212 us)
+// Tiles of 2 and 3 column blocks, in an object of their own (rglru_wgrad_b.hip): in one with the others they move those, and the complex-gated
+// forward and backward, whose own instructions are the same, took 214 us instead of 212 (16 blocks of 128, B 1 T 2771; 210 and 204 on another
+// card, 197 either way on a third).
 hipError_t launch_small(int n, const WgradArgs &a, hipStream_t s);
 
 }  // namespace wgrad
