@@ -24,9 +24,12 @@ Shape shape(int ra, int cb, int parts, bool half) {
 // 0.9 us + 0.8 per 32 columns and takes 0.23 us + 0.025 per 32 columns for a stage, or all together as long as the operands need,
 // 0.08 us for a MB of them and 0.02 for a MB that comes to a workgroup, more where workgroups are fewer than compute units; the final sums
 // read 1 MB in 0.16 us (least squares over 7000 calls: 112 - 512 channels, 1 - 16 blocks, 1 - 2048 stages, 1 - 64 slices, tiles of all and of half the
-// columns; what it takes is on average 0.6 %, at most 5 %, slower than the best of them). us of the backward, so : with as many slices as a fixed start of 12 us per workgroup pays for and halves
-// from 224 channels on only : with tiles of 256 x 128 and slices of 8 stages and more: one block of 208, B 18 T 273 51 : 62 : 50; one of
-// 192, T 4096 97 : 119 : 103; two of 160, B 16 T 59 31 : 41 : 34; 16 of 128, T 512 33 : 38 : 35; 10 of 192, T 156 33 : 40 : 35.
+// columns; what it takes is on average 0.6 %, at most 5 %, slower than the best of them). us of the backward, so : with as many slices as a
+// fixed start of 12 us per workgroup pays for, and halves from 224 channels on only : with tiles of 256 x 128 and slices of 8 stages and more:
+// one block of 208, B 18 T 273 51 : 62 : 50; one of 192, T 4096 97 : 119 : 103; two of 160, B 16 T 59 31 : 41 : 34; 16 of 128, T 512 33 : 38 :
+// 35; 10 of 192, T 156 33 : 40 : 35.
+// Against the second of these rules at 409 sizes: 3.9 % faster on average, more than 1 % faster at 250 and 1 - 3.4 % slower at 10, the worst of them 10
+// and 16 blocks of 208 or 256 with 16 stages (16 of 256: 2 slices 56.4, 4 54.6; forward and backward of B 1 T 357 68.2, 67.4 before).
 long long cost(const Shape &q, int nst, int nb, int ra, int cb, int S, int per) {
   const long long tiles = (long long)nb * q.njt * q.nkt, rounds = (tiles * S + 255) / 256, KB = ((long long)nb * ra * cb * S) >> 8;
   const long long all = ((long long)nb * (ra + cb) * nst) >> 4, moved = (tiles * (256 + 32 * q.n) * nst) >> 4;   // KB
